@@ -141,7 +141,7 @@ def traffic_from_profiles(kernel_src_hash, workload, kernel):
 def kernel_source_hash():
     import hashlib
     h = hashlib.sha256()
-    for name in ("kernels.hip", "ssj_device.h"):
+    for name in ("kernels.hip", "merge_device.h", "ssj_device.h"):
         with open(os.path.join(ROOT, "paper_1812_09141_amd", "csrc", name), "rb") as f:
             h.update(f.read())
     return h.hexdigest()

@@ -275,10 +275,15 @@ int ssj_verify_groups_batch_device(ssj_ctx* ctx, const ssj_coll* coll_r, const s
  * ssj_candidates_device writes the candidates themselves (*d_count: their
  * number, possibly above out_cap; then out_cap of them are written);
  * ssj_join_device verifies them into d_out / d_count like
- * ssj_verify_device; ssj_join does the same with host output buffers.  All
- * three synchronise the stream three times to size their buffers (the
- * prefix index, the probe work items and the candidate count) and share the
- * context's device scratch.
+ * ssj_verify_device; ssj_join does the same with host output buffers.  The
+ * joins verify each pair as a probe meets it, without a list of candidates in
+ * between (positional has no influence on them then); a join whose probes
+ * meet more than 2^31 - 1 list entries is run as candidates, then
+ * verification.  ssj_candidates_device synchronises the stream three times to
+ * size its buffers (the prefix index, the probe work items and the candidate
+ * count), ssj_join_device waits once, for the number of entries met, or not
+ * at all where the sets have at most 65,536 prefix tokens together.  All
+ * three share the context's device scratch.
  */
 int ssj_candidates_device(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den,
                           int positional, ssj_pair* d_out, int64_t out_cap, int64_t* d_count,

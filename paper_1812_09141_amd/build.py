@@ -9,7 +9,7 @@ ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libssj.so")
 SOURCES = [os.path.join(CSRC, "kernels.hip"), os.path.join(CSRC, "filter.hip"),
-           os.path.join(CSRC, "runtime.hip")]
+           os.path.join(CSRC, "join.hip"), os.path.join(CSRC, "runtime.hip")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 

@@ -26,6 +26,7 @@
 #include "ssj.h"
 #include "ssj_device.h"
 #include "filter.h"
+#include "join.h"
 
 namespace {
 
@@ -58,6 +59,8 @@ constexpr size_t kBytesPerPair = 8 + 8 + 4 * ssj::kQueues;
 // buffers of kRingPiece pairs, at most kMaxPieces pieces per device batch
 constexpr int64_t kRingPiece = (int64_t)1 << 20;
 constexpr int64_t kMaxPieces = 64;
+// pairs that ssj_join copies along with the count
+constexpr int64_t kEarlyPairs = 4096;
 // a stream slot may always hold this many pairs, whatever the budget leaves
 constexpr int64_t kSlotFloor = 1024;
 constexpr int64_t kSlotResults = (int64_t)1 << 16;  // pinned result pairs per slot at start
@@ -203,6 +206,9 @@ struct ssj_coll {
     int64_t n_tokens = 0;
     int64_t max_len = 0;
     uint64_t dev_bytes = 0;  // device bytes of its tokens and set records
+    bool size_sorted = true;   // set sizes do not decrease with the id
+    uint32_t max_token = 0;
+    std::vector<std::pair<uint32_t, uint32_t>> sizes;  // set sizes that occur, with the number of sets
     mutable std::atomic<int> inflight{0};  // stream requests not yet finished
 };
 
@@ -265,6 +271,20 @@ struct ssj_ctx {
                keys_cap = 0, keys2_cap = 0, probes_cap = 0, temp_cap = 0, items_cap = 0, istart_cap = 0,
                range_cap = 0;
     } flt;
+    // the whole self-join on the GPU (join.h), grown to the largest one
+    struct {
+        uint32_t *pre = nullptr, *keys = nullptr, *keys2 = nullptr, *vals2 = nullptr, *lo = nullptr, *first = nullptr,
+                 *spill_o = nullptr;
+        uint4 *ent = nullptr, *sent = nullptr, *spill = nullptr;
+        uint2* extra = nullptr;
+        unsigned char* temp = nullptr;
+        size_t pre_cap = 0, keys_cap = 0, keys2_cap = 0, vals2_cap = 0, lo_cap = 0, first_cap = 0, spill_o_cap = 0,
+               ent_cap = 0, sent_cap = 0, spill_cap = 0, extra_cap = 0, temp_cap = 0;
+        ssj::JoinCtl* ctl = nullptr;                 // zero between joins
+        unsigned long long* h_totals = nullptr;      // pinned
+        int2* h_pairs = nullptr;                     // pinned, kEarlyPairs: ssj_join's first pairs
+        hipEvent_t ev = nullptr;                     // the totals are on the host
+    } join;
     std::atomic<bool> failed{false};
     std::vector<ssj_coll*> colls;
     std::map<GraphKey, GraphEntry> graphs;
@@ -1147,6 +1167,32 @@ int ssj_init(const ssj_opts* opts, ssj_ctx** out) {
     return SSJ_OK;
 }
 
+}  // extern "C"
+
+namespace {
+
+// The set sizes that occur and how many sets have them (may throw bad_alloc).
+std::vector<std::pair<uint32_t, uint32_t>> set_sizes(const int64_t* offsets, int64_t n_sets, bool size_sorted) {
+    std::vector<std::pair<uint32_t, uint32_t>> r;
+    auto add = [&](uint32_t len) {
+        if (r.empty() || r.back().first != len) r.emplace_back(len, 0u);
+        ++r.back().second;
+    };
+    if (size_sorted) {
+        for (int64_t i = 0; i < n_sets; ++i) add((uint32_t)(offsets[i + 1] - offsets[i]));
+        return r;
+    }
+    std::vector<uint32_t> len((size_t)n_sets);
+    for (int64_t i = 0; i < n_sets; ++i) len[(size_t)i] = (uint32_t)(offsets[i + 1] - offsets[i]);
+    std::sort(len.begin(), len.end());
+    for (uint32_t v : len) add(v);
+    return r;
+}
+
+}  // namespace
+
+extern "C" {
+
 int ssj_shutdown(ssj_ctx* ctx) {
     if (!ctx) return SSJ_OK;
     (void)hipSetDevice(ctx->device);
@@ -1171,6 +1217,14 @@ int ssj_shutdown(ssj_ctx* ctx) {
                         (void*)ctx->flt.keys2, (void*)ctx->flt.probes, (void*)ctx->flt.temp,
                         (void*)ctx->flt.items, (void*)ctx->flt.istart, (void*)ctx->flt.range})
             if (q) (void)hipFree(q);
+        for (void* q : {(void*)ctx->join.pre, (void*)ctx->join.keys, (void*)ctx->join.keys2, (void*)ctx->join.vals2,
+                        (void*)ctx->join.lo, (void*)ctx->join.first, (void*)ctx->join.spill_o, (void*)ctx->join.ent,
+                        (void*)ctx->join.sent, (void*)ctx->join.spill, (void*)ctx->join.extra,
+                        (void*)ctx->join.temp, (void*)ctx->join.ctl})
+            if (q) (void)hipFree(q);
+        if (ctx->join.h_totals) (void)hipHostFree(ctx->join.h_totals);
+        if (ctx->join.h_pairs) (void)hipHostFree(ctx->join.h_pairs);
+        if (ctx->join.ev) (void)hipEventDestroy(ctx->join.ev);
         if (ctx->d_count) (void)hipFree(ctx->d_count);
         if (ctx->h_count) (void)hipHostFree(ctx->h_count);
         if (ctx->copy_stream) (void)hipStreamSynchronize(ctx->copy_stream);
@@ -1210,6 +1264,8 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
     if (offsets[0] != 0 || offsets[n_sets] != n_tokens)
         return set_error(SSJ_EINVAL, "offsets[0] must be 0 and offsets[n_sets] == n_tokens");
     int64_t max_len = 0;
+    int32_t max_token = 0;
+    bool size_sorted = true;
     for (int64_t i = 0; i < n_sets; ++i) {
         const int64_t b = offsets[i], e = offsets[i + 1];
         if (e <= b) {
@@ -1223,15 +1279,19 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
                 return set_error(SSJ_EINVAL, "tokens of set " + std::to_string(i) +
                                                  " are not strictly increasing");
         }
+        size_sorted = size_sorted && (i == 0 || e - b >= b - offsets[i - 1]);
         max_len = std::max(max_len, e - b);
+        max_token = std::max(max_token, tokens[e - 1]);
     }
     // Device layout: every set starts on a 16-byte boundary (a multiple of 4
     // tokens), so a lane can read 4 consecutive tokens of a set with one
     // aligned 16-byte load; the slots after a set's end hold -1.
     std::vector<uint32_t> start;
     std::vector<int32_t> padded;
+    std::vector<std::pair<uint32_t, uint32_t>> sizes;
     uint64_t n_dev = 0;
     try {
+        sizes = set_sizes(offsets, n_sets, size_sorted);
         start.resize((size_t)std::max<int64_t>(n_sets, 1));
         for (int64_t i = 0; i < n_sets; ++i) {
             start[(size_t)i] = (uint32_t)n_dev;
@@ -1263,6 +1323,9 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
     c->n_sets = n_sets;
     c->n_tokens = n_tokens;
     c->max_len = max_len;
+    c->size_sorted = size_sorted;
+    c->max_token = (uint32_t)max_token;
+    c->sizes = std::move(sizes);
     int64_t* d_off = nullptr;
     uint32_t* d_start = nullptr;
     hipError_t e = hipSuccess;
@@ -1603,6 +1666,101 @@ int gpu_candidates(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_
     return SSJ_OK;
 }
 
+// A self-join of coll at t = t_num / t_den on st (join.h), its similar pairs
+// in d_out and their number in d_count.  *done: whether it was run; a join
+// whose probes meet more list entries than that path takes is left to the
+// general one (candidates, then verification), which refuses what is too
+// large.  The host waits for the totals only (and not at all where the number
+// of prefix entries alone bounds them); the probes run meanwhile.  With d_out
+// null the pairs go to ctx->d_out, grown to hold them (out_cap at most).
+// ctx->mu held.
+int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, int2* d_out, int64_t out_cap,
+             long long* d_count, hipStream_t st, bool* done) {
+    auto& J = ctx->join;
+    *done = false;
+    uint64_t m64 = 0;
+    for (const auto& s : coll->sizes)
+        m64 += (s.first - ((uint64_t)t_num * s.first + (uint64_t)t_den - 1) / (uint64_t)t_den + 1) * s.second;
+    if (coll->n_sets == 0 || m64 >= (1ull << 30)) return SSJ_OK;
+    const size_t m = (size_t)m64;
+    if (!J.ctl) {
+        HIP_OR_FAIL(ctx, hipHostMalloc((void**)&J.h_totals, 2 * sizeof(unsigned long long), hipHostMallocDefault));
+        HIP_OR_FAIL(ctx, hipEventCreateWithFlags(&J.ev, hipEventDisableTiming));
+        ssj::JoinCtl* ctl = nullptr;
+        HIP_OR_FAIL(ctx, hipMalloc((void**)&ctl, sizeof(ssj::JoinCtl)));
+        J.ctl = ctl;
+        HIP_OR_FAIL(ctx, hipMemset(J.ctl, 0, sizeof(ssj::JoinCtl)));
+        HIP_OR_FAIL(ctx, hipDeviceSynchronize());
+    }
+    ssj::JoinArgs a{};
+    a.sorted = coll->size_sorted && coll->max_len < (int64_t)ssj::kMaxFirst ? 1u : 0u;
+    HIP_OR_FAIL(ctx, grow(J.pre, J.pre_cap, (size_t)coll->n_sets + 1));
+    HIP_OR_FAIL(ctx, grow(J.keys, J.keys_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.keys2, J.keys2_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.vals2, J.vals2_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.ent, J.ent_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.sent, J.sent_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.lo, J.lo_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.first, J.first_cap, a.sorted ? (size_t)coll->max_len + 1 : 1));
+    HIP_OR_FAIL(ctx, grow(J.extra, J.extra_cap, ssj::join_extra_cap((uint32_t)m)));
+    HIP_OR_FAIL(ctx, grow(J.spill, J.spill_cap, ssj::kSpillCap));
+    HIP_OR_FAIL(ctx, grow(J.spill_o, J.spill_o_cap, ssj::kSpillCap));
+    a.heads = coll->d_heads;
+    a.tok = coll->d_tok;
+    a.n = (uint32_t)coll->n_sets;
+    a.m = (uint32_t)m;
+    a.key_bits = 1;
+    while (a.key_bits < 32 && (coll->max_token >> a.key_bits) != 0) ++a.key_bits;
+    a.num = (unsigned long long)t_num;
+    a.den = (unsigned long long)t_den;
+    overlap_rule(SSJ_SIM_JACCARD, t_num, t_den, a.req);
+    a.req.out = d_out;
+    a.req.cap = (unsigned long long)out_cap;
+    a.req.d_count = d_count;
+    a.pre = J.pre;
+    a.keys = J.keys;
+    a.keys2 = J.keys2;
+    a.vals2 = J.vals2;
+    a.ent = J.ent;
+    a.sent = J.sent;
+    a.lo = J.lo;
+    a.first = J.first;
+    a.extra = J.extra;
+    a.extra_cap = ssj::join_extra_cap((uint32_t)m);
+    a.spill = J.spill;
+    a.spill_o = J.spill_o;
+    a.ctl = J.ctl;
+    a.h_totals = J.h_totals;
+    size_t tb = 0;
+    HIP_OR_FAIL(ctx, ssj::join_index(a, nullptr, &tb, st));
+    HIP_OR_FAIL(ctx, grow(J.temp, J.temp_cap, std::max<size_t>(tb, 1)));
+    tb = J.temp_cap;
+    HIP_OR_FAIL(ctx, ssj::join_index(a, J.temp, &tb, st));
+    HIP_OR_FAIL(ctx, ssj::join_ranges(a, ctx->n_cu, st));
+    // m (m - 1) / 2 meetings at most
+    const uint64_t most = m64 * (m64 - 1) / 2;
+    const bool bounded = most <= ssj::kMaxMeets;
+    bool waited = bounded;
+    if (!bounded) HIP_OR_FAIL(ctx, hipEventRecord(J.ev, st));
+    if (!d_out && out_cap > 0) {
+        // at most as many pairs as meetings: their number is waited for only
+        // where the buffer would be a large one
+        uint64_t want = std::min<uint64_t>((uint64_t)out_cap, std::max<uint64_t>(most, 1));
+        if (want > (1u << 20)) {
+            HIP_OR_FAIL(ctx, bounded ? hipStreamSynchronize(st) : hipEventSynchronize(J.ev));
+            waited = true;
+            want = std::min<uint64_t>(want, std::min<uint64_t>(std::max<uint64_t>(J.h_totals[0], 1), ssj::kMaxMeets));
+        }
+        HIP_OR_FAIL(ctx, grow(ctx->d_out, ctx->out_cap, (size_t)want));
+        a.req.out = ctx->d_out;
+        a.req.cap = want;
+    }
+    HIP_OR_FAIL(ctx, ssj::join_probe(a, ctx->n_cu, st));
+    if (!waited) HIP_OR_FAIL(ctx, hipEventSynchronize(J.ev));
+    *done = bounded || ssj::join_fits(J.h_totals[0], J.h_totals[1], a.m);
+    return SSJ_OK;
+}
+
 int check_filter_args(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den) {
     int rc = check_ctx(ctx);
     if (rc != SSJ_OK) return rc;
@@ -1640,6 +1798,10 @@ int ssj_join_device(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t
     std::lock_guard<std::mutex> g(ctx->mu);
     HIP_OR_FAIL(ctx, hipSetDevice(ctx->device));
     hipStream_t st = (hipStream_t)hip_stream;
+    bool done = false;
+    if ((rc = gpu_join(ctx, coll, t_num, t_den, reinterpret_cast<int2*>(d_out), out_cap,
+                       reinterpret_cast<long long*>(d_count), st, &done)) != SSJ_OK || done)
+        return rc;
     int64_t n = 0;
     if ((rc = gpu_candidates(ctx, coll, t_num, t_den, positional != 0, st, &n)) != SSJ_OK) return rc;
     Req r{ctx->d_pairs, n, t_num, t_den, reinterpret_cast<int2*>(d_out), out_cap,
@@ -1656,18 +1818,36 @@ int ssj_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     std::lock_guard<std::mutex> g(ctx->mu);
     HIP_OR_FAIL(ctx, hipSetDevice(ctx->device));
     hipStream_t st = ctx->stream;
-    int64_t n = 0;
-    if ((rc = gpu_candidates(ctx, coll, t_num, t_den, positional != 0, st, &n)) != SSJ_OK) return rc;
-    HIP_OR_FAIL(ctx, grow(ctx->d_out, ctx->out_cap, (size_t)std::max<int64_t>(n, 1)));
-    Req r{ctx->d_pairs, n, t_num, t_den, ctx->d_out, n, ctx->d_count, SSJ_SIM_JACCARD};
-    if ((rc = enqueue_launch(ctx, coll, ctx->def, &r, 1, st, ctx->plan)) != SSJ_OK) return rc;
-    HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_count, ctx->d_count, sizeof(long long), hipMemcpyDeviceToHost, st));
+    bool done = false;
+    int64_t early = 0;  // pairs already on the host
+    if ((rc = gpu_join(ctx, coll, t_num, t_den, nullptr, out_cap, ctx->h_count, st, &done)) != SSJ_OK) return rc;
+    if (done) {
+        // the count is stored in pinned memory by the join's last kernel, and
+        // the first pairs come with it
+        if (out_cap > 0 && !ctx->join.h_pairs)
+            HIP_OR_FAIL(ctx, hipHostMalloc((void**)&ctx->join.h_pairs, kEarlyPairs * sizeof(int2),
+                                           hipHostMallocDefault));
+        early = std::min<int64_t>({kEarlyPairs, out_cap, (int64_t)ctx->out_cap});
+        if (early > 0)
+            HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->join.h_pairs, ctx->d_out, (size_t)early * sizeof(int2),
+                                            hipMemcpyDeviceToHost, st));
+    } else {
+        int64_t n = 0;
+        if ((rc = gpu_candidates(ctx, coll, t_num, t_den, positional != 0, st, &n)) != SSJ_OK) return rc;
+        HIP_OR_FAIL(ctx, grow(ctx->d_out, ctx->out_cap, (size_t)std::max<int64_t>(n, 1)));
+        Req r{ctx->d_pairs, n, t_num, t_den, ctx->d_out, n, ctx->d_count, SSJ_SIM_JACCARD};
+        if ((rc = enqueue_launch(ctx, coll, ctx->def, &r, 1, st, ctx->plan)) != SSJ_OK) return rc;
+        HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_count, ctx->d_count, sizeof(long long), hipMemcpyDeviceToHost, st));
+    }
     HIP_OR_FAIL(ctx, hipStreamSynchronize(st));
     const long long k = *ctx->h_count;
     if (k < 0) return set_error(SSJ_EDEVICE, "id error in generated candidates");
     const int64_t take = std::min<int64_t>(k, out_cap);
-    if (take > 0) {
-        HIP_OR_FAIL(ctx, hipMemcpyAsync(out, ctx->d_out, (size_t)take * 8, hipMemcpyDeviceToHost, st));
+    early = std::min(early, take);
+    if (early > 0) std::memcpy(out, ctx->join.h_pairs, (size_t)early * sizeof(int2));
+    if (take > early) {
+        HIP_OR_FAIL(ctx, hipMemcpyAsync(out + early, ctx->d_out + early, (size_t)(take - early) * 8,
+                                        hipMemcpyDeviceToHost, st));
         HIP_OR_FAIL(ctx, hipStreamSynchronize(st));
     }
     *out_n = k;
