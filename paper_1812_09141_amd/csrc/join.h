@@ -23,7 +23,9 @@ struct alignas(64) JoinCtl {
 
 constexpr uint32_t kUnitMeets = 2048;                        // meetings per work unit
 constexpr unsigned long long kMaxMeets = 0x7fffffffull;      // meetings that a join takes
-constexpr uint32_t kMaxFirst = 1u << 16;                     // sizes in the table of first entries
+constexpr uint32_t kSortTile = 4096;                         // entries per workgroup of the sort
+constexpr uint32_t kSortBits = 10;                           // most bits per pass
+constexpr uint32_t kLut = 1024;                              // coarse index of the set sizes
 constexpr uint32_t kSpillCap = 1u << 18;                     // cut-off merges that are queued
 
 // Whether the totals of a probe pass (meetings, meetings without the length
@@ -39,20 +41,34 @@ __host__ inline uint32_t join_extra_cap(uint32_t m) {
     return (uint32_t)((pairs < kMaxMeets ? pairs : kMaxMeets) / kUnitMeets) + 1u;
 }
 
+// Workgroups and passes of the sort of m entries by key_bits bits.
+__host__ inline uint32_t join_tiles(uint32_t m) { return (m + kSortTile - 1u) / kSortTile; }
+__host__ inline uint32_t join_passes(uint32_t key_bits) { return (key_bits + kSortBits - 1u) / kSortBits; }
+
 struct JoinArgs {
     const uint4* heads;   // set records of the collection
     const int32_t* tok;   // its tokens
     uint32_t n;           // sets
     uint32_t m;           // prefix entries of all sets
     uint32_t key_bits;    // bits of the largest token
-    uint32_t sorted;      // != 0: set sizes do not decrease with the id and first holds every size
+    // set sizes that do not decrease with the id: the sizes in ascending order,
+    // {first set, size, first token's index}, then {n}; else n_classes = 0
+    const uint4* classes;
+    uint32_t n_classes;
+    uint32_t lut_shift;   // (m - 1) >> lut_shift < kLut
+    uint4* cls;           // n_classes + 1: {first entry, first set, size, entries per set}
+    uint2* cls2;          // n_classes: {first token's index, first entry of the sets met}
+    uint32_t* lut;        // kLut
     unsigned long long num, den;  // t
     Request req;          // overlap rule, output (out, cap, d_count)
-    uint32_t* pre;        // n + 1: prefix entries of the sets before
-    uint32_t *keys, *keys2, *vals2;  // m each: tokens, sorted tokens, entry numbers in their order
-    uint4 *ent, *sent;    // m each: entries in set order, in token order
+    uint32_t* pre;        // n + 1: prefix entries of the sets before (n_classes = 0)
+    uint4* ent;           // m: entries in set order (n_classes = 0)
+    uint32_t* keys;       // m: tokens in set order
+    uint2* pairs[2];      // m each: {token, entry} on their way to token order
+    uint32_t* counts;     // 2^kSortBits at most x join_tiles(m)
+    uint32_t* totals;     // 2^kSortBits
+    uint4* sent;          // m: entries in token order
     uint32_t* lo;         // m: first list entry that the probe meets
-    uint32_t* first;      // first entry of the sets of at least this size
     uint2* extra;         // further units: group, first meeting
     uint32_t extra_cap;
     uint4* spill;         // kSpillCap: probe entry, list entry, merge state (i, j)
@@ -61,11 +77,10 @@ struct JoinArgs {
     unsigned long long* h_totals;  // pinned: meets, all
 };
 
-// Each call with d_temp null only sets *temp_bytes to the temporary storage
+// Index, ranges and work units; a.h_totals holds the totals once it has
+// finished.  With d_temp null it only sets *temp_bytes to the temporary storage
 // it needs.
-hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, hipStream_t st);
-// Ranges and work units; a.h_totals holds the totals once it has finished.
-hipError_t join_ranges(const JoinArgs& a, int n_cu, hipStream_t st);
+hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, int n_cu, hipStream_t st);
 // Probes, verification, count (nothing but the count -1 where the totals do
 // not fit join_fits).
 hipError_t join_probe(const JoinArgs& a, int n_cu, hipStream_t st);

@@ -16,16 +16,17 @@
 // overlap 1, which decides a pair that meets there first.  A pair that passes
 // is reported if no common token lies before i and j.
 //
-// With the set sizes in ascending order (the paper's layout) a probe's list
-// starts at the first set that is long enough, found through a table of the
-// first entry per size; in any other order the whole list is walked.
+// With the set sizes in ascending order (the paper's layout) the sets of one
+// size are consecutive and have as many entries each, so everything about an
+// entry follows from its number and a table of the sizes, and a probe's list
+// starts at the first set that is long enough.  In any other order an entry is
+// looked up, and the whole list is walked.
 //
 // Measured, whole joins on one MI355X, against a counting and a filling pass
 // over the lists, a list of candidates and its verification: 100,000 short
 // sets at t = 0.6 (3.1M meetings) 1,465 -> 272 us, 50,000 long sets at 0.7
 // 3,628 -> 319 us, a heavy tail of 500,000 sets at 0.75 (169M meetings) 13.4
 // -> 0.93 ms, 5,000 short sets with the results in host memory 220 -> 122 us.
-#include <rocprim/device/device_radix_sort.hpp>
 #include <rocprim/device/device_scan.hpp>
 #include <rocprim/iterator/counting_iterator.hpp>
 #include <rocprim/iterator/transform_iterator.hpp>
@@ -36,7 +37,10 @@
 namespace ssj {
 namespace {
 
-constexpr uint32_t kEntrySpan = 512;  // entries per wavefront of k_join_entries
+constexpr int kSortBlock = 512;                                    // threads of the entry and sort kernels
+constexpr uint32_t kSortWaves = (uint32_t)(kSortBlock / kWave);
+constexpr uint32_t kSortRows = kSortTile / (uint32_t)kSortBlock;   // items per thread
+constexpr uint32_t kEntrySpan = kSortTile / kSortWaves;            // entries per wavefront
 constexpr int kRangeBlock = 1024;
 constexpr uint32_t kStage = 256;      // staged output pairs per wavefront
 constexpr uint32_t kQueue = 2 * kWave;  // meetings waiting for their merge per wavefront
@@ -79,68 +83,285 @@ __device__ __forceinline__ uint32_t lane_u32(uint32_t v, int src) {
 
 __device__ __forceinline__ uint32_t bperm_u32(uint32_t v, uint32_t src) { return (uint32_t)bperm((int)v, (int)src); }
 
-// Entries in set order: token and {set, size, position, index of the next
-// token} of entry e.  A wavefront writes kEntrySpan consecutive entries, 64
-// at a time: it finds the set of its first entry by a 64-way search of pre,
-// and within 64 entries (of at most 64 sets, none of which is without
-// entries) every set marks where it begins and a running maximum gives every
-// lane its set.  Reads and writes are consecutive over the lanes; a thread per
-// set wrote the 2.0M entries of 50,000 long sets in 173 us.
-__global__ __launch_bounds__(kBlock) void k_join_entries(JoinArgs a) {
-    __shared__ uint32_t s_marks[kBlock];
-    const int lane = lane_id();
-    uint32_t* marks = s_marks + (threadIdx.x & ~63u);
-    const uint32_t wave = (blockIdx.x * kBlock + threadIdx.x) / kWave;
-    const uint32_t e_begin = wave * kEntrySpan;
-    if (e_begin >= a.m) return;
-    const uint32_t e_end = min(a.m, e_begin + kEntrySpan);
-    // the set holding e_begin: the largest x with pre[x] <= e_begin
-    uint32_t x0 = 0, hi = a.n;
-    while (hi - x0 > 1u) {
-        const uint32_t step = (hi - x0 + 63u) / 64u;
-        const uint32_t x = x0 + (uint32_t)lane * step;
-        const uint32_t c = (uint32_t)__popcll(ballot(x < hi && a.pre[min(x, a.n)] <= e_begin));
-        x0 += (c - 1u) * step;
-        hi = min(hi, x0 + step);
+// The sizes of a collection in ascending order: entries before the first set
+// of each size, entries per set, and the first entry of the sets that are long
+// enough for it (thr); and a coarse index of the sizes by entry number (the
+// size of every (1 << lut_shift)-th entry).  One workgroup.
+__global__ __launch_bounds__(kRangeBlock) void k_join_classes(JoinArgs a) {
+    constexpr int kWaves = kRangeBlock / kWave;
+    __shared__ uint32_t s_sum[kWaves];
+    const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
+    uint32_t carry = 0;
+    for (uint32_t b = 0; b < a.n_classes; b += kRangeBlock) {
+        const uint32_t c = b + threadIdx.x;
+        const bool in = c < a.n_classes;
+        const uint4 st = a.classes[in ? c : a.n_classes];
+        const uint32_t p = in ? st.y - needed(st.y, a.num, a.den) + 1u : 0u;
+        const uint32_t cnt = in ? (a.classes[c + 1u].x - st.x) * p : 0u;
+        const uint32_t incl = wave_add_scan(cnt, lane);
+        if (lane == kWave - 1) s_sum[w] = incl;
+        __syncthreads();
+        uint32_t before = carry;
+        for (int k = 0; k < kWaves; ++k) {
+            before += k < w ? s_sum[k] : 0u;
+            carry += s_sum[k];
+        }
+        if (in) a.cls[c] = make_uint4(before + incl - cnt, st.x, st.y, p);
+        __syncthreads();
     }
-    for (uint32_t kb = e_begin; kb < e_end; kb += kWave) {
-        const uint32_t xl = min(x0 + (uint32_t)lane, a.n - 1u);
-        const bool is_set = x0 + (uint32_t)lane < a.n;
-        const uint32_t at = a.pre[xl];
-        const uint4 h = a.heads[2 * xl];
-        marks[lane] = lane == 0 ? 1u : 0u;
+    if (threadIdx.x == 0) a.cls[a.n_classes] = make_uint4(carry, a.n, 0u, 1u);
+    __syncthreads();
+    for (uint32_t c = threadIdx.x; c < a.n_classes; c += kRangeBlock) {
+        const uint4 st = a.classes[c];
+        const uint32_t need = needed(st.y, a.num, a.den);
+        uint32_t lo = 0, hi = c;  // the first size >= need (need <= its own size)
+        while (lo < hi) {
+            const uint32_t mid = lo + (hi - lo) / 2u;
+            if (a.cls[mid].z < need)
+                lo = mid + 1u;
+            else
+                hi = mid;
+        }
+        a.cls2[c] = make_uint2(st.z, a.cls[lo].x);
+    }
+    for (uint32_t k = threadIdx.x; k < kLut; k += kRangeBlock) {
+        const uint32_t e = k << a.lut_shift;
+        if (e >= a.m) break;
+        uint32_t lo = 0, hi = a.n_classes;  // the last size that begins at or before e
+        while (hi - lo > 1u) {
+            const uint32_t mid = lo + (hi - lo) / 2u;
+            if (a.cls[mid].x <= e)
+                lo = mid;
+            else
+                hi = mid;
+        }
+        a.lut[k] = lo;
+    }
+}
+
+// Entry e of a collection with ascending sizes: {set, size, position, index of
+// the next token}; *thr receives the first entry that it meets.
+__device__ __forceinline__ uint4 entry_of(const JoinArgs& a, uint32_t e, uint32_t* thr) {
+    uint32_t c = a.lut[e >> a.lut_shift];
+    while (a.cls[c + 1u].x <= e) ++c;
+    const uint4 k = a.cls[c];
+    const uint2 k2 = a.cls2[c];
+    const uint32_t r = e - k.x, i = r / k.w, j = r - i * k.w;
+    *thr = k2.y;
+    return make_uint4(k.y + i, k.z, j, k2.x + i * ((k.z + 3u) & ~3u) + j + 1u);
+}
+
+// Adds the workgroup's digit counts to the matrix of counts, one row per
+// digit and one column per workgroup.
+__device__ __forceinline__ void store_counts(const JoinArgs& a, const uint32_t* hist, uint32_t digits) {
+    __syncthreads();
+    for (uint32_t d = threadIdx.x; d < digits; d += kSortBlock)
+        a.counts[(size_t)d * gridDim.x + blockIdx.x] = hist[d];
+}
+
+// Tokens of the entries in set order, and the digit counts of the first sort
+// pass.  SORTED: from the table of sizes.  Otherwise each wavefront walks
+// kEntrySpan consecutive entries 64 at a time: it finds the set of its first
+// entry by a 64-way search of pre, and within 64 entries (of at most 64 sets,
+// none of which is without entries) every set marks where it begins and a
+// running maximum gives every lane its set; the entries are stored too.  Reads
+// and writes are consecutive over the lanes either way (a thread per set wrote
+// the 2.0M entries of 50,000 long sets in 173 us; now 12 us).
+template <bool SORTED>
+__global__ __launch_bounds__(kSortBlock) void k_join_entries(JoinArgs a, uint32_t digits) {
+    extern __shared__ uint32_t s_hist[];
+    __shared__ uint32_t s_marks[SORTED ? 1 : kSortBlock];
+    for (uint32_t d = threadIdx.x; d < digits; d += kSortBlock) s_hist[d] = 0u;
+    __syncthreads();
+    const int lane = lane_id();
+    if constexpr (SORTED) {
+#pragma unroll 2
+        for (uint32_t k = 0; k < kSortRows; ++k) {
+            const uint32_t e = blockIdx.x * kSortTile + k * kSortBlock + threadIdx.x;
+            if (e >= a.m) break;
+            uint32_t thr;
+            const uint32_t key = (uint32_t)a.tok[entry_of(a, e, &thr).w - 1u];
+            a.keys[e] = key;
+            atomicAdd(&s_hist[key & (digits - 1u)], 1u);
+        }
+    } else {
+        uint32_t* marks = s_marks + (threadIdx.x & ~63u);
+        const uint32_t e_begin = blockIdx.x * kSortTile + threadIdx.x / kWave * kEntrySpan;
+        const uint32_t e_end = min(a.m, e_begin + kEntrySpan);
+        // the set holding e_begin: the largest x with pre[x] <= e_begin
+        uint32_t x0 = 0, hi = e_begin < e_end ? a.n : 0u;
+        while (hi > x0 + 1u) {
+            const uint32_t step = (hi - x0 + 63u) / 64u;
+            const uint32_t x = x0 + (uint32_t)lane * step;
+            const uint32_t c = (uint32_t)__popcll(ballot(x < hi && a.pre[min(x, a.n)] <= e_begin));
+            x0 += (c - 1u) * step;
+            hi = min(hi, x0 + step);
+        }
+        for (uint32_t kb = e_begin; kb < e_end; kb += kWave) {
+            const uint32_t xl = min(x0 + (uint32_t)lane, a.n - 1u);
+            const bool is_set = x0 + (uint32_t)lane < a.n;
+            const uint32_t at = a.pre[xl];
+            const uint4 h = a.heads[2 * xl];
+            marks[lane] = lane == 0 ? 1u : 0u;
+            wave_sync();
+            if (is_set && at >= kb && at - kb < (uint32_t)kWave) marks[at - kb] = (uint32_t)lane + 1u;
+            wave_sync();
+            const uint32_t o = wave_max_scan(marks[lane], lane) - 1u;
+            wave_sync();
+            const uint32_t e = kb + (uint32_t)lane;
+            const uint32_t len = bperm_u32(h.y, o), start = bperm_u32(h.x, o), j = e - bperm_u32(at, o);
+            if (e < e_end) {
+                const uint32_t key = (uint32_t)a.tok[start + j];
+                a.keys[e] = key;
+                a.ent[e] = make_uint4(x0 + o, len, j, start + j + 1u);
+                atomicAdd(&s_hist[key & (digits - 1u)], 1u);
+            }
+            // the set of the next 64's first entry (64 sets from it hold them all)
+            x0 += lane_u32(o, kWave - 1);
+            if (x0 + 1u < a.n && a.pre[x0 + 1u] <= kb + kWave) ++x0;
+        }
+    }
+    store_counts(a, s_hist, digits);
+}
+
+// The sort of the entries by token: least significant digit first, digits of
+// up to 10 bits (two passes for up to 1M tokens), each pass a count per digit
+// and tile of kSortTile entries, a scan of each digit's row, and a scatter.
+// The entries start in set order and every pass keeps the order of equal
+// digits, so a list ends up in set order.  Bound by the scattered 8-byte
+// writes and by the launches; 2.0M entries, 20 bits: 107 us with rocPRIM's
+// radix sort (three passes of 8 bits), 45 us so.
+__global__ __launch_bounds__(kSortBlock) void k_sort_count(JoinArgs a, const uint2* __restrict__ in, uint32_t shift,
+                                                           uint32_t digits) {
+    extern __shared__ uint32_t s_hist[];
+    for (uint32_t d = threadIdx.x; d < digits; d += kSortBlock) s_hist[d] = 0u;
+    __syncthreads();
+    uint32_t key[kSortRows];
+#pragma unroll
+    for (uint32_t k = 0; k < kSortRows; ++k) {
+        const uint32_t e = blockIdx.x * kSortTile + k * kSortBlock + threadIdx.x;
+        key[k] = in[min(e, a.m - 1u)].x;
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kSortRows; ++k) {
+        const uint32_t e = blockIdx.x * kSortTile + k * kSortBlock + threadIdx.x;
+        if (e < a.m) atomicAdd(&s_hist[(key[k] >> shift) & (digits - 1u)], 1u);
+    }
+    store_counts(a, s_hist, digits);
+}
+
+// One workgroup per digit: its row of counts becomes the exclusive sums, its
+// total goes to totals.
+__global__ __launch_bounds__(kBlock) void k_sort_rows(JoinArgs a, uint32_t tiles) {
+    constexpr int kWaves = kBlock / kWave;
+    __shared__ uint32_t s_sum[kWaves];
+    const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
+    uint32_t* row = a.counts + (size_t)blockIdx.x * tiles;
+    uint32_t carry = 0;
+    for (uint32_t b = 0; b < tiles; b += kBlock) {
+        const uint32_t k = b + threadIdx.x;
+        const uint32_t v = k < tiles ? row[k] : 0u;
+        const uint32_t incl = wave_add_scan(v, lane);
+        if (lane == kWave - 1) s_sum[w] = incl;
+        __syncthreads();
+        uint32_t before = carry;
+        for (int q = 0; q < kWaves; ++q) {
+            before += q < w ? s_sum[q] : 0u;
+            carry += s_sum[q];
+        }
+        if (k < tiles) row[k] = before + incl - v;
+        __syncthreads();
+    }
+    if (threadIdx.x == 0) a.totals[blockIdx.x] = carry;
+}
+
+// Moves a tile's entries to their places.  A wavefront ranks its entries 64 at
+// a time: the lanes with the same digit find each other by one ballot per
+// digit bit, and the wavefront's count of the digit so far (LDS, written by
+// the last of them) comes before.  FIRST: the tokens of the entries in set
+// order (entry e is item e).
+template <bool FIRST>
+__global__ __launch_bounds__(kSortBlock) void k_sort_scatter(JoinArgs a, const uint2* __restrict__ in,
+                                                             uint2* __restrict__ out, uint32_t shift, uint32_t bits) {
+    extern __shared__ uint32_t s_cnt[];  // [kSortWaves][digits]
+    __shared__ uint32_t s_sum[kSortWaves];
+    const uint32_t digits = 1u << bits;
+    const int lane = lane_id();
+    const uint32_t w = threadIdx.x / kWave;
+    for (uint32_t k = threadIdx.x; k < digits * kSortWaves; k += kSortBlock) s_cnt[k] = 0u;
+    uint2 item[kSortRows];
+    const uint32_t e0 = blockIdx.x * kSortTile + w * kEntrySpan + (uint32_t)lane;
+#pragma unroll
+    for (uint32_t k = 0; k < kSortRows; ++k) {
+        const uint32_t e = min(e0 + k * kWave, a.m - 1u);
+        item[k] = FIRST ? make_uint2(a.keys[e], e) : in[e];
+    }
+    __syncthreads();
+    uint32_t* cnt = s_cnt + w * digits;
+    uint32_t rank[kSortRows];
+#pragma unroll
+    for (uint32_t k = 0; k < kSortRows; ++k) {
+        const bool valid = e0 + k * kWave < a.m;
+        const uint32_t d = (item[k].x >> shift) & (digits - 1u);
+        unsigned long long peers = ballot(valid);
+        for (uint32_t b = 0; b < bits; ++b) {
+            const bool one = ((d >> b) & 1u) != 0u;
+            const unsigned long long m = ballot(one);
+            peers &= one ? m : ~m;
+        }
+        const uint32_t before = cnt[d];
+        const uint32_t among = mbcnt(peers), n = (uint32_t)__popcll(peers);
+        rank[k] = before + among;
         wave_sync();
-        if (is_set && at >= kb && at - kb < (uint32_t)kWave) marks[at - kb] = (uint32_t)lane + 1u;
+        if (valid && among == n - 1u) cnt[d] = before + n;
         wave_sync();
-        const uint32_t o = wave_max_scan(marks[lane], lane) - 1u;
-        wave_sync();
-        const uint32_t e = kb + (uint32_t)lane;
-        const uint32_t len = bperm_u32(h.y, o), start = bperm_u32(h.x, o), j = e - bperm_u32(at, o);
-        if (e < e_end) {
-            a.keys[e] = (uint32_t)a.tok[start + j];
-            a.ent[e] = make_uint4(x0 + o, len, j, start + j + 1u);
-            if (a.sorted && j == 0u) {
-                // the first set of every size above its predecessor's
-                const uint32_t x = x0 + o;
-                for (uint32_t s = x ? a.heads[2 * (x - 1u)].y + 1u : 0u; s <= len; ++s) a.first[s] = e;
+    }
+    __syncthreads();
+    // the digit's place: smaller digits, earlier tiles, earlier wavefronts
+    uint32_t carry = 0;
+    for (uint32_t b = 0; b < digits; b += kSortBlock) {
+        const uint32_t d = b + threadIdx.x;
+        const uint32_t v = d < digits ? a.totals[d] : 0u;
+        const uint32_t incl = wave_add_scan(v, lane);
+        if (lane == kWave - 1) s_sum[w] = incl;
+        __syncthreads();
+        uint32_t before = carry;
+        for (uint32_t q = 0; q < kSortWaves; ++q) {
+            before += q < w ? s_sum[q] : 0u;
+            carry += s_sum[q];
+        }
+        if (d < digits) {
+            uint32_t at = before + incl - v + a.counts[(size_t)d * gridDim.x + blockIdx.x];
+            for (uint32_t q = 0; q < kSortWaves; ++q) {
+                const uint32_t n = s_cnt[q * digits + d];
+                s_cnt[q * digits + d] = at;
+                at += n;
             }
         }
-        // the set of the next 64's first entry (64 sets from it hold them all)
-        x0 += lane_u32(o, kWave - 1);
-        if (x0 + 1u < a.n && a.pre[x0 + 1u] <= kb + kWave) ++x0;
+        __syncthreads();
+    }
+#pragma unroll
+    for (uint32_t k = 0; k < kSortRows; ++k) {
+        const uint32_t d = (item[k].x >> shift) & (digits - 1u);
+        if (e0 + k * kWave < a.m) out[cnt[d] + rank[k]] = item[k];
     }
 }
 
 // Smallest list position from which on every entry before q is of q's list
 // (token w) and not below entry number thr: doubling steps back from q, then
-// bisection.  Within a list the entry numbers ascend.
-__device__ __forceinline__ uint32_t list_begin(const uint32_t* __restrict__ keys, const uint32_t* __restrict__ vals,
+// bisection.  Within a list the entry numbers ascend.  tile holds the
+// list's entries from position b on (most lists begin there).
+__device__ __forceinline__ uint32_t list_begin(const uint2* __restrict__ list, const uint2* tile, uint32_t b,
                                                uint32_t q, uint32_t w, uint32_t thr) {
     uint32_t good = q, step = 1, bad = 0;
     bool found = false;  // bad is outside
+    auto inside = [&](uint32_t c) {
+        const uint2 v = c >= b ? tile[c - b] : list[c];
+        return v.x == w && v.y >= thr;
+    };
     while (good > 0u) {
         const uint32_t c = good >= step ? good - step : 0u;
-        if (keys[c] == w && vals[c] >= thr) {
+        if (inside(c)) {
             good = c;
             step *= 2u;
         } else {
@@ -151,7 +372,7 @@ __device__ __forceinline__ uint32_t list_begin(const uint32_t* __restrict__ keys
     }
     while (found && good - bad > 1u) {
         const uint32_t mid = bad + (good - bad) / 2u;
-        if (keys[mid] == w && vals[mid] >= thr)
+        if (inside(mid))
             good = mid;
         else
             bad = mid;
@@ -175,8 +396,10 @@ __device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v)
 // one atomic per workgroup and pass.  The last workgroup to finish stores the
 // totals for the host (atomics only, each one complete before the next is
 // issued, so no fence is needed).
-__global__ __launch_bounds__(kRangeBlock) void k_join_ranges(JoinArgs a) {
+template <bool SORTED>
+__global__ __launch_bounds__(kRangeBlock) void k_join_ranges(JoinArgs a, const uint2* __restrict__ list) {
     constexpr int kWaves = kRangeBlock / kWave;
+    __shared__ uint2 s_tile[kRangeBlock + 1];
     __shared__ uint32_t s_extra[kWaves];
     __shared__ uint32_t s_base;
     __shared__ unsigned long long s_tot[2 * kWaves];
@@ -185,16 +408,19 @@ __global__ __launch_bounds__(kRangeBlock) void k_join_ranges(JoinArgs a) {
     for (uint32_t b = blockIdx.x * kRangeBlock; b < a.m; b += gridDim.x * kRangeBlock) {
         const uint32_t q = b + threadIdx.x;
         unsigned long long cnt = 0ull;
+        const uint2 it = list[min(q, a.m - 1u)];
+        s_tile[threadIdx.x] = it;
+        if (threadIdx.x == kRangeBlock - 1) s_tile[kRangeBlock] = list[min(q + 1u, a.m - 1u)];
+        __syncthreads();
         if (q < a.m) {
-            const uint32_t key = a.keys2[q];
-            const uint4 en = a.ent[a.vals2[q]];
+            uint32_t thr = 0;
+            const uint4 en = SORTED ? entry_of(a, it.y, &thr) : a.ent[it.y];
             a.sent[q] = en;
-            const uint32_t thr = a.sorted ? a.first[needed(en.y, a.num, a.den)] : 0u;
-            const uint32_t lo = list_begin(a.keys2, a.vals2, q, key, thr);
+            const uint32_t lo = list_begin(list, s_tile, b, q, it.x, thr);
             a.lo[q] = lo;
             cnt = q - lo;
-            if (q + 1u == a.m || a.keys2[q + 1u] != key) {
-                const unsigned long long len = q - list_begin(a.keys2, a.vals2, q, key, 0u) + 1ull;
+            if (q + 1u == a.m || s_tile[threadIdx.x + 1].x != it.x) {
+                const unsigned long long len = q - list_begin(list, s_tile, b, q, it.x, 0u) + 1ull;
                 all += len * (len - 1ull) / 2ull;
             }
         }
@@ -443,37 +669,56 @@ __global__ void k_join_finalize(JoinArgs a) {
 
 }  // namespace
 
-hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, hipStream_t st) {
-    auto lengths = rocprim::make_transform_iterator(rocprim::counting_iterator<uint32_t>(0u),
-                                                    PrefixLength{a.heads, a.n, a.num, a.den});
-    size_t scan_bytes = *temp_bytes, sort_bytes = *temp_bytes;
-    auto scan = [&]() {
-        return rocprim::exclusive_scan(d_temp, scan_bytes, lengths, a.pre, 0u, (size_t)a.n + 1,
-                                       rocprim::plus<uint32_t>(), st);
-    };
-    // stable, and the entries come in set order: sorted by token alone they
-    // are sorted by (token, set)
-    auto sort = [&]() {
-        return rocprim::radix_sort_pairs(d_temp, sort_bytes, a.keys, a.keys2, rocprim::counting_iterator<uint32_t>(0u),
-                                         a.vals2, (size_t)a.m, 0u, a.key_bits, st);
-    };
-    hipError_t e = scan();
-    if (e != hipSuccess) return e;
-    if (!d_temp) {
-        if ((e = sort()) != hipSuccess) return e;
-        *temp_bytes = scan_bytes > sort_bytes ? scan_bytes : sort_bytes;
-        return hipSuccess;
+hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, int n_cu, hipStream_t st) {
+    hipError_t e = hipSuccess;
+    if (!a.n_classes) {
+        auto lengths = rocprim::make_transform_iterator(rocprim::counting_iterator<uint32_t>(0u),
+                                                        PrefixLength{a.heads, a.n, a.num, a.den});
+        e = rocprim::exclusive_scan(d_temp, *temp_bytes, lengths, a.pre, 0u, (size_t)a.n + 1,
+                                    rocprim::plus<uint32_t>(), st);
+        if (e != hipSuccess || !d_temp) return e;
+    } else {
+        if (!d_temp) {
+            *temp_bytes = 0;
+            return hipSuccess;
+        }
+        hipLaunchKernelGGL(k_join_classes, dim3(1), dim3(kRangeBlock), 0, st, a);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
     }
-    const uint32_t waves = (a.m + kEntrySpan - 1u) / kEntrySpan;
-    const uint32_t per = kBlock / kWave;
-    hipLaunchKernelGGL(k_join_entries, dim3((waves + per - 1u) / per), dim3(kBlock), 0, st, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    return sort();
-}
-
-hipError_t join_ranges(const JoinArgs& a, int n_cu, hipStream_t st) {
-    const uint32_t b = (a.m + kRangeBlock - 1u) / kRangeBlock, most = 2u * (uint32_t)n_cu;
-    hipLaunchKernelGGL(k_join_ranges, dim3(b < most ? b : most), dim3(kRangeBlock), 0, st, a);
+    const uint32_t tiles = join_tiles(a.m);
+    const dim3 g(tiles), b(kSortBlock);
+    const uint2* in = nullptr;
+    uint2* out = a.pairs[0];
+    uint32_t shift = 0;
+    for (uint32_t pass = 0, left = join_passes(a.key_bits); left > 0u; ++pass, --left) {
+        const uint32_t bits = (a.key_bits - shift + left - 1u) / left, digits = 1u << bits;
+        if (pass == 0) {
+            if (a.n_classes)
+                hipLaunchKernelGGL(k_join_entries<true>, g, b, digits * 4u, st, a, digits);
+            else
+                hipLaunchKernelGGL(k_join_entries<false>, g, b, digits * 4u, st, a, digits);
+        } else {
+            hipLaunchKernelGGL(k_sort_count, g, b, digits * 4u, st, a, in, shift, digits);
+        }
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        hipLaunchKernelGGL(k_sort_rows, dim3(digits), dim3(kBlock), 0, st, a, tiles);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        const uint32_t lds = digits * kSortWaves * 4u;
+        if (pass == 0)
+            hipLaunchKernelGGL(k_sort_scatter<true>, g, b, lds, st, a, in, out, shift, bits);
+        else
+            hipLaunchKernelGGL(k_sort_scatter<false>, g, b, lds, st, a, in, out, shift, bits);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+        in = out;
+        out = a.pairs[(pass + 1u) & 1u];
+        shift += bits;
+    }
+    const uint32_t rb = (a.m + kRangeBlock - 1u) / kRangeBlock, most = 2u * (uint32_t)n_cu;
+    const dim3 rg(rb < most ? rb : most);
+    if (a.n_classes)
+        hipLaunchKernelGGL(k_join_ranges<true>, rg, dim3(kRangeBlock), 0, st, a, in);
+    else
+        hipLaunchKernelGGL(k_join_ranges<false>, rg, dim3(kRangeBlock), 0, st, a, in);
     return hipGetLastError();
 }
 

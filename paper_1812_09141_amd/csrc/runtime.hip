@@ -202,6 +202,8 @@ struct ssj_coll {
     ssj_ctx* ctx = nullptr;
     int32_t* d_tok = nullptr;
     uint4* d_heads = nullptr;  // 32-byte record per set: start, len, first tokens
+    const uint4* d_classes = nullptr;  // with size_sorted, after the records: per set size {first set, size,
+                                       // start of its tokens}, then {n_sets}
     int64_t n_sets = 0;
     int64_t n_tokens = 0;
     int64_t max_len = 0;
@@ -273,13 +275,13 @@ struct ssj_ctx {
     } flt;
     // the whole self-join on the GPU (join.h), grown to the largest one
     struct {
-        uint32_t *pre = nullptr, *keys = nullptr, *keys2 = nullptr, *vals2 = nullptr, *lo = nullptr, *first = nullptr,
-                 *spill_o = nullptr;
-        uint4 *ent = nullptr, *sent = nullptr, *spill = nullptr;
-        uint2* extra = nullptr;
+        uint32_t *pre = nullptr, *keys = nullptr, *counts = nullptr, *lut = nullptr, *lo = nullptr, *spill_o = nullptr;
+        uint4 *cls = nullptr, *ent = nullptr, *sent = nullptr, *spill = nullptr;
+        uint2 *cls2 = nullptr, *pairs0 = nullptr, *pairs1 = nullptr, *extra = nullptr;
         unsigned char* temp = nullptr;
-        size_t pre_cap = 0, keys_cap = 0, keys2_cap = 0, vals2_cap = 0, lo_cap = 0, first_cap = 0, spill_o_cap = 0,
-               ent_cap = 0, sent_cap = 0, spill_cap = 0, extra_cap = 0, temp_cap = 0;
+        size_t pre_cap = 0, keys_cap = 0, counts_cap = 0, lut_cap = 0, lo_cap = 0, spill_o_cap = 0, cls_cap = 0,
+               cls2_cap = 0, pairs0_cap = 0, pairs1_cap = 0, ent_cap = 0, sent_cap = 0, spill_cap = 0, extra_cap = 0,
+               temp_cap = 0;
         ssj::JoinCtl* ctl = nullptr;                 // zero between joins
         unsigned long long* h_totals = nullptr;      // pinned
         int2* h_pairs = nullptr;                     // pinned, kEarlyPairs: ssj_join's first pairs
@@ -1217,8 +1219,9 @@ int ssj_shutdown(ssj_ctx* ctx) {
                         (void*)ctx->flt.keys2, (void*)ctx->flt.probes, (void*)ctx->flt.temp,
                         (void*)ctx->flt.items, (void*)ctx->flt.istart, (void*)ctx->flt.range})
             if (q) (void)hipFree(q);
-        for (void* q : {(void*)ctx->join.pre, (void*)ctx->join.keys, (void*)ctx->join.keys2, (void*)ctx->join.vals2,
-                        (void*)ctx->join.lo, (void*)ctx->join.first, (void*)ctx->join.spill_o, (void*)ctx->join.ent,
+        for (void* q : {(void*)ctx->join.pre, (void*)ctx->join.keys, (void*)ctx->join.counts, (void*)ctx->join.lut,
+                        (void*)ctx->join.lo, (void*)ctx->join.spill_o, (void*)ctx->join.cls, (void*)ctx->join.cls2,
+                        (void*)ctx->join.pairs0, (void*)ctx->join.pairs1, (void*)ctx->join.ent,
                         (void*)ctx->join.sent, (void*)ctx->join.spill, (void*)ctx->join.extra,
                         (void*)ctx->join.temp, (void*)ctx->join.ctl})
             if (q) (void)hipFree(q);
@@ -1289,9 +1292,11 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
     std::vector<uint32_t> start;
     std::vector<int32_t> padded;
     std::vector<std::pair<uint32_t, uint32_t>> sizes;
+    std::vector<uint4> classes;
     uint64_t n_dev = 0;
     try {
         sizes = set_sizes(offsets, n_sets, size_sorted);
+        classes.resize(size_sorted ? sizes.size() + 1 : 0);
         start.resize((size_t)std::max<int64_t>(n_sets, 1));
         for (int64_t i = 0; i < n_sets; ++i) {
             start[(size_t)i] = (uint32_t)n_dev;
@@ -1303,6 +1308,14 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
         for (int64_t i = 0; i < n_sets; ++i)
             std::memcpy(padded.data() + start[(size_t)i], tokens + offsets[i],
                         (size_t)(offsets[i + 1] - offsets[i]) * 4);
+        if (size_sorted) {
+            uint32_t first = 0;
+            for (size_t k = 0; k < sizes.size(); ++k) {
+                classes[k] = make_uint4(first, sizes[k].first, start[first], 0u);
+                first += sizes[k].second;
+            }
+            classes.back() = make_uint4(first, 0u, 0u, 0u);
+        }
     } catch (const std::bad_alloc&) {
         return set_error(SSJ_ENOMEM, "host allocation failed");
     }
@@ -1331,7 +1344,13 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
     hipError_t e = hipSuccess;
     do {
         if ((e = hipMalloc((void**)&c->d_tok, padded.size() * 4)) != hipSuccess) break;
-        if ((e = hipMalloc((void**)&c->d_heads, (size_t)std::max<int64_t>(n_sets, 1) * 32)) != hipSuccess) break;
+        const size_t n_rec = (size_t)std::max<int64_t>(n_sets, 1) * 2;
+        if ((e = hipMalloc((void**)&c->d_heads, (n_rec + classes.size()) * sizeof(uint4))) != hipSuccess) break;
+        if (!classes.empty()) {
+            c->d_classes = c->d_heads + n_rec;
+            if ((e = hipMemcpyAsync(c->d_heads + n_rec, classes.data(), classes.size() * sizeof(uint4),
+                                    hipMemcpyHostToDevice, ctx->stream)) != hipSuccess) break;
+        }
         if ((e = hipMalloc((void**)&d_off, (size_t)(n_sets + 1) * 8)) != hipSuccess) break;
         if ((e = hipMalloc((void**)&d_start, start.size() * 4)) != hipSuccess) break;
         if ((e = hipMemcpyAsync(c->d_tok, padded.data(), padded.size() * 4, hipMemcpyHostToDevice, ctx->stream)) != hipSuccess) break;
@@ -1693,50 +1712,65 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
         HIP_OR_FAIL(ctx, hipDeviceSynchronize());
     }
     ssj::JoinArgs a{};
-    a.sorted = coll->size_sorted && coll->max_len < (int64_t)ssj::kMaxFirst ? 1u : 0u;
-    HIP_OR_FAIL(ctx, grow(J.pre, J.pre_cap, (size_t)coll->n_sets + 1));
+    const uint32_t n_classes = coll->size_sorted ? (uint32_t)coll->sizes.size() : 0u;
+    a.key_bits = 1;
+    while (a.key_bits < 32 && (coll->max_token >> a.key_bits) != 0) ++a.key_bits;
+    const size_t digits = (size_t)1 << std::min(a.key_bits, ssj::kSortBits);
+    const uint32_t extra = ssj::join_extra_cap((uint32_t)m);
+    if (n_classes) {
+        HIP_OR_FAIL(ctx, grow(J.cls, J.cls_cap, (size_t)n_classes + 1));
+        HIP_OR_FAIL(ctx, grow(J.cls2, J.cls2_cap, n_classes));
+        HIP_OR_FAIL(ctx, grow(J.lut, J.lut_cap, ssj::kLut));
+    } else {
+        HIP_OR_FAIL(ctx, grow(J.pre, J.pre_cap, (size_t)coll->n_sets + 1));
+        HIP_OR_FAIL(ctx, grow(J.ent, J.ent_cap, m));
+    }
     HIP_OR_FAIL(ctx, grow(J.keys, J.keys_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.keys2, J.keys2_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.vals2, J.vals2_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.ent, J.ent_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.pairs0, J.pairs0_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.pairs1, J.pairs1_cap, m));
+    // the digit counts per tile, then the digit totals
+    HIP_OR_FAIL(ctx, grow(J.counts, J.counts_cap, digits * ((size_t)ssj::join_tiles((uint32_t)m) + 1)));
     HIP_OR_FAIL(ctx, grow(J.sent, J.sent_cap, m));
     HIP_OR_FAIL(ctx, grow(J.lo, J.lo_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.first, J.first_cap, a.sorted ? (size_t)coll->max_len + 1 : 1));
-    HIP_OR_FAIL(ctx, grow(J.extra, J.extra_cap, ssj::join_extra_cap((uint32_t)m)));
+    HIP_OR_FAIL(ctx, grow(J.extra, J.extra_cap, extra));
     HIP_OR_FAIL(ctx, grow(J.spill, J.spill_cap, ssj::kSpillCap));
     HIP_OR_FAIL(ctx, grow(J.spill_o, J.spill_o_cap, ssj::kSpillCap));
     a.heads = coll->d_heads;
     a.tok = coll->d_tok;
     a.n = (uint32_t)coll->n_sets;
     a.m = (uint32_t)m;
-    a.key_bits = 1;
-    while (a.key_bits < 32 && (coll->max_token >> a.key_bits) != 0) ++a.key_bits;
     a.num = (unsigned long long)t_num;
     a.den = (unsigned long long)t_den;
     overlap_rule(SSJ_SIM_JACCARD, t_num, t_den, a.req);
     a.req.out = d_out;
     a.req.cap = (unsigned long long)out_cap;
     a.req.d_count = d_count;
+    a.classes = coll->d_classes;
+    a.n_classes = n_classes;
+    while (((a.m - 1u) >> a.lut_shift) >= ssj::kLut) ++a.lut_shift;
+    a.cls = J.cls;
+    a.cls2 = J.cls2;
+    a.lut = J.lut;
     a.pre = J.pre;
-    a.keys = J.keys;
-    a.keys2 = J.keys2;
-    a.vals2 = J.vals2;
     a.ent = J.ent;
+    a.keys = J.keys;
+    a.pairs[0] = J.pairs0;
+    a.pairs[1] = J.pairs1;
+    a.totals = J.counts;
+    a.counts = J.counts + digits;
     a.sent = J.sent;
     a.lo = J.lo;
-    a.first = J.first;
     a.extra = J.extra;
-    a.extra_cap = ssj::join_extra_cap((uint32_t)m);
+    a.extra_cap = extra;
     a.spill = J.spill;
     a.spill_o = J.spill_o;
     a.ctl = J.ctl;
     a.h_totals = J.h_totals;
     size_t tb = 0;
-    HIP_OR_FAIL(ctx, ssj::join_index(a, nullptr, &tb, st));
+    HIP_OR_FAIL(ctx, ssj::join_index(a, nullptr, &tb, ctx->n_cu, st));
     HIP_OR_FAIL(ctx, grow(J.temp, J.temp_cap, std::max<size_t>(tb, 1)));
     tb = J.temp_cap;
-    HIP_OR_FAIL(ctx, ssj::join_index(a, J.temp, &tb, st));
-    HIP_OR_FAIL(ctx, ssj::join_ranges(a, ctx->n_cu, st));
+    HIP_OR_FAIL(ctx, ssj::join_index(a, J.temp, &tb, ctx->n_cu, st));
     // m (m - 1) / 2 meetings at most
     const uint64_t most = m64 * (m64 - 1) / 2;
     const bool bounded = most <= ssj::kMaxMeets;
