@@ -10,28 +10,37 @@
 
 namespace ssj {
 
+constexpr uint32_t kSlots = 32;  // counters that the workgroups of a kernel spread over
+constexpr uint32_t kExtraLists = 8;
+constexpr uint32_t kUnitMeets = 2048;  // meetings per work unit of the probe kernel
+
 // Counters of one join in flight; every join's last kernel zeroes them again.
-struct alignas(64) JoinCtl {
-    unsigned long long meets;      // list entries that the probes meet
-    unsigned long long all;        // the same without the length bound
+struct alignas(128) JoinCtl {
+    unsigned long long meets;      // list entries that the probes meet, << 16
     unsigned long long out_count;  // similar pairs appended so far
-    unsigned int extra;            // units after the first of their groups
     unsigned int spilled;          // merges cut off by the step budget
-    unsigned int done;             // workgroups of k_join_ranges that have finished
-    unsigned int pad[7];
+    unsigned int drained;          // workgroups of k_join_drain that have finished
+    unsigned int pad[2];
+    struct alignas(128) {
+        unsigned long long sum;    // meetings << 16, plus the workgroups that counted them
+        unsigned int extra;        // units in the extra list of this number
+    } slot[kSlots];
 };
 
-constexpr uint32_t kUnitMeets = 2048;                        // meetings per work unit
 constexpr unsigned long long kMaxMeets = 0x7fffffffull;      // meetings that a join takes
 constexpr uint32_t kSortTile = 4096;                         // entries per workgroup of the sort
 constexpr uint32_t kSortBits = 10;                           // most bits per pass
 constexpr uint32_t kLut = 1024;                              // coarse index of the set sizes
 constexpr uint32_t kSpillCap = 1u << 18;                     // cut-off merges that are queued
 
-// Whether the totals of a probe pass (meetings, meetings without the length
-// bound, over m prefix entries) are within what a join takes.
-__host__ __device__ inline bool join_fits(unsigned long long meets, unsigned long long all, uint32_t m) {
-    return meets <= kMaxMeets && (unsigned long long)m + all / 64ull < 0x80000000ull;
+// Whether a probe pass over m prefix entries with this many meetings is one
+// that a join takes.  Besides the meetings it bounds those of a walk over whole
+// lists in pieces of 64 entries: the sets of a list of n entries whose sizes
+// differ by less than the factor t all meet, so with sizes in at most groups
+// such groups the list has n^2 / (2 groups) - n / 2 meetings at least, and whole
+// lists have groups (meets + m / 2) entries at most.
+__host__ __device__ inline bool join_fits(unsigned long long meets, uint32_t groups, uint32_t m) {
+    return meets <= kMaxMeets && (unsigned long long)m + groups * (meets + m / 2ull) / 64ull < 0x80000000ull;
 }
 
 // Work units besides the first of every group of 64 entries that a join of m
@@ -57,7 +66,9 @@ struct JoinArgs {
     uint32_t n_classes;
     uint32_t lut_shift;   // (m - 1) >> lut_shift < kLut
     uint4* cls;           // n_classes + 1: {first entry, first set, size, entries per set}
-    uint2* cls2;          // n_classes: {first token's index, first entry of the sets met}
+    uint4* cls2;          // n_classes: {first token's index, first entry of the sets met, division by the
+                          // entries per set: multiplier and shifts}
+    uint32_t size_groups; // groups of sizes within the factor t (1 where whole lists are walked)
     uint32_t* lut;        // kLut
     unsigned long long num, den;  // t
     Request req;          // overlap rule, output (out, cap, d_count)
@@ -67,18 +78,19 @@ struct JoinArgs {
     uint2* pairs[2];      // m each: {token, entry} on their way to token order
     uint32_t* counts;     // 2^kSortBits at most x join_tiles(m)
     uint32_t* totals;     // 2^kSortBits
-    uint4* sent;          // m: entries in token order
+    uint4* sent;          // m: entries in token order: {set, size, tokens after this one, the next token}
+    uint32_t* at;         // m: index of that next token
     uint32_t* lo;         // m: first list entry that the probe meets
-    uint2* extra;         // further units: group, first meeting
+    uint2* extra;         // kExtraLists lists of extra_cap: further units, {group, first meeting}
     uint32_t extra_cap;
     uint4* spill;         // kSpillCap: probe entry, list entry, merge state (i, j)
     uint32_t* spill_o;    // kSpillCap: merge state (o)
     JoinCtl* ctl;
-    unsigned long long* h_totals;  // pinned: meets, all
+    unsigned long long* h_meets;   // pinned
 };
 
-// Index, ranges and work units; a.h_totals holds the totals once it has
-// finished.  With d_temp null it only sets *temp_bytes to the temporary storage
+// Index, ranges and work units; *a.h_meets holds the number of meetings
+// once it has finished.  With d_temp null it only sets *temp_bytes to the temporary storage
 // it needs.
 hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, int n_cu, hipStream_t st);
 // Probes, verification, count (nothing but the count -1 where the totals do

@@ -12,7 +12,9 @@
 // required overlap alpha is dropped on two sizes and two positions alone.
 // (That covers the length filter: for |s| < t |r| alpha exceeds |s|.)  This
 // leaves 10% of the meetings of short sets at t = 0.6, 12% of those of long
-// sets, 52% of a heavy tail's; the others are merged from (i + 1, j + 1) with
+// sets, 52% of a heavy tail's; the two tokens after the meeting, kept with the
+// entries, lower the bound by one where they differ (the heavy tail's probe
+// kernel 738 -> 427 us).  The others are merged from (i + 1, j + 1) with
 // overlap 1, which decides a pair that meets there first.  A pair that passes
 // is reported if no common token lies before i and j.
 //
@@ -24,9 +26,9 @@
 //
 // Measured, whole joins on one MI355X, against a counting and a filling pass
 // over the lists, a list of candidates and its verification: 100,000 short
-// sets at t = 0.6 (3.1M meetings) 1,465 -> 272 us, 50,000 long sets at 0.7
-// 3,628 -> 319 us, a heavy tail of 500,000 sets at 0.75 (169M meetings) 13.4
-// -> 0.93 ms, 5,000 short sets with the results in host memory 220 -> 122 us.
+// sets at t = 0.6 (3.1M meetings) 1,440 -> 143 us, 50,000 long sets at 0.7
+// 3,631 -> 249 us, a heavy tail of 500,000 sets at 0.75 (169M meetings) 13.5
+// -> 0.55 ms, 5,000 short sets with the results in host memory 216 -> 110 us.
 #include <rocprim/device/device_scan.hpp>
 #include <rocprim/iterator/counting_iterator.hpp>
 #include <rocprim/iterator/transform_iterator.hpp>
@@ -41,11 +43,12 @@ constexpr int kSortBlock = 512;                                    // threads of
 constexpr uint32_t kSortWaves = (uint32_t)(kSortBlock / kWave);
 constexpr uint32_t kSortRows = kSortTile / (uint32_t)kSortBlock;   // items per thread
 constexpr uint32_t kEntrySpan = kSortTile / kSortWaves;            // entries per wavefront
-constexpr int kRangeBlock = 1024;
+constexpr int kClassBlock = 1024;
+constexpr int kRangeBlock = 256;
+constexpr int kDrainBlock = 1024;
 constexpr uint32_t kStage = 256;      // staged output pairs per wavefront
 constexpr uint32_t kQueue = 2 * kWave;  // meetings waiting for their merge per wavefront
 constexpr uint32_t kMergeBudget = 32;   // window steps before a merge goes to the drain kernel
-constexpr uint32_t kBackSteps = 4;      // steps back to an earlier meeting before a merge
 
 __device__ __forceinline__ uint32_t needed(uint32_t len, unsigned long long num, unsigned long long den) {
     return (uint32_t)((num * len + den - 1ull) / den);
@@ -87,12 +90,12 @@ __device__ __forceinline__ uint32_t bperm_u32(uint32_t v, uint32_t src) { return
 // of each size, entries per set, and the first entry of the sets that are long
 // enough for it (thr); and a coarse index of the sizes by entry number (the
 // size of every (1 << lut_shift)-th entry).  One workgroup.
-__global__ __launch_bounds__(kRangeBlock) void k_join_classes(JoinArgs a) {
-    constexpr int kWaves = kRangeBlock / kWave;
+__global__ __launch_bounds__(kClassBlock) void k_join_classes(JoinArgs a) {
+    constexpr int kWaves = kClassBlock / kWave;
     __shared__ uint32_t s_sum[kWaves];
     const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
     uint32_t carry = 0;
-    for (uint32_t b = 0; b < a.n_classes; b += kRangeBlock) {
+    for (uint32_t b = 0; b < a.n_classes; b += kClassBlock) {
         const uint32_t c = b + threadIdx.x;
         const bool in = c < a.n_classes;
         const uint4 st = a.classes[in ? c : a.n_classes];
@@ -111,7 +114,7 @@ __global__ __launch_bounds__(kRangeBlock) void k_join_classes(JoinArgs a) {
     }
     if (threadIdx.x == 0) a.cls[a.n_classes] = make_uint4(carry, a.n, 0u, 1u);
     __syncthreads();
-    for (uint32_t c = threadIdx.x; c < a.n_classes; c += kRangeBlock) {
+    for (uint32_t c = threadIdx.x; c < a.n_classes; c += kClassBlock) {
         const uint4 st = a.classes[c];
         const uint32_t need = needed(st.y, a.num, a.den);
         uint32_t lo = 0, hi = c;  // the first size >= need (need <= its own size)
@@ -122,9 +125,15 @@ __global__ __launch_bounds__(kRangeBlock) void k_join_classes(JoinArgs a) {
             else
                 hi = mid;
         }
-        a.cls2[c] = make_uint2(st.z, a.cls[lo].x);
+        // division by the entries per set, d: the round-up multiplier of
+        // Granlund and Montgomery (PLDI 1994) for 32-bit dividends
+        const uint32_t d = a.cls[c].w;
+        uint32_t l = 0;
+        while (l < 32u && (1ull << l) < d) ++l;
+        const unsigned long long magic = (((1ull << l) - d) << 32) / d + 1ull;
+        a.cls2[c] = make_uint4(st.z, a.cls[lo].x, (uint32_t)magic, min(l, 1u) | ((max(l, 1u) - 1u) << 8));
     }
-    for (uint32_t k = threadIdx.x; k < kLut; k += kRangeBlock) {
+    for (uint32_t k = threadIdx.x; k < kLut; k += kClassBlock) {
         const uint32_t e = k << a.lut_shift;
         if (e >= a.m) break;
         uint32_t lo = 0, hi = a.n_classes;  // the last size that begins at or before e
@@ -145,8 +154,9 @@ __device__ __forceinline__ uint4 entry_of(const JoinArgs& a, uint32_t e, uint32_
     uint32_t c = a.lut[e >> a.lut_shift];
     while (a.cls[c + 1u].x <= e) ++c;
     const uint4 k = a.cls[c];
-    const uint2 k2 = a.cls2[c];
-    const uint32_t r = e - k.x, i = r / k.w, j = r - i * k.w;
+    const uint4 k2 = a.cls2[c];
+    const uint32_t r = e - k.x, t = __umulhi(k2.z, r);
+    const uint32_t i = (t + ((r - t) >> (k2.w & 0xffu))) >> (k2.w >> 8), j = r - i * k.w;
     *thr = k2.y;
     return make_uint4(k.y + i, k.z, j, k2.x + i * ((k.z + 3u) & ~3u) + j + 1u);
 }
@@ -229,8 +239,9 @@ __global__ __launch_bounds__(kSortBlock) void k_join_entries(JoinArgs a, uint32_
 // and tile of kSortTile entries, a scan of each digit's row, and a scatter.
 // The entries start in set order and every pass keeps the order of equal
 // digits, so a list ends up in set order.  Bound by the scattered 8-byte
-// writes and by the launches; 2.0M entries, 20 bits: 107 us with rocPRIM's
-// radix sort (three passes of 8 bits), 45 us so.
+// writes and by the launches; 2.0M entries of 20 bits: 107 us with rocPRIM's
+// radix sort (three passes of 8 bits), 71 us so; 0.54M of 18 bits: 148 us (its
+// merge sort) and 35 us.
 __global__ __launch_bounds__(kSortBlock) void k_sort_count(JoinArgs a, const uint2* __restrict__ in, uint32_t shift,
                                                            uint32_t digits) {
     extern __shared__ uint32_t s_hist[];
@@ -383,49 +394,44 @@ __device__ __forceinline__ uint32_t list_begin(const uint2* __restrict__ list, c
 // Waits until every memory operation of the wavefront has completed.
 __device__ __forceinline__ void memory_wait() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
 
-__device__ __forceinline__ unsigned long long wave_sum_u64(unsigned long long v) {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-    return v;
-}
-
 // Entries in list order, the range of list entries that each meets, and the
 // work units of the probe kernel: a unit is up to kUnitMeets meetings of one
-// group of 64 consecutive entries.  The first unit of group g is unit g; the
-// few groups with more meetings append the others to extra, reserved with
-// one atomic per workgroup and pass.  The last workgroup to finish stores the
-// totals for the host (atomics only, each one complete before the next is
-// issued, so no fence is needed).
+// group of 64 consecutive entries.  The first unit of group g is unit g; groups
+// with more meetings append the others to one of kExtraLists lists.  The last
+// workgroup to finish stores the number of meetings for the host.  An atomic
+// on one address takes about 10 ns whoever issues it, so the lists and the
+// counts spread over several (with one address each they took 40 us at 2.0M
+// entries and 2,048 workgroups, the rest of the kernel 37 us).
 template <bool SORTED>
 __global__ __launch_bounds__(kRangeBlock) void k_join_ranges(JoinArgs a, const uint2* __restrict__ list) {
     constexpr int kWaves = kRangeBlock / kWave;
-    __shared__ uint2 s_tile[kRangeBlock + 1];
+    __shared__ uint2 s_tile[kRangeBlock];
     __shared__ uint32_t s_extra[kWaves];
     __shared__ uint32_t s_base;
-    __shared__ unsigned long long s_tot[2 * kWaves];
+    __shared__ unsigned long long s_tot[kWaves];
     const int lane = lane_id(), w = (int)(threadIdx.x / kWave);
-    unsigned long long meets = 0ull, all = 0ull;
+    unsigned long long meets = 0ull;
     for (uint32_t b = blockIdx.x * kRangeBlock; b < a.m; b += gridDim.x * kRangeBlock) {
         const uint32_t q = b + threadIdx.x;
-        unsigned long long cnt = 0ull;
+        uint32_t cnt = 0;
         const uint2 it = list[min(q, a.m - 1u)];
         s_tile[threadIdx.x] = it;
-        if (threadIdx.x == kRangeBlock - 1) s_tile[kRangeBlock] = list[min(q + 1u, a.m - 1u)];
         __syncthreads();
         if (q < a.m) {
             uint32_t thr = 0;
             const uint4 en = SORTED ? entry_of(a, it.y, &thr) : a.ent[it.y];
-            a.sent[q] = en;
+            const uint32_t rem = en.y - en.z - 1u;
+            // (no token: larger than every token)
+            a.sent[q] = make_uint4(en.x, en.y, rem, rem != 0u ? (uint32_t)a.tok[en.w] : 0xffffffffu);
+            a.at[q] = en.w;
             const uint32_t lo = list_begin(list, s_tile, b, q, it.x, thr);
             a.lo[q] = lo;
             cnt = q - lo;
-            if (q + 1u == a.m || s_tile[threadIdx.x + 1].x != it.x) {
-                const unsigned long long len = q - list_begin(list, s_tile, b, q, it.x, 0u) + 1ull;
-                all += len * (len - 1ull) / 2ull;
-            }
         }
-        const unsigned long long T = wave_sum_u64(cnt);
-        meets += lane == 0 ? T : 0ull;
+        // (cnt < 2^30: the sum of 64 in two halves)
+        const unsigned long long T = lane_u32(wave_add_scan(cnt & 0xffffu, lane), kWave - 1) +
+                                     ((unsigned long long)lane_u32(wave_add_scan(cnt >> 16, lane), kWave - 1) << 16);
+        meets += T;
         const uint32_t more = T > kUnitMeets ? (uint32_t)min((T - 1ull) / kUnitMeets, 0xffffffull) : 0u;
         if (lane == 0) s_extra[w] = more;
         __syncthreads();
@@ -435,48 +441,68 @@ __global__ __launch_bounds__(kRangeBlock) void k_join_ranges(JoinArgs a, const u
             sum += s_extra[k];
         }
         if (sum > 0u) {  // uniform in the workgroup
-            if (threadIdx.x == 0) s_base = atomicAdd(&a.ctl->extra, sum);
+            const uint32_t x = blockIdx.x % kExtraLists;
+            if (threadIdx.x == 0) s_base = atomicAdd(&a.ctl->slot[x].extra, sum);
             __syncthreads();
             for (uint32_t k = (uint32_t)lane; k < more; k += kWave) {
-                const uint32_t slot = s_base + before + k;
-                if (slot < a.extra_cap) a.extra[slot] = make_uint2((b / kWave) + (uint32_t)w, (k + 1u) * kUnitMeets);
+                const uint32_t at = s_base + before + k;
+                if (at < a.extra_cap)
+                    a.extra[(size_t)x * a.extra_cap + at] = make_uint2((b / kWave) + (uint32_t)w, (k + 1u) * kUnitMeets);
             }
         }
         __syncthreads();
     }
-    all = wave_sum_u64(all);
-    if (lane == 0) {
-        s_tot[w] = meets;
-        s_tot[kWaves + w] = all;
-    }
+    if (lane == 0) s_tot[w] = meets;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int k = 1; k < kWaves; ++k) {
-            meets += s_tot[k];
-            all += s_tot[kWaves + k];
-        }
-        atomicAdd(&a.ctl->meets, meets);
-        atomicAdd(&a.ctl->all, all);
-        memory_wait();
-        if (atomicAdd(&a.ctl->done, 1u) == gridDim.x - 1u) {
-            a.h_totals[0] = atomicAdd(&a.ctl->meets, 0ull);
-            a.h_totals[1] = atomicAdd(&a.ctl->all, 0ull);
+        for (int k = 1; k < kWaves; ++k) meets += s_tot[k];
+        // one atomic per workgroup, on kSlots addresses, then one per address:
+        // the meetings (2^33 stand for more) and the workgroups counted in one
+        // word
+        const uint32_t slot = blockIdx.x % kSlots;
+        const unsigned long long add = (min(meets, 1ull << 33) << 16) + 1ull;
+        const unsigned long long sum = atomicAdd(&a.ctl->slot[slot].sum, add) + add;
+        const uint32_t of = (gridDim.x - slot + kSlots - 1u) / kSlots, slots = min(gridDim.x, kSlots);
+        if ((sum & 0xffffull) == of) {
+            const unsigned long long all_add = ((sum >> 16) << 16) + 1ull;
+            const unsigned long long all = atomicAdd(&a.ctl->meets, all_add) + all_add;
+            if ((all & 0xffffull) == slots) *a.h_meets = all >> 16;
         }
     }
 }
 
-// Steps back from positions (i, j) of two sets through their common tokens:
-// whether a token is common to A[0, i) and B[0, j).  After at most limit steps
-// it stops with (i, j) where it stopped.
-__device__ __forceinline__ bool common_before(const int32_t* __restrict__ A, uint32_t& i,
-                                              const int32_t* __restrict__ B, uint32_t& j, uint32_t limit) {
-    for (uint32_t s = 0; s < limit && i > 0u && j > 0u; ++s) {
+// Whether a token is common to A[0, i) and B[0, j), by a merge from their ends
+// (an earlier meeting of two similar sets is mostly a few tokens back).
+__device__ __forceinline__ bool common_before(const int32_t* __restrict__ A, uint32_t i, const int32_t* __restrict__ B,
+                                              uint32_t j) {
+    while (i > 0u && j > 0u) {
         const int32_t x = A[i - 1u], y = B[j - 1u];
         if (x == y) return true;
         i -= x > y ? 1u : 0u;
         j -= y > x ? 1u : 0u;
     }
     return false;
+}
+
+// Whether the 4-token windows that end before positions i and j (both above 0)
+// of the sets at sa and sb share a token before them.  (A token at or after
+// position i is not below the token met there, one before j is.)
+__device__ __forceinline__ bool common_window(const int32_t* __restrict__ tok, uint32_t sa, uint32_t i, uint32_t sb,
+                                              uint32_t j) {
+    const uint4* __restrict__ t4 = reinterpret_cast<const uint4*>(tok);
+    const uint32_t wa = (i - 1u) >> 2;
+    int32_t x[4], y[4];
+    unpack_window(t4[(sa >> 2) + wa], x);
+    unpack_window(t4[(sb >> 2) + ((j - 1u) >> 2)], y);
+    bool hit = false;
+#pragma unroll
+    for (uint32_t k = 0; k < 4u; ++k) {
+        bool eq = false;
+#pragma unroll
+        for (int l = 0; l < 4; ++l) eq |= x[k] == y[l];
+        hit |= eq && 4u * wa + k < i;
+    }
+    return hit;
 }
 
 __device__ __forceinline__ uint32_t load_agent(const unsigned int* p) {
@@ -500,8 +526,8 @@ __device__ void flush_pairs(const JoinArgs& a, uint32_t c, const int2* w_out) {
     wave_sync();
 }
 
-// Probes and merges.  A wavefront takes units (k_join_ranges) and walks the
-// meetings of a group 64 at a time, whatever the lengths of its lists: the
+// Probes and merges.  A wavefront takes units of up to kUnitMeets meetings of a
+// group of 64 entries and walks them 64 at a time, whatever the lengths of its lists: the
 // meetings of the group's entries are numbered through (a running sum), and
 // lane k of a step takes meeting t0 + k.  Where one probe's list covers the
 // whole step its values are scalars, else every probe marks where its
@@ -521,10 +547,13 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
     int2* w_out = s_out + wl * kStage;
     uint2* queue = s_queue + wl * kQueue;
     uint32_t* marks = s_marks + wl * kWave;
-    if (!join_fits(load_agent(&a.ctl->meets), load_agent(&a.ctl->all), a.m)) return;
+    if (!join_fits(load_agent(&a.ctl->meets) >> 16, a.size_groups, a.m)) return;
     const uint32_t n_groups = (a.m + kWave - 1u) / kWave;
-    const uint32_t n_units = n_groups + min(load_agent(&a.ctl->extra), a.extra_cap);
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWaves + wl));
+    // extra units of each list (lane k: list k), and up to its end
+    const uint32_t l_extra = lane < (int)kExtraLists ? min(load_agent(&a.ctl->slot[lane].extra), a.extra_cap) : 0u;
+    const uint32_t l_ends = wave_add_scan(l_extra, lane);
+    const uint32_t n_units = n_groups + lane_u32(l_ends, kWave - 1);
     const Request& R = a.req;
     uint32_t ocnt = 0, qcnt = 0;
 
@@ -536,19 +565,25 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
         const uint2 qq = queue[qcnt + min((uint32_t)lane, n - 1u)];
         wave_sync();
         const uint4 er = a.sent[qq.x], es = a.sent[qq.y];
+        const uint32_t ar = a.at[qq.x], as = a.at[qq.y];
         const uint32_t na = er.y, nb = es.y;
-        const uint32_t sa = er.w - er.z - 1u, sb = es.w - es.z - 1u;
+        // merge state after the meeting, and the tokens before it (bi, bj)
+        uint32_t i = na - er.z, j = nb - es.z, o = 1u;
+        const uint32_t sa = ar - i, sb = as - j;
+        const uint32_t bi = i - 1u, bj = j - 1u;
         const uint32_t alpha = required_overlap<false>(na, nb, R);
-        uint32_t i = er.z + 1u, j = es.z + 1u, o = 1u;
-        uint32_t bi = er.z, bj = es.z;
         bool pass = have && o >= alpha;
-        bool act = have && !pass;
-        if (have && bi > 0u && bj > 0u && common_before(a.tok + sa, bi, a.tok + sb, bj, kBackSteps)) {
-            pass = false;
-            act = false;
-        }
         bool spill = false;
-        if (act) pass = merge_windows(a.tok, sa, na, a.tok, sb, nb, alpha, i, j, o, kMergeBudget, &spill);
+        if (have && !pass) {
+            // near-copies meet at most of their tokens: where the windows before
+            // the meeting share a token, this is not their first (the two loads
+            // go out with those of the merge)
+            Windows w;
+            load_windows(a.tok, sa, na, a.tok, sb, nb, i, j, w);
+            bool later = false;
+            if (bi > 0u && bj > 0u) later = common_window(a.tok, sa, bi, sb, bj);
+            if (!later) pass = merge_loaded(a.tok, sa, na, a.tok, sb, nb, alpha, i, j, o, kMergeBudget, &spill, w);
+        }
         const unsigned long long ms = ballot(spill);
         if (ms != 0ull) {
             uint32_t base = 0;
@@ -565,7 +600,7 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
                 }
             }
         }
-        if (pass && bi > 0u && bj > 0u && common_before(a.tok + sa, bi, a.tok + sb, bj, 0xffffffffu)) pass = false;
+        if (pass && common_before(a.tok + sa, bi, a.tok + sb, bj)) pass = false;
         const unsigned long long mp = ballot(pass);
         if (R.cap != 0 && pass) w_out[ocnt + mbcnt(mp)] = make_int2((int)er.x, (int)es.x);
         ocnt += (uint32_t)__popcll(mp);
@@ -578,9 +613,11 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
     for (uint32_t u = wave; u < n_units; u += gridDim.x * kWaves) {
         uint32_t g = u, begin = 0;
         if (u >= n_groups) {
-            const uint2 x = a.extra[u - n_groups];
-            g = x.x;
-            begin = x.y;
+            const uint32_t k = u - n_groups;
+            const int x = (int)__popcll(ballot(l_ends <= k));  // its list
+            const uint2 v = a.extra[(size_t)x * a.extra_cap + (k - (x ? lane_u32(l_ends, x - 1) : 0u))];
+            g = v.x;
+            begin = v.y;
         }
         const uint32_t rank = g * kWave + (uint32_t)lane;
         const uint32_t rc = min(rank, a.m - 1u);
@@ -591,15 +628,16 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
         const uint32_t start = incl - cnt;  // the probe's first meeting
         const uint32_t T = lane_u32(incl, kWave - 1);
         const uint32_t end = min(T, begin + kUnitMeets);
-        const uint32_t rem = er.y - er.z - 1u, shift = lo - start;
-        uint32_t u_end = 0, u_len = 0, u_rem = 0, u_shift = 0, u_rank = 0;  // the last step's last probe
+        const uint32_t shift = lo - start;
+        uint32_t u_end = 0, u_len = 0, u_rem = 0, u_next = 0, u_shift = 0, u_rank = 0;  // the last step's last probe
         for (uint32_t t0 = begin; t0 < end; t0 += kWave) {
             const uint32_t t = t0 + (uint32_t)lane;
             const bool in = t < end;
-            uint32_t r_len, r_rem, r_rank, s_rank;
+            uint32_t r_len, r_rem, r_next, r_rank, s_rank;
             if (u_end >= t0 + kWave) {
                 r_len = u_len;
                 r_rem = u_rem;
+                r_next = u_next;
                 r_rank = u_rank;
                 s_rank = u_shift + t;
             } else {
@@ -610,19 +648,23 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
                 const uint32_t own = wave_max_scan(marks[lane], lane) - 1u;
                 wave_sync();
                 r_len = bperm_u32(er.y, own);
-                r_rem = bperm_u32(rem, own);
+                r_rem = bperm_u32(er.z, own);
+                r_next = bperm_u32(er.w, own);
                 r_rank = g * kWave + own;
                 s_rank = bperm_u32(shift, own) + t;
                 const int last = (int)lane_u32(own, kWave - 1);
                 u_end = lane_u32(incl, last);
                 u_len = lane_u32(er.y, last);
-                u_rem = lane_u32(rem, last);
+                u_rem = lane_u32(er.z, last);
+                u_next = lane_u32(er.w, last);
                 u_shift = lane_u32(shift, last);
                 u_rank = g * kWave + (uint32_t)last;
             }
             const uint4 es = a.sent[in ? s_rank : rc];
             const uint32_t alpha = required_overlap<false>(r_len, es.y, R);
-            const bool keep = in && 1u + min(r_rem, es.y - es.z - 1u) >= alpha;
+            // one step of the merge: the lower of the next tokens has no partner
+            const uint32_t left = min(r_rem - (r_next < es.w ? 1u : 0u), es.z - (es.w < r_next ? 1u : 0u));
+            const bool keep = in && 1u + left >= alpha;
             const unsigned long long mk = ballot(keep);
             if (mk != 0ull) {
                 if (keep) queue[qcnt + mbcnt(mk)] = make_uint2(r_rank, s_rank);
@@ -632,38 +674,60 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
         }
     }
     if (qcnt > 0u) merge_queued(qcnt);
-    if (ocnt > 0u) flush_pairs(a, ocnt, w_out);
+    // the rest of the workgroup's pairs with one atomic (every wavefront of the
+    // grid ends here, and atomics on one address take about 8 ns each)
+    __syncthreads();
+    uint32_t* ends = reinterpret_cast<uint32_t*>(s_queue);
+    if (lane == 0) ends[wl] = ocnt;
+    __syncthreads();
+    uint32_t before = 0, sum = 0;
+    for (uint32_t k = 0; k < (uint32_t)kWaves; ++k) {
+        before += k < wl ? ends[k] : 0u;
+        sum += ends[k];
+    }
+    if (sum == 0u) return;
+    __shared__ unsigned long long s_base;
+    if (threadIdx.x == 0) s_base = atomicAdd(&a.ctl->out_count, (unsigned long long)sum);
+    if (R.cap == 0) return;
+    __syncthreads();
+    for (uint32_t k = (uint32_t)lane; k < ocnt; k += kWave) {
+        const unsigned long long to = s_base + before + k;
+        if (to < R.cap) R.out[to] = w_out[k];
+    }
 }
 
-// Merges that the probe kernel cut off, continued by a wavefront per pair.
-__global__ __launch_bounds__(kBlock) void k_join_drain(JoinArgs a) {
-    constexpr int G = kWave;
+// Merges that the probe kernel cut off, continued by a wavefront per pair; the
+// last workgroup to finish publishes the count (-1 where nothing was joined)
+// and zeroes the counters.
+__global__ __launch_bounds__(kDrainBlock) void k_join_drain(JoinArgs a) {
     const uint32_t cnt = min(load_agent(&a.ctl->spilled), kSpillCap);
     const int g = lane_id();
-    const int gbase = 0;
-    for (uint32_t k = (blockIdx.x * kBlock + threadIdx.x) / G; k < cnt; k += gridDim.x * kBlock / G) {
+    const uint32_t waves = gridDim.x * (uint32_t)(kDrainBlock / kWave);
+    for (uint32_t k = (blockIdx.x * kDrainBlock + threadIdx.x) / kWave; k < cnt; k += waves) {
         const uint4 st = a.spill[k];
         const uint4 er = a.sent[st.x], es = a.sent[st.y];
-        const int32_t* A = a.tok + (er.w - er.z - 1u);
-        const int32_t* B = a.tok + (es.w - es.z - 1u);
+        const uint32_t bi = er.y - er.z - 1u, bj = es.y - es.z - 1u;  // tokens before the meeting
+        const int32_t* A = a.tok + (a.at[st.x] - bi - 1u);
+        const int32_t* B = a.tok + (a.at[st.y] - bj - 1u);
         const uint32_t alpha = required_overlap<false>(er.y, es.y, a.req);
-        bool pass = merge_group<G>(A, er.y, B, es.y, alpha, g, gbase, st.z, st.w, a.spill_o[k]);
-        // (er.z and es.z tokens before the meeting: none may be common)
-        if (pass && er.z > 0u && es.z > 0u) pass = !merge_group<G>(A, er.z, B, es.z, 1u, g, gbase);
+        bool pass = merge_group<kWave>(A, er.y, B, es.y, alpha, g, 0, st.z, st.w, a.spill_o[k]);
+        // none of the tokens before may be common
+        if (pass && bi > 0u && bj > 0u) pass = !merge_group<kWave>(A, bi, B, bj, 1u, g, 0);
         if (pass && g == 0) {
             const unsigned long long at = atomicAdd(&a.ctl->out_count, 1ull);
             if (at < a.req.cap) a.req.out[at] = make_int2((int)er.x, (int)es.x);
         }
     }
-}
-
-// Publishes the count (-1 where nothing was joined) and zeroes the counters.
-__global__ void k_join_finalize(JoinArgs a) {
-    if (threadIdx.x == 0) {
-        const bool fits = join_fits(a.ctl->meets, a.ctl->all, a.m);
-        *a.req.d_count = fits ? (long long)a.ctl->out_count : -1ll;
-        a.ctl->meets = a.ctl->all = a.ctl->out_count = 0ull;
-        a.ctl->extra = a.ctl->spilled = a.ctl->done = 0u;
+    memory_wait();
+    __syncthreads();
+    if (threadIdx.x != 0 || atomicAdd(&a.ctl->drained, 1u) != gridDim.x - 1u) return;
+    const bool fits = join_fits(load_agent(&a.ctl->meets) >> 16, a.size_groups, a.m);
+    *a.req.d_count = fits ? (long long)load_agent(&a.ctl->out_count) : -1ll;
+    a.ctl->meets = a.ctl->out_count = 0ull;
+    a.ctl->spilled = a.ctl->drained = 0u;
+    for (uint32_t k = 0; k < kSlots; ++k) {
+        a.ctl->slot[k].sum = 0ull;
+        a.ctl->slot[k].extra = 0u;
     }
 }
 
@@ -682,7 +746,7 @@ hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, int n
             *temp_bytes = 0;
             return hipSuccess;
         }
-        hipLaunchKernelGGL(k_join_classes, dim3(1), dim3(kRangeBlock), 0, st, a);
+        hipLaunchKernelGGL(k_join_classes, dim3(1), dim3(kClassBlock), 0, st, a);
         if ((e = hipGetLastError()) != hipSuccess) return e;
     }
     const uint32_t tiles = join_tiles(a.m);
@@ -713,7 +777,7 @@ hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, int n
         out = a.pairs[(pass + 1u) & 1u];
         shift += bits;
     }
-    const uint32_t rb = (a.m + kRangeBlock - 1u) / kRangeBlock, most = 2u * (uint32_t)n_cu;
+    const uint32_t rb = (a.m + kRangeBlock - 1u) / kRangeBlock, most = (2048u / kRangeBlock) * (uint32_t)n_cu;
     const dim3 rg(rb < most ? rb : most);
     if (a.n_classes)
         hipLaunchKernelGGL(k_join_ranges<true>, rg, dim3(kRangeBlock), 0, st, a, in);
@@ -723,17 +787,15 @@ hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, int n
 }
 
 hipError_t join_probe(const JoinArgs& a, int n_cu, hipStream_t st) {
-    // units: the groups and what the larger ones have besides; the extra
-    // units' number is known on the device only
+    // units: the groups and what the larger ones have besides (their number is
+    // known on the device only)
     const uint32_t per = kBlock / kWave;
     const unsigned long long units = (unsigned long long)(a.m + kWave - 1u) / kWave + a.extra_cap;
     const unsigned long long b = (units + per - 1u) / per, most = 6ull * (unsigned long long)n_cu;
     hipLaunchKernelGGL(k_join_probe, dim3((unsigned)(b < most ? b : most)), dim3(kBlock), 0, st, a);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_join_drain, dim3(8u * (unsigned)n_cu), dim3(kBlock), 0, st, a);
-    if ((e = hipGetLastError()) != hipSuccess) return e;
-    hipLaunchKernelGGL(k_join_finalize, dim3(1), dim3(kWave), 0, st, a);
+    hipLaunchKernelGGL(k_join_drain, dim3((unsigned)n_cu), dim3(kDrainBlock), 0, st, a);
     return hipGetLastError();
 }
 

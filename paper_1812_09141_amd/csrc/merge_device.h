@@ -196,31 +196,47 @@ __device__ __forceinline__ void step_windows(const int32_t (&a)[4], const int32_
 // budget steps a merge still undecided stops with *spilled set (all lanes
 // enter together, so the step count is the same in every lane and the cut is
 // a wave-uniform branch).
-__device__ __forceinline__ bool merge_windows(const int32_t* __restrict__ tok_a, uint32_t sa,
-                                              uint32_t na, const int32_t* __restrict__ tok_b,
-                                              uint32_t sb, uint32_t nb, uint32_t alpha, uint32_t& i,
-                                              uint32_t& j, uint32_t& o, uint32_t budget, bool* spilled) {
+//
+// The windows as separate 32-bit values (selects on whole vectors become
+// address selects into scratch memory): the current and the next one of each
+// side.
+struct Windows {
+    int32_t a[4], b[4], an[4], bn[4];
+};
+
+__device__ __forceinline__ void unpack_window(uint4 v, int32_t (&d)[4]) {
+    d[0] = (int32_t)v.x;
+    d[1] = (int32_t)v.y;
+    d[2] = (int32_t)v.z;
+    d[3] = (int32_t)v.w;
+}
+
+// The windows at merge state (i, j), i < na and j < nb.
+__device__ __forceinline__ void load_windows(const int32_t* __restrict__ tok_a, uint32_t sa, uint32_t na,
+                                             const int32_t* __restrict__ tok_b, uint32_t sb, uint32_t nb, uint32_t i,
+                                             uint32_t j, Windows& w) {
     const uint4* __restrict__ t4a = reinterpret_cast<const uint4*>(tok_a);
     const uint4* __restrict__ t4b = reinterpret_cast<const uint4*>(tok_b);
     const uint32_t qa = sa >> 2, qb = sb >> 2;              // first window of each set
     const uint32_t la = (na - 1u) >> 2, lb = (nb - 1u) >> 2;  // last window index
+    unpack_window(t4a[qa + (i >> 2)], w.a);
+    unpack_window(t4b[qb + (j >> 2)], w.b);
+    unpack_window(t4a[qa + min((i >> 2) + 1u, la)], w.an);
+    unpack_window(t4b[qb + min((j >> 2) + 1u, lb)], w.bn);
+}
+
+__device__ __forceinline__ bool merge_loaded(const int32_t* __restrict__ tok_a, uint32_t sa,
+                                             uint32_t na, const int32_t* __restrict__ tok_b,
+                                             uint32_t sb, uint32_t nb, uint32_t alpha, uint32_t& i,
+                                             uint32_t& j, uint32_t& o, uint32_t budget, bool* spilled, Windows& w) {
+    const uint4* __restrict__ t4a = reinterpret_cast<const uint4*>(tok_a);
+    const uint4* __restrict__ t4b = reinterpret_cast<const uint4*>(tok_b);
+    const uint32_t qa = sa >> 2, qb = sb >> 2;
+    const uint32_t la = (na - 1u) >> 2, lb = (nb - 1u) >> 2;
     uint32_t wa = i >> 2, wb = j >> 2;
-    // the windows as separate 32-bit values (selects on whole vectors become
-    // address selects into scratch memory)
-    int32_t a[4], b[4], an[4], bn[4];
-    auto unpack = [](uint4 v, int32_t (&d)[4]) {
-        d[0] = (int32_t)v.x;
-        d[1] = (int32_t)v.y;
-        d[2] = (int32_t)v.z;
-        d[3] = (int32_t)v.w;
-    };
-    unpack(t4a[qa + wa], a);
-    unpack(t4b[qb + wb], b);
-    unpack(t4a[qa + min(wa + 1u, la)], an);
-    unpack(t4b[qb + min(wb + 1u, lb)], bn);
     for (uint32_t step = 1;; ++step) {
         const uint32_t ba = wa << 2, bb = wb << 2;
-        step_windows(a, b, ba, bb, na, nb, i, j, o);
+        step_windows(w.a, w.b, ba, bb, na, nb, i, j, o);
         if (o >= alpha) return true;
         if (o + min(na - i, nb - j) < alpha) return false;
         if (step >= budget) {
@@ -232,13 +248,22 @@ __device__ __forceinline__ bool merge_windows(const int32_t* __restrict__ tok_a,
         wb += adv_b ? 1u : 0u;
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            a[k] = adv_a ? an[k] : a[k];
-            b[k] = adv_b ? bn[k] : b[k];
+            w.a[k] = adv_a ? w.an[k] : w.a[k];
+            w.b[k] = adv_b ? w.bn[k] : w.b[k];
         }
         __builtin_amdgcn_sched_barrier(0);
-        unpack(t4a[qa + min(wa + 1u, la)], an);
-        unpack(t4b[qb + min(wb + 1u, lb)], bn);
+        unpack_window(t4a[qa + min(wa + 1u, la)], w.an);
+        unpack_window(t4b[qb + min(wb + 1u, lb)], w.bn);
     }
+}
+
+__device__ __forceinline__ bool merge_windows(const int32_t* __restrict__ tok_a, uint32_t sa,
+                                              uint32_t na, const int32_t* __restrict__ tok_b,
+                                              uint32_t sb, uint32_t nb, uint32_t alpha, uint32_t& i,
+                                              uint32_t& j, uint32_t& o, uint32_t budget, bool* spilled) {
+    Windows w;
+    load_windows(tok_a, sa, na, tok_b, sb, nb, i, j, w);
+    return merge_loaded(tok_a, sa, na, tok_b, sb, nb, alpha, i, j, o, budget, spilled, w);
 }
 
 }  // namespace

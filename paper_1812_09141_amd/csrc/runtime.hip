@@ -8,6 +8,7 @@
 #include <array>
 #include <atomic>
 #include <chrono>
+#include <cmath>
 #include <condition_variable>
 #include <cstdio>
 #include <cstring>
@@ -275,17 +276,18 @@ struct ssj_ctx {
     } flt;
     // the whole self-join on the GPU (join.h), grown to the largest one
     struct {
-        uint32_t *pre = nullptr, *keys = nullptr, *counts = nullptr, *lut = nullptr, *lo = nullptr, *spill_o = nullptr;
-        uint4 *cls = nullptr, *ent = nullptr, *sent = nullptr, *spill = nullptr;
-        uint2 *cls2 = nullptr, *pairs0 = nullptr, *pairs1 = nullptr, *extra = nullptr;
+        uint32_t *pre = nullptr, *keys = nullptr, *counts = nullptr, *lut = nullptr, *lo = nullptr, *at = nullptr,
+                 *spill_o = nullptr;
+        uint4 *cls = nullptr, *cls2 = nullptr, *ent = nullptr, *sent = nullptr, *spill = nullptr;
+        uint2 *pairs0 = nullptr, *pairs1 = nullptr, *extra = nullptr;
         unsigned char* temp = nullptr;
-        size_t pre_cap = 0, keys_cap = 0, counts_cap = 0, lut_cap = 0, lo_cap = 0, spill_o_cap = 0, cls_cap = 0,
+        size_t pre_cap = 0, keys_cap = 0, counts_cap = 0, lut_cap = 0, lo_cap = 0, at_cap = 0, spill_o_cap = 0, cls_cap = 0,
                cls2_cap = 0, pairs0_cap = 0, pairs1_cap = 0, ent_cap = 0, sent_cap = 0, spill_cap = 0, extra_cap = 0,
                temp_cap = 0;
         ssj::JoinCtl* ctl = nullptr;                 // zero between joins
-        unsigned long long* h_totals = nullptr;      // pinned
+        unsigned long long* h_meets = nullptr;       // pinned
         int2* h_pairs = nullptr;                     // pinned, kEarlyPairs: ssj_join's first pairs
-        hipEvent_t ev = nullptr;                     // the totals are on the host
+        hipEvent_t ev = nullptr;                     // the number of meetings is on the host
     } join;
     std::atomic<bool> failed{false};
     std::vector<ssj_coll*> colls;
@@ -1220,12 +1222,12 @@ int ssj_shutdown(ssj_ctx* ctx) {
                         (void*)ctx->flt.items, (void*)ctx->flt.istart, (void*)ctx->flt.range})
             if (q) (void)hipFree(q);
         for (void* q : {(void*)ctx->join.pre, (void*)ctx->join.keys, (void*)ctx->join.counts, (void*)ctx->join.lut,
-                        (void*)ctx->join.lo, (void*)ctx->join.spill_o, (void*)ctx->join.cls, (void*)ctx->join.cls2,
+                        (void*)ctx->join.lo, (void*)ctx->join.at, (void*)ctx->join.spill_o, (void*)ctx->join.cls, (void*)ctx->join.cls2,
                         (void*)ctx->join.pairs0, (void*)ctx->join.pairs1, (void*)ctx->join.ent,
                         (void*)ctx->join.sent, (void*)ctx->join.spill, (void*)ctx->join.extra,
                         (void*)ctx->join.temp, (void*)ctx->join.ctl})
             if (q) (void)hipFree(q);
-        if (ctx->join.h_totals) (void)hipHostFree(ctx->join.h_totals);
+        if (ctx->join.h_meets) (void)hipHostFree(ctx->join.h_meets);
         if (ctx->join.h_pairs) (void)hipHostFree(ctx->join.h_pairs);
         if (ctx->join.ev) (void)hipEventDestroy(ctx->join.ev);
         if (ctx->d_count) (void)hipFree(ctx->d_count);
@@ -1703,7 +1705,7 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     if (coll->n_sets == 0 || m64 >= (1ull << 30)) return SSJ_OK;
     const size_t m = (size_t)m64;
     if (!J.ctl) {
-        HIP_OR_FAIL(ctx, hipHostMalloc((void**)&J.h_totals, 2 * sizeof(unsigned long long), hipHostMallocDefault));
+        HIP_OR_FAIL(ctx, hipHostMalloc((void**)&J.h_meets, sizeof(unsigned long long), hipHostMallocDefault));
         HIP_OR_FAIL(ctx, hipEventCreateWithFlags(&J.ev, hipEventDisableTiming));
         ssj::JoinCtl* ctl = nullptr;
         HIP_OR_FAIL(ctx, hipMalloc((void**)&ctl, sizeof(ssj::JoinCtl)));
@@ -1716,7 +1718,6 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     a.key_bits = 1;
     while (a.key_bits < 32 && (coll->max_token >> a.key_bits) != 0) ++a.key_bits;
     const size_t digits = (size_t)1 << std::min(a.key_bits, ssj::kSortBits);
-    const uint32_t extra = ssj::join_extra_cap((uint32_t)m);
     if (n_classes) {
         HIP_OR_FAIL(ctx, grow(J.cls, J.cls_cap, (size_t)n_classes + 1));
         HIP_OR_FAIL(ctx, grow(J.cls2, J.cls2_cap, n_classes));
@@ -1731,8 +1732,10 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     // the digit counts per tile, then the digit totals
     HIP_OR_FAIL(ctx, grow(J.counts, J.counts_cap, digits * ((size_t)ssj::join_tiles((uint32_t)m) + 1)));
     HIP_OR_FAIL(ctx, grow(J.sent, J.sent_cap, m));
+    HIP_OR_FAIL(ctx, grow(J.at, J.at_cap, m));
     HIP_OR_FAIL(ctx, grow(J.lo, J.lo_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.extra, J.extra_cap, extra));
+    a.extra_cap = ssj::join_extra_cap((uint32_t)m);
+    HIP_OR_FAIL(ctx, grow(J.extra, J.extra_cap, (size_t)ssj::kExtraLists * a.extra_cap));
     HIP_OR_FAIL(ctx, grow(J.spill, J.spill_cap, ssj::kSpillCap));
     HIP_OR_FAIL(ctx, grow(J.spill_o, J.spill_o_cap, ssj::kSpillCap));
     a.heads = coll->d_heads;
@@ -1759,13 +1762,21 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     a.totals = J.counts;
     a.counts = J.counts + digits;
     a.sent = J.sent;
+    a.at = J.at;
     a.lo = J.lo;
     a.extra = J.extra;
-    a.extra_cap = extra;
     a.spill = J.spill;
     a.spill_o = J.spill_o;
     a.ctl = J.ctl;
-    a.h_totals = J.h_totals;
+    a.h_meets = J.h_meets;
+    // sizes 1 .. max_len in groups that differ by less than the factor t (at
+    // most as many as there are sizes)
+    a.size_groups = 1;
+    if (n_classes) {
+        const double f = (double)t_num / (double)t_den;
+        const double g = f < 1.0 ? std::log((double)coll->max_len) / -std::log(f) + 2.0 : (double)n_classes;
+        a.size_groups = (uint32_t)std::min(g, (double)n_classes);
+    }
     size_t tb = 0;
     HIP_OR_FAIL(ctx, ssj::join_index(a, nullptr, &tb, ctx->n_cu, st));
     HIP_OR_FAIL(ctx, grow(J.temp, J.temp_cap, std::max<size_t>(tb, 1)));
@@ -1783,7 +1794,7 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
         if (want > (1u << 20)) {
             HIP_OR_FAIL(ctx, bounded ? hipStreamSynchronize(st) : hipEventSynchronize(J.ev));
             waited = true;
-            want = std::min<uint64_t>(want, std::min<uint64_t>(std::max<uint64_t>(J.h_totals[0], 1), ssj::kMaxMeets));
+            want = std::min<uint64_t>(want, std::min<uint64_t>(std::max<uint64_t>(*J.h_meets, 1), ssj::kMaxMeets));
         }
         HIP_OR_FAIL(ctx, grow(ctx->d_out, ctx->out_cap, (size_t)want));
         a.req.out = ctx->d_out;
@@ -1791,7 +1802,7 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     }
     HIP_OR_FAIL(ctx, ssj::join_probe(a, ctx->n_cu, st));
     if (!waited) HIP_OR_FAIL(ctx, hipEventSynchronize(J.ev));
-    *done = bounded || ssj::join_fits(J.h_totals[0], J.h_totals[1], a.m);
+    *done = bounded || ssj::join_fits(*J.h_meets, a.size_groups, a.m);
     return SSJ_OK;
 }
 
