@@ -335,8 +335,7 @@ def measure(W, args, src_hash):
     avg_in_ms = in_ms / launches
     avg_def_ms = def_ms / launches
     # in-order kernel alone, or with the deferred kernel when one runs (events
-    # right before and after each verification kernel; the one-wavefront
-    # finalize kernel is not included)
+    # right before and after each verification kernel)
     avg_kernel_ms = avg_in_ms + (avg_def_ms if deferred else 0.0)
     achieved = b_alg / (avg_kernel_ms * 1e-3) / 1e9 if avg_kernel_ms > 0 else 0.0
     kname = kernel_name_of(plan)

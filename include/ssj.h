@@ -169,7 +169,7 @@ int ssj_verify_device(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand
  * nothing -- no hipMalloc / hipFree, no graph, no timing events.  Its
  * counters and deferral queues live in a fixed device array that the library
  * holds on each device from ssj_init until the process ends
- * (SSJ_NOALLOC_SCRATCH_BYTES: a 256-byte counter block plus 6 queue words per
+ * (SSJ_NOALLOC_SCRATCH_BYTES: 8 KiB for the counters plus 6 queue words per
  * pair for SSJ_NOALLOC_MAX_PAIRS pairs, about 24 MiB).
  * n_cand above SSJ_NOALLOC_MAX_PAIRS returns SSJ_EINVAL without enqueuing
  * anything (split larger inputs into several calls).  Every call on one
@@ -178,7 +178,7 @@ int ssj_verify_device(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand
  * Each launch leaves the counters zeroed for the next.
  */
 #define SSJ_NOALLOC_MAX_PAIRS (1 << 20)
-#define SSJ_NOALLOC_SCRATCH_BYTES (256 + 6 * 4 * SSJ_NOALLOC_MAX_PAIRS)
+#define SSJ_NOALLOC_SCRATCH_BYTES (8192 + 6 * 4 * SSJ_NOALLOC_MAX_PAIRS)
 int ssj_verify_device_noalloc(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand,
                               int64_t n_cand, int64_t t_num, int64_t t_den, ssj_pair* d_out,
                               int64_t out_cap, int64_t* d_count, void* hip_stream);

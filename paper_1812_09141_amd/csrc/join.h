@@ -10,7 +10,6 @@
 
 namespace ssj {
 
-constexpr uint32_t kSlots = 32;  // counters that the workgroups of a kernel spread over
 constexpr uint32_t kExtraLists = 8;
 constexpr uint32_t kUnitMeets = 2048;  // meetings per work unit of the probe kernel
 

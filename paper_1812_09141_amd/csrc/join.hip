@@ -391,9 +391,6 @@ __device__ __forceinline__ uint32_t list_begin(const uint2* __restrict__ list, c
     return good;
 }
 
-// Waits until every memory operation of the wavefront has completed.
-__device__ __forceinline__ void memory_wait() { asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory"); }
-
 // Entries in list order, the range of list entries that each meets, and the
 // work units of the probe kernel: a unit is up to kUnitMeets meetings of one
 // group of 64 consecutive entries.  The first unit of group g is unit g; groups
@@ -503,13 +500,6 @@ __device__ __forceinline__ bool common_window(const int32_t* __restrict__ tok, u
         hit |= eq && 4u * wa + k < i;
     }
     return hit;
-}
-
-__device__ __forceinline__ uint32_t load_agent(const unsigned int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ unsigned long long load_agent(const unsigned long long* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 // Moves the wavefront's c staged pairs to the output.

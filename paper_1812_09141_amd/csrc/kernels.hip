@@ -75,10 +75,6 @@ __device__ __forceinline__ int2 load_pair(const int2* __restrict__ cand, uint32_
     return cand[k];
 }
 
-__device__ __forceinline__ uint32_t load_relaxed(const unsigned int* p) {
-    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 // One thread: sequential early-terminating merge.
 __device__ __forceinline__ bool merge_thread(const int32_t* __restrict__ A, uint32_t na,
                                              const int32_t* __restrict__ B, uint32_t nb,
@@ -211,21 +207,58 @@ __device__ __forceinline__ void stage_pass(bool pass, int2 pr, int2* w_out, uint
 }
 
 // Moves the wavefront's c staged pairs of request r to the request's output
-// with one global atomic.  Called by the whole wavefront.
-__device__ void wave_flush_out(const LaunchArgs& a, int r, uint32_t c, const int2* w_out) {
-    wave_sync();
+// with one global atomic.  The pairs of a request without an output buffer are
+// only counted, in the workgroup's LDS (s_only).  Called by the whole
+// wavefront.
+__device__ void wave_flush_out(const LaunchArgs& a, int r, uint32_t c, const int2* w_out, uint32_t* s_only) {
     const int lane = lane_id();
+    if (a.req[r].cap == 0) {
+        if (lane == 0) atomicAdd(&s_only[r], c);
+        return;
+    }
+    wave_sync();
     unsigned long long base = 0ull;
     if (lane == 0) base = atomicAdd(&a.ctr->out_count[r], (unsigned long long)c);
     base = lane0_u64(base);
     const Request& R = a.req[r];
-    if (R.cap != 0) {
-        for (uint32_t i = (uint32_t)lane; i < c; i += kWave) {
-            const unsigned long long k = base + i;
-            if (k < R.cap) R.out[k] = w_out[i];
-        }
+    for (uint32_t i = (uint32_t)lane; i < c; i += kWave) {
+        const unsigned long long k = base + i;
+        if (k < R.cap) R.out[k] = w_out[i];
     }
     wave_sync();
+}
+
+// Called by one wavefront of every workgroup when all memory operations of
+// the workgroup have completed (memory_wait in each of its wavefronts): the
+// workgroup counts as finished, on one of kSlots addresses, and the last one of
+// the grid publishes each request's count (-1 after an id error) and returns
+// the counters to zero for the next launch.  Counts and flags are read with
+// atomics, which the others' completed atomics precede, so no fence is needed
+// (a device-scope fence per workgroup writes back the XCD's L2 and cost about
+// 60 us per launch; a kernel of its own for this took 4.6 us).
+__device__ void finish_workgroup(const LaunchArgs& a) {
+    const int lane = lane_id();
+    uint32_t last = 0;
+    if (lane == 0) {
+        const uint32_t slot = blockIdx.x % kSlots;
+        const uint32_t of = (gridDim.x - slot + kSlots - 1u) / kSlots;
+        if (atomicAdd(&a.ctr->slot[slot].done, 1u) == of - 1u)
+            last = atomicAdd(&a.ctr->done, 1u) == min(gridDim.x, kSlots) - 1u ? 1u : 0u;
+    }
+    if (__builtin_amdgcn_readfirstlane((int)last) == 0) return;
+    if (lane < a.n_req) {
+        const unsigned long long cnt = load_agent(&a.ctr->out_count[lane]);
+        const unsigned err = load_agent(&a.ctr->err[lane]);
+        *a.req[lane].d_count = err ? -1ll : (long long)cnt;
+        a.ctr->out_count[lane] = 0ull;
+        a.ctr->err[lane] = 0u;
+    }
+    if (lane < kQueues) {
+        a.ctr->head[lane] = 0u;
+        a.ctr->tail[lane] = 0u;
+    }
+    if (lane < (int)kSlots) a.ctr->slot[lane].done = 0u;
+    if (lane == 0) a.ctr->done = 0u;
 }
 
 // Entries of class q in the wavefront's deferred queues: 8 bits per class
@@ -691,7 +724,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     // staged output pairs per wavefront: every flush is one atomic on the
     // request's counter, and same-address atomics from all wavefronts are
     // serialised, so flushes carry at least kWStage - kWave pairs
-    constexpr uint32_t kWStage = kWaveStage;
+    constexpr uint32_t kWStage = wave_stage(S);
     // the wavefront index is uniform in the wavefront: taken through a scalar
     // register for the chunk walk (which then stays scalar); the LDS
     // addresses use the per-lane copy (vector registers are the cheaper ones)
@@ -720,6 +753,12 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     // the window rings of merge_ring
     __shared__ uint4 s_ring[S ? kWaves * kRingSlots : 1];
     uint4* w_ring = s_ring + (S ? wl * kRingSlots : 0u);
+    // pairs of the requests without an output buffer, and the wavefronts that
+    // have finished
+    __shared__ uint32_t s_only[kMaxReq], s_finished;
+    if (threadIdx.x < (unsigned)kMaxReq) s_only[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) s_finished = 0u;
+    __syncthreads();
     uint32_t ocnt = 0, hcnt = 0;
     unsigned long long dc = 0ull;  // deferred queue fill counts (dcount)
     const uint32_t n_chunks = a.tile_off[a.n_req];
@@ -879,7 +918,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
         // fit, or when the next chunk belongs to another request
         const bool same_next = Tn < n_chunks && r_cur == r;
         if (ocnt > 0 && ((R.cap != 0 && ocnt > kWStage - kWave) || !same_next)) {
-            wave_flush_out(a, r, ocnt, w_out);
+            wave_flush_out(a, r, ocnt, w_out, s_only);
             ocnt = 0;
         }
         if (deferring) {
@@ -898,24 +937,16 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
             if (dcount(dc, q) > 0) wave_flush_deferred(a, q, dcount(dc, q), w_defer);
         }
     }
-}
-
-// Publishes each request's count (-1 after an id error) and returns the
-// counters to zero for the next launch.  One workgroup, after the verify
-// kernels of the launch (the kernel boundary makes their atomics visible).
-__global__ void k_finalize(LaunchArgs a) {
-    const int t = (int)threadIdx.x;
-    if (t < a.n_req) {
-        const unsigned long long cnt = a.ctr->out_count[t];
-        const unsigned err = a.ctr->err[t];
-        *a.req[t].d_count = err ? -1ll : (long long)cnt;
-        a.ctr->out_count[t] = 0ull;
-        a.ctr->err[t] = 0u;
-    }
-    if (t < kQueues) {
-        a.ctr->head[t] = 0u;
-        a.ctr->tail[t] = 0u;
-    }
+    // the workgroup's last wavefront adds its counts and finishes it
+    memory_wait();
+    uint32_t fin = 0;
+    if (lane == 0) fin = atomicAdd(&s_finished, 1u);
+    if ((uint32_t)__builtin_amdgcn_readfirstlane((int)fin) != kWaves - 1u) return;
+    wave_sync();
+    if (lane < kMaxReq && s_only[lane] != 0u) atomicAdd(&a.ctr->out_count[lane], (unsigned long long)s_only[lane]);
+    if (a.two_kernels) return;
+    memory_wait();
+    finish_workgroup(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1025,12 +1056,12 @@ __global__ __launch_bounds__(kBlock) void k_verify_deferred(LaunchArgs a) {
     for (int q = kQueues - 1; q >= 0; --q) {
         if (q < a.defer_from && q != kSpillQ) break;
         if (lanes_of_queue(a, q) != kBlock) continue;
-        const uint32_t cnt = load_relaxed(&a.ctr->tail[q]);
+        const uint32_t cnt = load_agent(&a.ctr->tail[q]);
         const uint32_t* queue = a.queues + (size_t)q * a.qcap;
         for (;;) {
             if (threadIdx.x == 0) {
                 // a plain read first: no atomic traffic once the queue is drained
-                s_tile = load_relaxed(&a.ctr->head[q]) >= cnt ? cnt : atomicAdd(&a.ctr->head[q], 1u);
+                s_tile = load_agent(&a.ctr->head[q]) >= cnt ? cnt : atomicAdd(&a.ctr->head[q], 1u);
             }
             __syncthreads();
             const uint32_t t = s_tile;
@@ -1052,7 +1083,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_deferred(LaunchArgs a) {
     }
     for (int q = kQueues - 1; q >= 0; --q) {
         if (q < a.defer_from && q != kSpillQ) break;
-        const uint32_t cnt = load_relaxed(&a.ctr->tail[q]);
+        const uint32_t cnt = load_agent(&a.ctr->tail[q]);
         if (cnt == 0) continue;
         switch (lanes_of_queue(a, q)) {
             case 1: drain_static<1, C, GR>(a, q, cnt); break;
@@ -1064,6 +1095,9 @@ __global__ __launch_bounds__(kBlock) void k_verify_deferred(LaunchArgs a) {
             default: break;
         }
     }
+    memory_wait();
+    __syncthreads();
+    if (threadIdx.x < (unsigned)kWave) finish_workgroup(a);
 }
 
 // ---------------------------------------------------------------------------
@@ -1205,9 +1239,9 @@ hipError_t launch_build_heads(const int64_t* d_offsets, const uint32_t* d_start,
 }
 
 size_t tiles_lds_bytes(const LaunchArgs& a) {
-    // per wavefront: kWaveStage staged output pairs, then defer_cap entries
+    // per wavefront: wave_stage staged output pairs, then defer_cap entries
     // per queue (a multiple of 16 bytes)
-    const size_t stage = (size_t)kWaveStage * sizeof(int2);
+    const size_t stage = (size_t)wave_stage(a.staged != 0) * sizeof(int2);
     const size_t defer = (size_t)wave_queues(a.defer_from, spilling(a)) * a.defer_cap * 4u;
     return (size_t)(kBlock / kWave) * (stage + defer);
 }
@@ -1227,13 +1261,6 @@ hipError_t launch_clear_words(uint32_t* d_words, size_t n, hipStream_t st) {
     hipLaunchKernelGGL(k_clear_words, dim3((unsigned)b), dim3(kBlock), 0, st, d_words, (uint32_t)n);
     return hipGetLastError();
 }
-
-hipError_t launch_finalize(const LaunchArgs& a, hipStream_t st) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kWave), 0, st, a);
-    return hipGetLastError();
-}
-
-const void* kernel_finalize() { return (const void*)&k_finalize; }
 
 hipError_t launch_verify_deferred(const LaunchArgs& a, int grid, hipStream_t st) {
     const void* f = kernel_verify_deferred(a.cosine != 0, a.grouped != 0);

@@ -174,13 +174,13 @@ struct GraphKey {
     }
 };
 
-// A launch as a graph of kernel nodes (in-order, [deferred], finalize) whose
+// A launch as a graph of kernel nodes (in-order, [deferred]) whose
 // arguments are replaced before every replay.
 struct GraphEntry {
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
-    hipGraphNode_t nodes[3] = {nullptr, nullptr, nullptr};
-    hipKernelNodeParams params[3] = {};
+    hipGraphNode_t nodes[2] = {nullptr, nullptr};
+    hipKernelNodeParams params[2] = {};
     int n_nodes = 0;
 };
 
@@ -385,6 +385,22 @@ bool plan_valid(const ssj_plan& p) {
 // A plan runs the deferred kernel when it defers classes or cuts merges off.
 bool plan_two_kernels(const ssj_plan& p) { return p.defer_from < ssj::kClasses || p.spill_iters > 0; }
 
+// The plan as far as it concerns sets of at most max_r and max_s tokens: a
+// class that no pair is long enough for is not deferred to, and a budget that
+// no merge can outrun (every window step uses up a window of a side) is none.
+// Without either the launch is the in-order kernel alone, whose instance has
+// no queueing code (206 pairs of sets of about 12 tokens with a new context's
+// plan: 16.7 -> 11.1 us; with sets of 2,000 tokens both kernels run as before).
+ssj_plan plan_for(const ssj_plan& plan, int64_t max_r, int64_t max_s) {
+    constexpr uint32_t bounds[ssj::kClasses] = SSJ_CLASS_BOUNDS;
+    ssj_plan p = plan;
+    int longest = 0;
+    while (longest < ssj::kClasses - 1 && max_r + max_s > (int64_t)bounds[longest]) ++longest;
+    if (longest < p.defer_from) p.defer_from = ssj::kClasses;
+    if ((max_r + 3) / 4 + (max_s + 3) / 4 <= p.spill_iters) p.spill_iters = 0;
+    return p;
+}
+
 hipEvent_t timing_event(ssj_ctx* ctx) {
     std::lock_guard<std::mutex> g(ctx->tmu);
     if (!ctx->ev_pool.empty()) {
@@ -468,17 +484,15 @@ int launch_graph(ssj_ctx* ctx, const ssj::LaunchArgs& a, int g1, int g2, bool tw
         GraphEntry ge;
         HIP_OR_FAIL(ctx, hipGraphCreate(&ge.graph, 0));
         // (grouped launches do not use graphs)
-        const void* funcs[3] = {ssj::kernel_verify_tiles(a.inline_lanes, a.hard_lanes, a.staged != 0, two,
+        const void* funcs[2] = {ssj::kernel_verify_tiles(a.inline_lanes, a.hard_lanes, a.staged != 0, two,
                                                          a.cosine != 0, false),
-                                ssj::kernel_verify_deferred(a.cosine != 0, false), ssj::kernel_finalize()};
-        const int grids[3] = {g1, g2, 1};
-        const int blocks[3] = {ssj::kBlock, ssj::kBlock, ssj::kWave};
-        for (int k = 0; k < 3; ++k) {
-            if (k == 1 && !two) continue;
+                                ssj::kernel_verify_deferred(a.cosine != 0, false)};
+        const int grids[2] = {g1, g2};
+        for (int k = 0; k < (two ? 2 : 1); ++k) {
             hipKernelNodeParams p{};
             p.func = const_cast<void*>(funcs[k]);
             p.gridDim = dim3((unsigned)grids[k]);
-            p.blockDim = dim3((unsigned)blocks[k]);
+            p.blockDim = dim3((unsigned)ssj::kBlock);
             p.sharedMemBytes = k == 0 ? (unsigned)ssj::tiles_lds_bytes(a) : 0u;
             p.kernelParams = kparams;
             p.extra = nullptr;
@@ -505,9 +519,10 @@ int launch_graph(ssj_ctx* ctx, const ssj::LaunchArgs& a, int g1, int g2, bool tw
 // Enqueues one launch verifying up to kMaxReq requests already on the device:
 // r ids index coll, s ids coll_s (null: coll, a self-join).
 int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* reqs, int n_req,
-                   hipStream_t st, const ssj_plan& plan, bool allow_graph = true,
+                   hipStream_t st, const ssj_plan& ctx_plan, bool allow_graph = true,
                    const ssj_coll* coll_s = nullptr, bool allow_timing = true) {
     const ssj_coll* cs = coll_s ? coll_s : coll;
+    const ssj_plan plan = plan_for(ctx_plan, coll->max_len, cs->max_len);
     ssj::LaunchArgs a{};
     a.tok = coll->d_tok;
     a.heads = coll->d_heads;
@@ -564,6 +579,7 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     a.pair_off[n_req] = (uint32_t)pairs;
     a.group_off[n_req] = (uint32_t)groups;
     const bool two = plan_two_kernels(plan);
+    a.two_kernels = two ? 1u : 0u;
     if (two) {
         HIP_OR_FAIL(ctx, grow(sc.d_queues, sc.q_cap, (size_t)ssj::kQueues * std::max<uint64_t>(pairs, 1)));
     }
@@ -589,8 +605,7 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     const int period = ctx->timing_period.load();
     const bool timing = allow_timing && period > 0 && (ctx->timing_tick.fetch_add(1) % (uint64_t)period) == 0;
     if (timing) {
-        // marker events right before and after each verification kernel (the
-        // finalize kernel is not timed)
+        // marker events right before and after each verification kernel
         for (int k = 0; k < (two ? 4 : 2); ++k) {
             ev[k] = timing_event(ctx);
             if (!ev[k]) return hip_fail(ctx, "hipEventCreate", hipErrorOutOfMemory);
@@ -611,7 +626,6 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
             HIP_OR_FAIL(ctx, ssj::launch_verify_deferred(a, g2, st));
             if (timing) HIP_OR_FAIL(ctx, hipEventRecord(ev[3], st));
         }
-        HIP_OR_FAIL(ctx, ssj::launch_finalize(a, st));
     }
     if (timing) {
         std::lock_guard<std::mutex> g(ctx->tmu);
@@ -1001,8 +1015,7 @@ void engine_loop(StreamEngine* E) {
 
 // Takes this device's address of scratch (once per device, with the device
 // current) and clears its counter block with a fill kernel; the context
-// keeps views of it.  Every launch's finalize kernel leaves the counters at
-// zero again.
+// keeps views of it.  Every launch leaves the counters at zero again.
 int noalloc_setup(ssj_ctx* ctx) {
     if (ctx->device >= kMaxDevices) return set_error(SSJ_EINVAL, "device ordinal too large");
     void* ptr = nullptr;

@@ -13,7 +13,11 @@ constexpr int kBlock = 256;      // threads per workgroup of every verify kernel
 constexpr int kWave = 64;        // CDNA wavefront width
 constexpr int kMaxReq = 16;      // requests per launch
 constexpr int kHeadTokens = 6;   // leading tokens kept in each 32-byte set record
-constexpr unsigned kWaveStage = 8 * kWave;  // staged output pairs per wavefront (in-order kernel)
+// Staged output pairs per wavefront (in-order kernel).  The window ring takes
+// 24 KiB of LDS per workgroup, which with 512 pairs leaves four workgroups per
+// compute unit; with 256 there are five (620,000 pairs of long sets, with the
+// count published by the last kernel: 137 -> 128 us).
+__host__ __device__ constexpr unsigned wave_stage(bool staged) { return staged ? 4u * kWave : 8u * kWave; }
 
 // How a request turns set sizes into its required overlap alpha (the
 // equivalent overlap of paper Table 1).
@@ -50,15 +54,22 @@ struct Request {
     uint32_t pad;
 };
 
-// Per-launch device counters.  Every launch leaves them zeroed again (its
-// final one-workgroup kernel resets them), so no memset is needed before a
+constexpr unsigned kSlots = 32;  // counters that the workgroups of a kernel spread over: an atomic
+                                 // on one address takes about 10 ns, whoever issues it
+
+// Per-launch device counters.  Every launch leaves them zeroed again (the last
+// workgroup of its last kernel resets them), so no memset is needed before a
 // launch, also not inside a captured graph.
 struct alignas(256) Counters {
     unsigned long long out_count[kMaxReq];  // passing pairs appended so far
     unsigned int err[kMaxReq];              // != 0: an id was out of range
     unsigned int head[kQueues];             // work-stealing cursors of the queues
     unsigned int tail[kQueues];             // entries in each queue
-    unsigned int pad[64 - kMaxReq - 2 * kQueues];
+    unsigned int done;                      // slots whose workgroups have all finished
+    unsigned int pad[63 - kMaxReq - 2 * kQueues];
+    struct alignas(128) {
+        unsigned int done;                  // workgroups that have finished
+    } slot[kSlots];
 };
 
 // Everything one launch needs (passed by value as the kernel argument).
@@ -86,6 +97,7 @@ struct LaunchArgs {
                                          // ring in LDS, their loads two steps ahead
                                          // (merge_ring); spill_iters counts window steps
     uint32_t grouped;                    // != 0: every request of the launch is grouped
+    uint32_t two_kernels;                // != 0: the deferred kernel follows (and publishes the counts)
     uint32_t* probes;                    // grouped launches that defer: the probe id of every
                                          // queued pair, by global pair index
     uint4* spill_state;                  // launches whose merges spill: {i, j, o, 0} of every
@@ -110,10 +122,12 @@ hipError_t launch_build_heads(const int64_t* d_offsets, const uint32_t* d_start,
                               uint4* d_heads, int64_t n_sets, hipStream_t st);
 // Group pre-pass of a grouped launch (a.grouped): writes every request's
 // chunk_g and checks its group ends (not decreasing, none above n, the last
-// one n); malformed ends set the request's error flag, which the launch's
-// finalize kernel reports.  Candidates no group covers are verified with
-// probe id -1, an id error.
+// one n); malformed ends set the request's error flag, which the launch
+// reports.  Candidates no group covers are verified with probe id -1, an id
+// error.
 hipError_t launch_group_chunks(const LaunchArgs& a, hipStream_t st);
+// (The last kernel of a launch publishes the request counts and resets the
+// counters: the in-order kernel, or with two_kernels the deferred one.)
 // The in-order kernel: every pair of a class below defer_from is verified
 // with inline_lanes lanes; the others are queued for launch_verify_deferred,
 // and so is every thread-per-pair merge still undecided after spill_iters
@@ -123,8 +137,6 @@ hipError_t launch_verify_tiles(const LaunchArgs& a, int grid, hipStream_t st);
 hipError_t launch_verify_deferred(const LaunchArgs& a, int grid, hipStream_t st);
 // Dynamic LDS of the in-order kernel for a.defer_from / a.spill_iters / a.defer_cap.
 size_t tiles_lds_bytes(const LaunchArgs& a);
-// Publishes the request counts and resets the counters (always last).
-hipError_t launch_finalize(const LaunchArgs& a, hipStream_t st);
 // Zeroes n 32-bit words of device memory with a fill kernel.
 hipError_t launch_clear_words(uint32_t* d_words, size_t n, hipStream_t st);
 
@@ -134,7 +146,6 @@ hipError_t launch_clear_words(uint32_t* d_words, size_t n, hipStream_t st);
 // staged selects the plain one).
 const void* kernel_verify_tiles(int lanes, int hard_lanes, bool staged, bool deferring, bool cosine, bool grouped);
 const void* kernel_verify_deferred(bool cosine, bool grouped);
-const void* kernel_finalize();
 
 // LDS queues of a wavefront of the in-order kernel: one per deferred class,
 // one more for spilled merges.

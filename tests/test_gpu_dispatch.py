@@ -1,0 +1,94 @@
+"""Launches at the edges of the rules that pick their kernels and at the ends of
+their workgroups: the longest pair just inside and just outside a deferred
+class, step budgets at the longest merge, and batches that mix requests with
+and without an output buffer, with more chunks than wavefronts of a workgroup;
+against the oracle (whole numbers: no tolerance)."""
+import os
+import sys
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, ROOT)
+
+import oracle  # noqa: E402
+from ssj_inputs import synth  # noqa: E402
+
+
+@pytest.fixture(scope="module")
+def S():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    import paper_1812_09141_amd.ssj as ssj
+    ssj.load_library()
+    return ssj
+
+
+@pytest.fixture(scope="module")
+def ctx(S):
+    c = S.ssj_init(0)
+    yield c
+    S.ssj_shutdown(c)
+
+
+def _pairs(n, k, seed):
+    return np.random.default_rng(seed).integers(0, n, (k, 2)).astype(np.int32)
+
+
+@pytest.mark.parametrize("longest", [16, 17, 64, 65, 256, 257])
+def test_longest_pair_at_a_class_bound(S, ctx, longest):
+    # pairs of the two longest sets have 2 longest - 1 and 2 longest tokens:
+    # 32 | 33, 128 | 129, 512 | 513 lie on either side of a bound
+    rng = np.random.default_rng(700 + longest)
+    base = np.sort(rng.choice(4 * longest, longest, replace=False))
+    sets = [np.sort(rng.choice(base, size=int(rng.integers(max(1, longest // 2), longest)), replace=False)).tolist()
+            for _ in range(150)]
+    sets += [base.tolist(), base[1:].tolist(), base.tolist()]
+    c = synth.collection_from_sets(sorted(sets, key=len))
+    cand = _pairs(c.n_sets, 5000, 1)
+    cand[:3] = [[c.n_sets - 1, c.n_sets - 2], [c.n_sets - 1, c.n_sets - 3], [c.n_sets - 3, c.n_sets - 2]]
+    steps = 2 * ((longest + 3) // 4)  # window steps that no merge outruns
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        for tn, td in [(1, 2), (9, 10)]:
+            want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, tn, td))
+            for kw in [dict(defer_from=d, lanes=(4, 8, 16, 64, 256)) for d in range(6)] + \
+                      [dict(defer_from=5, spill_iters=s, staged=g) for s in (steps - 1, steps) for g in (0, 1)]:
+                print(f"longest {longest} t={tn}/{td} {kw}", flush=True)
+                S.ssj_set_plan(ctx, S.make_plan(**kw))
+                assert np.array_equal(oracle.sort_pairs(S.ssj_verify(ctx, h, cand, tn, td)), want)
+    finally:
+        S.ssj_free_collection(ctx, h)
+
+
+@pytest.mark.parametrize("staged", [0, 1])
+def test_batch_of_counts_and_pairs(S, ctx, staged):
+    import torch
+    c = synth.near_duplicate_collection(np.random.default_rng(5), n_base=80, copies=4, max_size=30, universe=300)
+    S.ssj_set_plan(ctx, S.make_plan(defer_from=5, staged=staged, wg_per_cu=1))
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        sizes = [1, 63, 64, 65, 0, 300, 5000, 200_000, 64, 1, 70_000]
+        d_cnt = torch.full((len(sizes),), -7, dtype=torch.int64, device="cuda:0")
+        reqs, want, outs = [], [], []
+        for i, n in enumerate(sizes):
+            cand = _pairs(c.n_sets, n, 40 + i)
+            tn, td = [(1, 10), (1, 2), (0, 1)][i % 3]  # at 0 every pair passes: more than are staged
+            want.append(oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, tn, td)))
+            out = None if i % 2 else torch.full((max(n, 1), 2), -1, dtype=torch.int32, device="cuda:0")
+            outs.append(out)
+            reqs.append((torch.from_numpy(cand).to("cuda:0"), tn, td, out, d_cnt[i:i + 1]))
+        for _ in range(3):  # the counters return to zero after each launch
+            d_cnt.fill_(-7)
+            S.ssj_verify_batch_device(ctx, h, reqs)
+            torch.cuda.synchronize()
+            for i, w in enumerate(want):
+                assert int(d_cnt[i].item()) == w.shape[0], i
+                if outs[i] is not None:
+                    assert np.array_equal(oracle.sort_pairs(outs[i][:w.shape[0]].cpu().numpy()), w), i
+    finally:
+        S.ssj_free_collection(ctx, h)
