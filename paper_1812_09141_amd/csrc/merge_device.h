@@ -10,6 +10,27 @@ namespace {
 
 // Required overlap of a pair with sizes na, nb under the request's rule
 // (paper Table 1, in integers).
+//
+// Cosine for sizes below kCosineSizes and threshold terms below kCosineTerms:
+// the least o with (o den)^2 >= num^2 na nb.  The single-precision estimate of
+// num / den sqrt(na nb), below 2^16, is off by less than 2^-5 (five roundings
+// of 2^-23 at most), so its integer part less one is at most three below o and
+// never above it; exact steps finish the job.  3.4M pairs of two collections of
+// short sets at 3/5: 187.5 us a pass with the 128-bit form, 183.5 us so.
+__device__ __forceinline__ uint32_t cosine_overlap_small(uint32_t na, uint32_t nb, uint32_t num, uint32_t den,
+                                                         float ratio) {
+    const uint32_t p = na * nb;
+    const unsigned long long x = (unsigned long long)(num * num) * p;
+    const uint32_t e = (uint32_t)(ratio * __builtin_amdgcn_sqrtf((float)p));
+    uint32_t o = e > 0u ? e - 1u : 0u;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        const unsigned long long v = o * den;
+        o += v * v < x ? 1u : 0u;
+    }
+    return o;
+}
+
 __device__ __forceinline__ uint32_t cosine_overlap(uint32_t na, uint32_t nb, unsigned long long tn,
                                                    unsigned long long td) {
     // least o with (o td)^2 >= tn^2 na nb; both sides stay below 2^124.  A
@@ -28,7 +49,11 @@ __device__ __forceinline__ uint32_t cosine_overlap(uint32_t na, uint32_t nb, uns
 template <bool C>
 __device__ __forceinline__ uint32_t required_overlap(uint32_t na, uint32_t nb, const Request& R) {
     if constexpr (C) {
-        if (R.rule == kCosine) return cosine_overlap(na, nb, R.num, R.den);
+        if (R.rule == kCosine) {
+            if (R.cosine_ratio != 0.0f)
+                return cosine_overlap_small(na, nb, (uint32_t)R.num, (uint32_t)R.den, R.cosine_ratio);
+            return cosine_overlap(na, nb, R.num, R.den);
+        }
     }
     if (R.rule == kConstant) return (uint32_t)R.num;
     const unsigned long long L = (unsigned long long)na + nb;

@@ -18,6 +18,7 @@
 #include <map>
 #include <memory>
 #include <mutex>
+#include <numeric>
 #include <string>
 #include <thread>
 #include <tuple>
@@ -97,7 +98,8 @@ void division_magic(unsigned long long d, ssj::Request& R) {
     R.dshift = (uint32_t)std::min(l, 1) | ((uint32_t)std::max(l - 1, 0) << 8);
 }
 
-void overlap_rule(int sim, int64_t t_num, int64_t t_den, ssj::Request& R) {
+// max_r and max_s: the largest sets of the two sides.
+void overlap_rule(int sim, int64_t t_num, int64_t t_den, int64_t max_r, int64_t max_s, ssj::Request& R) {
     switch (sim) {
         case SSJ_SIM_DICE:
             R.rule = ssj::kLinear;
@@ -108,6 +110,12 @@ void overlap_rule(int sim, int64_t t_num, int64_t t_den, ssj::Request& R) {
             R.rule = ssj::kCosine;
             R.num = (unsigned long long)t_num;
             R.den = (unsigned long long)t_den;
+            if (const int64_t g = std::gcd(t_num, t_den);
+                t_num > 0 && t_den / g < ssj::kCosineTerms && max_r < ssj::kCosineSizes && max_s < ssj::kCosineSizes) {
+                R.num /= (unsigned long long)g;  // (t_num <= t_den)
+                R.den /= (unsigned long long)g;
+                R.cosine_ratio = (float)R.num / (float)R.den;
+            }
             break;
         case SSJ_SIM_OVERLAP:
             R.rule = ssj::kConstant;
@@ -561,7 +569,7 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
         R.out = q.d_out;
         R.d_count = q.d_count;
         R.cap = (unsigned long long)q.out_cap;
-        overlap_rule(q.sim, q.t_num, q.t_den, R);
+        overlap_rule(q.sim, q.t_num, q.t_den, coll->max_len, cs->max_len, R);
         if (R.rule == ssj::kCosine) a.cosine = 1u;
         R.n = (uint32_t)q.n;
         if (a.grouped) {
@@ -1757,7 +1765,7 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     a.m = (uint32_t)m;
     a.num = (unsigned long long)t_num;
     a.den = (unsigned long long)t_den;
-    overlap_rule(SSJ_SIM_JACCARD, t_num, t_den, a.req);
+    overlap_rule(SSJ_SIM_JACCARD, t_num, t_den, coll->max_len, coll->max_len, a.req);
     a.req.out = d_out;
     a.req.cap = (unsigned long long)out_cap;
     a.req.d_count = d_count;
@@ -2168,18 +2176,9 @@ int ssj_verify(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* cand, int64_t
 
 namespace {
 
-int64_t gcd64(int64_t a, int64_t b) {
-    while (b != 0) {
-        const int64_t t = a % b;
-        a = b;
-        b = t;
-    }
-    return a;
-}
-
 // Tuning cache key of a workload on the context's device.
 std::string tune_key(const ssj_ctx* ctx, const ssj_coll* coll, int64_t n_cand, int64_t t_num, int64_t t_den) {
-    const int64_t g = std::max<int64_t>(1, gcd64(t_num, t_den));
+    const int64_t g = std::max<int64_t>(1, std::gcd(t_num, t_den));
     return ctx->device_key + "|sets=" + std::to_string(coll->n_sets) + ",tokens=" + std::to_string(coll->n_tokens) +
            ",max_len=" + std::to_string(coll->max_len) + "|cand=" + std::to_string(n_cand) + "|t=" +
            std::to_string(t_num / g) + "/" + std::to_string(t_den / g);

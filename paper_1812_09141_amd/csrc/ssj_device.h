@@ -27,6 +27,11 @@ enum OverlapRule : uint32_t {
     kConstant = 2,  // alpha = num: Overlap
 };
 
+// Sizes, and terms of a threshold in lowest terms, up to which the Cosine rule
+// takes 64-bit arithmetic (kCosineSizes^2 kCosineTerms^2 <= 2^62).
+constexpr long long kCosineSizes = 1ll << 16;
+constexpr long long kCosineTerms = 1ll << 15;
+
 // One verification request inside a launch.
 struct Request {
     const int2* cand;          // (r, s) pairs
@@ -51,7 +56,7 @@ struct Request {
     // q = (t + ((x - t) >> (dshift & 0xff))) >> (dshift >> 8), t = mulhi(dmagic, x)
     uint32_t dmagic;
     uint32_t dshift;
-    uint32_t pad;
+    float cosine_ratio;        // kCosine in 64-bit arithmetic: num / den (0: it needs 128 bits)
 };
 
 constexpr unsigned kSlots = 32;  // counters that the workgroups of a kernel spread over: an atomic

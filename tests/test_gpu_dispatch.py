@@ -92,3 +92,34 @@ def test_batch_of_counts_and_pairs(S, ctx, staged):
                     assert np.array_equal(oracle.sort_pairs(outs[i][:w.shape[0]].cpu().numpy()), w), i
     finally:
         S.ssj_free_collection(ctx, h)
+
+
+@pytest.mark.parametrize("longest", [400, 65535, 65536])
+def test_cosine_at_the_threshold(S, ctx, longest):
+    """Prefixes of one set: of n and o <= n tokens the similarity is sqrt(o / n),
+    so o = n (t_num / t_den)^2 sits exactly at a threshold.  Sizes and threshold
+    terms (in lowest terms) on both sides of what 64-bit arithmetic takes."""
+    sims = [(3, 5), (60000, 100000), (1, 1), (181, 362), (32766, 32767), (32767, 32768), (32768, 32769),
+            (19, 20), ((1 << 31) - 2, (1 << 31) - 1)]
+    rng = np.random.default_rng(8)
+    lens = {1, 2, 3, longest - 1, longest}
+    for tn, td in sims:
+        for n in {longest, longest - 1, 25 * (longest // 25), 4, int(rng.integers(10, longest))}:
+            o = n * tn * tn // (td * td)
+            lens |= {x for x in (n, o - 1, o, o + 1) if 1 <= x <= longest}
+    lens = sorted(lens)
+    c = synth.collection_from_sets([list(range(x)) for x in lens])
+    r, s = np.tril_indices(c.n_sets, 0)
+    cand = np.stack([r, s], axis=1).astype(np.int32)
+    a, b = c.sizes()[r].astype(object), c.sizes()[s].astype(object)
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        S.ssj_set_plan(ctx, S.make_plan(defer_from=3, lanes=(4, 8, 16, 64, 256)))
+        for tn, td in sims:
+            # the overlap of two prefixes is the shorter one: o^2 td^2 >= tn^2 n o
+            keep = np.array([(y * td) ** 2 >= tn * tn * x * y for x, y in zip(a, b)], dtype=bool)
+            print(f"cosine {tn}/{td}, {longest}: {int(keep.sum())} of {cand.shape[0]}", flush=True)
+            got = oracle.sort_pairs(S.ssj_verify_sim(ctx, h, cand, "cosine", tn, td))
+            assert np.array_equal(got, oracle.sort_pairs(cand[keep])), (tn, td)
+    finally:
+        S.ssj_free_collection(ctx, h)
