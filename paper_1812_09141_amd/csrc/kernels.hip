@@ -163,11 +163,6 @@ __device__ bool merge_block(const int32_t* __restrict__ A, uint32_t na,
     }
 }
 
-__device__ __forceinline__ void append_one(int2 pr, const Request& R, unsigned long long* counter) {
-    const unsigned long long k = atomicAdd(counter, 1ull);
-    if (k < R.cap) R.out[k] = pr;
-}
-
 // Whether r indexes the r-side collection and s the s-side one.
 __device__ __forceinline__ bool ids_ok(int2 pr, const LaunchArgs& a) {
     return (uint32_t)pr.x < a.n_sets && (uint32_t)pr.y < a.n_sets_s;
@@ -623,14 +618,12 @@ __device__ __forceinline__ void chunk_thread_pairs(const LaunchArgs& a, const Re
     const uint32_t na = rec.ra0.y, nb = rec.rb0.y;
     const uint32_t L = na + nb;
     const int cls = deferring ? class_of(L, a) : 0;
-    const bool defer = ok && deferring && cls >= a.defer_from;
-    const bool run = ok && !defer;
-    const uint32_t alpha = run ? required_overlap<C>(na, nb, R) : 0u;
+    const uint32_t alpha = ok ? required_overlap<C>(na, nb, R) : 0u;
     uint32_t i = 0, j = 0, o = 0;
     bool pass = false, act = false;
     auto decide = [&]() {
-        pass = run && o >= alpha;
-        act = run && !pass && o + min(na - i, nb - j) >= alpha;
+        pass = ok && o >= alpha;
+        act = ok && !pass && o + min(na - i, nb - j) >= alpha;
     };
     // with try4 (wave-uniform) the head step first takes four record tokens
     // per side, and the six only when that left some lane of the chunk
@@ -646,6 +639,9 @@ __device__ __forceinline__ void chunk_thread_pairs(const LaunchArgs& a, const Re
         head_tiles<kHeadTokens>(rec.ra0, rec.ra1, rec.rb0, rec.rb1, &i, &j, &o);
         decide();
     }
+    // pairs of the deferred classes that the record tokens leave undecided
+    const bool defer = act && deferring && cls >= a.defer_from;
+    act = act && !defer;
     bool spill = false;
     if constexpr (F == 0) {
         const uint32_t budget = deferring ? a.spill_iters : 0xffffffffu;
@@ -988,11 +984,60 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Deferred classes.  Workgroup-mapped classes (lanes == kBlock) are taken one
-// pair per workgroup by work stealing; the others are split statically over
-// all wavefronts of the grid.
+// Deferred classes.  Workgroup-mapped classes (lanes == kBlock) are taken by
+// work stealing, a few pairs per workgroup at a time; the others are split
+// statically over all wavefronts of the grid.
+
+// Passing pairs of a wavefront of the deferred kernel, of any requests, in LDS.
+constexpr uint32_t kDeferStage = 2 * kWave;
+struct DeferStage {
+    int2* pr;        // kDeferStage
+    uint32_t* req;   // kDeferStage
+    uint32_t n;      // wave-uniform
+};
+
+// Moves entries [0, n) of a stage to their requests' outputs, with one atomic
+// per 64 entries and request.  Called by a whole wavefront.
+__device__ void flush_deferred_out(const LaunchArgs& a, const int2* pr, const uint32_t* req, uint32_t n) {
+    const int lane = lane_id();
+    wave_sync();
+    for (uint32_t b = 0; b < n; b += kWave) {
+        const uint32_t x = b + (uint32_t)lane;
+        const bool have = x < n;
+        const int2 p = pr[min(x, n - 1u)];
+        const uint32_t r = req[min(x, n - 1u)];
+        unsigned long long left = ballot(have);
+        while (left != 0ull) {
+            const uint32_t r0 = (uint32_t)__builtin_amdgcn_readlane((int)r, (int)__builtin_ctzll(left));
+            const unsigned long long same = ballot(have && r == r0);
+            unsigned long long base = 0ull;
+            if (lane == 0) base = atomicAdd(&a.ctr->out_count[r0], (unsigned long long)__popcll(same));
+            base = lane0_u64(base) + mbcnt(same);
+            if (have && r == r0 && base < a.req[r0].cap) a.req[r0].out[base] = p;
+            left &= ~same;
+        }
+    }
+    wave_sync();
+}
+
+// Stages the pairs of the lanes with pass set (all lanes of the wavefront
+// call it together).
+__device__ __forceinline__ void stage_deferred(const LaunchArgs& a, bool pass, int2 pr, int r, DeferStage& s) {
+    const unsigned long long m = ballot(pass);
+    if (m == 0ull) return;
+    if (s.n > kDeferStage - kWave) {
+        flush_deferred_out(a, s.pr, s.req, s.n);
+        s.n = 0;
+    }
+    if (pass) {
+        s.pr[s.n + mbcnt(m)] = pr;
+        s.req[s.n + mbcnt(m)] = (uint32_t)r;
+    }
+    s.n += (uint32_t)__popcll(m);
+}
+
 template <int G, bool C, bool GR>
-__device__ void drain_static(const LaunchArgs& a, int q, uint32_t cnt) {
+__device__ void drain_static(const LaunchArgs& a, int q, uint32_t cnt, DeferStage& stage) {
     constexpr int GPW = kWave / G;
     const int lane = lane_id();
     const int grp = lane / G, g = lane % G, gbase = grp * G;
@@ -1048,18 +1093,18 @@ __device__ void drain_static(const LaunchArgs& a, int q, uint32_t cnt) {
         const uint2 ds2 = set_desc_s(a, p2.y);
         const int32_t wa1 = first_tile_token(a.tok, suffix(dr1, st1.x), g);
         const int32_t wb1 = first_tile_token(a.tok_s, suffix(ds1, st1.y), g);
+        bool pass = false;
         if (t + (uint32_t)grp < cnt) {
             const Request& R = a.req[r0];
             const uint32_t alpha = required_overlap<C>(dr0.y, ds0.y, R) - st0.z;
             const uint2 ar = suffix(dr0, st0.x), as = suffix(ds0, st0.y);
-            bool pass;
             if constexpr (G == 1)
                 pass = merge_thread(a.tok + ar.x, ar.y, a.tok_s + as.x, as.y, alpha);
             else
                 pass = merge_group_first<G>(a.tok + ar.x, ar.y, a.tok_s + as.x, as.y, alpha, g, gbase, wa0,
                                             wb0);
-            if (pass && g == 0) append_one(p0, R, &a.ctr->out_count[r0]);
         }
+        stage_deferred(a, pass && g == 0, p0, r0, stage);
         e3 = e4;
         p0 = p1;
         r0 = r1;
@@ -1090,7 +1135,12 @@ template <bool C, bool GR>
 __global__ __launch_bounds__(kBlock) void k_verify_deferred(LaunchArgs a) {
     __shared__ int32_t sb[kBlock];
     __shared__ uint32_t red[16];
-    __shared__ uint32_t s_tile;
+    __shared__ uint32_t s_tile, s_take;
+    constexpr uint32_t kWaves = (uint32_t)(kBlock / kWave);
+    __shared__ int2 s_pr[kWaves * kDeferStage];
+    __shared__ uint32_t s_req[kWaves * kDeferStage], s_n[kWaves];
+    const uint32_t wl = threadIdx.x / kWave;
+    DeferStage stage{s_pr + wl * kDeferStage, s_req + wl * kDeferStage, 0u};
     for (int q = kQueues - 1; q >= 0; --q) {
         if (q < a.defer_from && q != kSpillQ) break;
         if (lanes_of_queue(a, q) != kBlock) continue;
@@ -1098,25 +1148,31 @@ __global__ __launch_bounds__(kBlock) void k_verify_deferred(LaunchArgs a) {
         const uint32_t* queue = a.queues + (size_t)q * a.qcap;
         for (;;) {
             if (threadIdx.x == 0) {
-                // a plain read first: no atomic traffic once the queue is drained
-                s_tile = load_agent(&a.ctr->head[q]) >= cnt ? cnt : atomicAdd(&a.ctr->head[q], 1u);
+                // a plain read first: no atomic traffic once the queue is
+                // drained.  Several pairs per atomic while many are left: at
+                // one, the atomics' rate (10 ns each) set the kernel's time
+                const uint32_t h = load_agent(&a.ctr->head[q]);
+                s_take = max(1u, (cnt - min(h, cnt)) / (4u * gridDim.x));
+                s_tile = h >= cnt ? cnt : atomicAdd(&a.ctr->head[q], s_take);
             }
             __syncthreads();
-            const uint32_t t = s_tile;
+            const uint32_t t0 = s_tile, t1 = min(cnt, t0 + s_take);
             __syncthreads();
-            if (t >= cnt) break;
-            const uint32_t gi = queue[t];
-            const int r = request_of_pair(gi, a);
-            const Request& R = a.req[r];
-            const int2 pr = queued_pair<GR>(a, gi, r);
-            const uint2 dr = set_desc(a, pr.x);
-            const uint2 ds = set_desc_s(a, pr.y);
-            // a spilled merge resumes from its state (as in drain_static)
-            const uint4 st = q == kSpillQ && a.spill_state != nullptr ? a.spill_state[gi]
-                                                                       : make_uint4(0u, 0u, 0u, 0u);
-            const bool pass = merge_block(a.tok + dr.x + st.x, dr.y - st.x, a.tok_s + ds.x + st.y, ds.y - st.y,
-                                          required_overlap<C>(dr.y, ds.y, R) - st.z, sb, red);
-            if (threadIdx.x == 0 && pass) append_one(pr, R, &a.ctr->out_count[r]);
+            if (t0 >= cnt) break;
+            for (uint32_t t = t0; t < t1; ++t) {
+                const uint32_t gi = queue[t];
+                const int r = request_of_pair(gi, a);
+                const Request& R = a.req[r];
+                const int2 pr = queued_pair<GR>(a, gi, r);
+                const uint2 dr = set_desc(a, pr.x);
+                const uint2 ds = set_desc_s(a, pr.y);
+                // a spilled merge resumes from its state (as in drain_static)
+                const uint4 st = q == kSpillQ && a.spill_state != nullptr ? a.spill_state[gi]
+                                                                           : make_uint4(0u, 0u, 0u, 0u);
+                const bool pass = merge_block(a.tok + dr.x + st.x, dr.y - st.x, a.tok_s + ds.x + st.y, ds.y - st.y,
+                                              required_overlap<C>(dr.y, ds.y, R) - st.z, sb, red);
+                if (wl == 0) stage_deferred(a, pass && threadIdx.x == 0, pr, r, stage);
+            }
         }
     }
     for (int q = kQueues - 1; q >= 0; --q) {
@@ -1124,18 +1180,38 @@ __global__ __launch_bounds__(kBlock) void k_verify_deferred(LaunchArgs a) {
         const uint32_t cnt = load_agent(&a.ctr->tail[q]);
         if (cnt == 0) continue;
         switch (lanes_of_queue(a, q)) {
-            case 1: drain_static<1, C, GR>(a, q, cnt); break;
-            case 4: drain_static<4, C, GR>(a, q, cnt); break;
-            case 8: drain_static<8, C, GR>(a, q, cnt); break;
-            case 16: drain_static<16, C, GR>(a, q, cnt); break;
-            case 32: drain_static<32, C, GR>(a, q, cnt); break;
-            case 64: drain_static<64, C, GR>(a, q, cnt); break;
+            case 1: drain_static<1, C, GR>(a, q, cnt, stage); break;
+            case 4: drain_static<4, C, GR>(a, q, cnt, stage); break;
+            case 8: drain_static<8, C, GR>(a, q, cnt, stage); break;
+            case 16: drain_static<16, C, GR>(a, q, cnt, stage); break;
+            case 32: drain_static<32, C, GR>(a, q, cnt, stage); break;
+            case 64: drain_static<64, C, GR>(a, q, cnt, stage); break;
             default: break;
         }
     }
+    // what the wavefronts have staged, one after the other into the first
+    // one's place, leaves with one atomic per request
+    if (lane_id() == 0) s_n[wl] = stage.n;
     memory_wait();
     __syncthreads();
-    if (threadIdx.x < (unsigned)kWave) finish_workgroup(a);
+    if (wl != 0) return;
+    for (uint32_t q = 1; q < kWaves; ++q) {
+        const uint32_t c = s_n[q];
+        if (c == 0u) continue;
+        if (stage.n + c > kDeferStage) {
+            flush_deferred_out(a, stage.pr, stage.req, stage.n);
+            stage.n = 0;
+        }
+        for (uint32_t x = (uint32_t)lane_id(); x < c; x += kWave) {
+            stage.pr[stage.n + x] = s_pr[q * kDeferStage + x];
+            stage.req[stage.n + x] = s_req[q * kDeferStage + x];
+        }
+        stage.n += c;
+        wave_sync();
+    }
+    if (stage.n > 0u) flush_deferred_out(a, stage.pr, stage.req, stage.n);
+    memory_wait();
+    finish_workgroup(a);
 }
 
 // ---------------------------------------------------------------------------
