@@ -370,8 +370,9 @@ int ssj_stream_stats(ssj_ctx* ctx, ssj_stream_stats_t* out, int reset);
  *     SSJ_CLASS_BOUNDS) is defer_from or higher are not finished by (1) but
  *     queued per class (with one thread per pair, those that the record
  *     tokens decide are not queued); a persistent kernel then drains each
- *     class with lanes[class] lanes per pair (256 = one workgroup per pair,
- *     handed out by work stealing).  defer_from = SSJ_N_CLASSES defers nothing and runs
+ *     class with lanes[class] lanes per pair, four tokens per lane and side
+ *     at a time (256 = a wavefront per pair, with tiles of 256 tokens from
+ *     the start).  defer_from = SSJ_N_CLASSES defers nothing and runs
  *     the in-order kernel alone.
  *  3. with one thread per pair and no hard lanes, spill_iters > 0 bounds the
  *     merge of each pair in (1) to that many steps over 4-token windows: a

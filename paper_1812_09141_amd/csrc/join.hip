@@ -690,6 +690,8 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
 // last workgroup to finish publishes the count (-1 where nothing was joined)
 // and zeroes the counters.
 __global__ __launch_bounds__(kDrainBlock) void k_join_drain(JoinArgs a) {
+    __shared__ uint32_t s_tile[kDrainBlock / kWave * kWideTile];
+    uint32_t* sb = s_tile + threadIdx.x / kWave * kWideTile;
     const uint32_t cnt = min(load_agent(&a.ctl->spilled), kSpillCap);
     const int g = lane_id();
     const uint32_t waves = gridDim.x * (uint32_t)(kDrainBlock / kWave);
@@ -700,9 +702,9 @@ __global__ __launch_bounds__(kDrainBlock) void k_join_drain(JoinArgs a) {
         const int32_t* A = a.tok + (a.at[st.x] - bi - 1u);
         const int32_t* B = a.tok + (a.at[st.y] - bj - 1u);
         const uint32_t alpha = required_overlap<false>(er.y, es.y, a.req);
-        bool pass = merge_group<kWave>(A, er.y, B, es.y, alpha, g, 0, st.z, st.w, a.spill_o[k]);
+        bool pass = merge_wide<kWave>(A, er.y, B, es.y, alpha, st.z, st.w, a.spill_o[k], g, 0, sb);
         // none of the tokens before may be common
-        if (pass && bi > 0u && bj > 0u) pass = !merge_group<kWave>(A, bi, B, bj, 1u, g, 0);
+        if (pass && bi > 0u && bj > 0u) pass = !merge_wide<kWave>(A, bi, B, bj, 1u, 0u, 0u, 0u, g, 0, sb);
         if (pass && g == 0) {
             const unsigned long long at = atomicAdd(&a.ctl->out_count, 1ull);
             if (at < a.req.cap) a.req.out[at] = make_int2((int)er.x, (int)es.x);

