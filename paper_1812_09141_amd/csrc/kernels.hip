@@ -15,7 +15,9 @@
 //
 // Mappings of pairs onto lanes (the paper's alternatives A/B/C of Sec. 3.3.2
 // give a probe set to a thread or a block; here the unit is one pair):
-//   * one thread per pair: the merge of the first six tokens of both sets,
+//   * one thread per pair: an upper bound of the overlap from two bitmaps of
+//     token hashes (signatures), which rejects nearly all pairs that are not
+//     similar; for the others the merge of the first six tokens of both sets,
 //     kept in their 32-byte set records, in straight-line code, then, for a
 //     pair still undecided, a merge over 16-byte windows of the token arrays
 //     (every set starts on a 16-byte boundary) with the next window in
@@ -46,9 +48,9 @@
 // Passing pairs are compacted in LDS (a ballot of the pass flags and each
 // lane's rank among the passing lanes) and moved to the request's output
 // with one global atomic per flush.  The in-order kernel keeps all of this
-// per wavefront, so it has no workgroup barrier, and each wavefront lowers
-// its priority as it works through its share, so that the youngest
-// wavefronts of a SIMD do not finish long after the rest.
+// per wavefront, so it has no workgroup barrier; with a group per pair each
+// wavefront lowers its priority as it works through its share, so that the
+// youngest wavefronts of a SIMD do not finish long after the rest.
 #include <algorithm>
 
 #include "merge_device.h"
@@ -417,6 +419,46 @@ __device__ __forceinline__ void issue_records(const LaunchArgs& a, int2 pr, Lane
     rec.rb1 = a.heads_s[2 * is + 1];
 }
 
+// Signatures of a lane's pair.
+template <int U>
+struct Signatures {
+    uint4 r[U], s[U];
+};
+
+// (ids past the last set read the last one's, with last 0 everything reads
+// the first one's)
+template <int U>
+__device__ __forceinline__ void issue_signatures(const uint4* sig, const uint4* sig_s, uint32_t last_r, uint32_t last_s,
+                                                 int2 pr, Signatures<U>& q) {
+    const size_t ir = min((uint32_t)pr.x, last_r), is = min((uint32_t)pr.y, last_s);
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        q.r[u] = sig[ir * U + u];
+        q.s[u] = sig_s[is * U + u];
+    }
+}
+
+// The most tokens that two sets can share by their signatures.  A token of
+// both sets has its bit in both bitmaps, so a set's bits that the other one
+// lacks stand for as many tokens of its own: |r| minus those of r, and |s|
+// minus those of s, bound the overlap.
+template <int U>
+__device__ __forceinline__ uint32_t most_shared(const Signatures<U>& q) {
+    uint32_t c = 0, nr = 0, ns = 0;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+        if (u > 0) {
+            c += (uint32_t)__popc(q.r[u].x & q.s[u].x);
+            nr += (uint32_t)__popc(q.r[u].x);
+            ns += (uint32_t)__popc(q.s[u].x);
+        }
+        c += (uint32_t)(__popc(q.r[u].y & q.s[u].y) + __popc(q.r[u].z & q.s[u].z) + __popc(q.r[u].w & q.s[u].w));
+        nr += (uint32_t)(__popc(q.r[u].y) + __popc(q.r[u].z) + __popc(q.r[u].w));
+        ns += (uint32_t)(__popc(q.s[u].y) + __popc(q.s[u].z) + __popc(q.s[u].w));
+    }
+    return c + min(q.r[0].x - nr, q.s[0].x - ns);
+}
+
 // Merge state after the first tile of one side is consumed, with the first
 // H record tokens of each side as the tiles (the tile merge of merge_group,
 // done by one lane in straight-line code): with m the smaller of the two
@@ -427,13 +469,8 @@ __device__ __forceinline__ void issue_records(const LaunchArgs& a, int2 pr, Lane
 // are not empty, so m >= 0).  A larger H gives a state at least as far along
 // the same merge.
 template <int H>
-__device__ __forceinline__ void head_tiles(uint4 a0, uint4 a1, uint4 b0, uint4 b1, uint32_t* i,
+__device__ __forceinline__ void head_tiles(const int32_t (&A)[H], const int32_t (&B)[H], uint32_t* i,
                                            uint32_t* j, uint32_t* o) {
-    static_assert(H >= 1 && H <= kHeadTokens, "head tiles come from the record tokens");
-    const int32_t A[kHeadTokens] = {(int32_t)a0.z, (int32_t)a0.w, (int32_t)a1.x,
-                                    (int32_t)a1.y, (int32_t)a1.z, (int32_t)a1.w};
-    const int32_t B[kHeadTokens] = {(int32_t)b0.z, (int32_t)b0.w, (int32_t)b1.x,
-                                    (int32_t)b1.y, (int32_t)b1.z, (int32_t)b1.w};
     int32_t am = A[0], bm = B[0];
 #pragma unroll
     for (int x = 1; x < H; ++x) {
@@ -549,25 +586,20 @@ __device__ __forceinline__ bool merge_ring(const int32_t* __restrict__ tok_a, ui
 }
 
 // Thread-per-pair verification of the lane's pair (chunk index kb + lane)
-// from its records: first the head tiles (head_tiles), which decide most
-// pairs (with try4, four tokens per side first: see the caller); a pair
-// still undecided continues from that merge state.  F == 0: it
+// from its records: first the head tiles (head_tiles); a pair they leave
+// undecided continues from that merge state.  F == 0: it
 // continues in the same lane over 16-byte windows of the token array
-// (merge_windows, or with S merge_ring, its loads two steps ahead through
-// the wavefront's window ring).  F > 0: it is appended, with
+// (merge_windows).  F > 0: it is appended, with
 // its merge state, to the wavefront's list of hard pairs (hcnt entries), which
 // groups of F lanes finish (finish_hard), so that no lane walks the token
 // array alone while the rest of its wavefront waits.
-template <int F, bool C, bool S, bool GR>
+template <int F, bool C, int M, bool GR>
 __device__ __forceinline__ void chunk_thread_pairs(const LaunchArgs& a, const Request& R, int r,
-                                                   uint32_t kb, int2 pr, const LaneRecords& rec,
+                                                   uint32_t k, bool valid, int2 pr, const LaneRecords& rec,
                                                    bool deferring, uint32_t* w_defer,
                                                    unsigned long long& dc, int2* w_out, uint32_t& ocnt,
-                                                   int2* w_hpr, uint32_t* w_hst, uint32_t& hcnt, uint4* ring,
-                                                   bool try4, bool& need6) {
+                                                   int2* w_hpr, uint32_t* w_hst, uint32_t& hcnt, uint4* ring) {
     const int lane = lane_id();
-    const uint32_t k = kb + (uint32_t)lane;
-    const bool valid = k < R.n;
     const bool ok = valid && ids_ok(pr, a);
     const uint32_t na = rec.ra0.y, nb = rec.rb0.y;
     const uint32_t L = na + nb;
@@ -579,27 +611,21 @@ __device__ __forceinline__ void chunk_thread_pairs(const LaunchArgs& a, const Re
         pass = ok && o >= alpha;
         act = ok && !pass && o + min(na - i, nb - j) >= alpha;
     };
-    // with try4 (wave-uniform) the head step first takes four record tokens
-    // per side, and the six only when that left some lane of the chunk
-    // undecided (need6); the six-token state supersedes the four-token one
-    bool full = true;
-    if (try4) {
-        head_tiles<4>(rec.ra0, rec.ra1, rec.rb0, rec.rb1, &i, &j, &o);
-        decide();
-        full = ballot(act) != 0ull;
-        need6 = full;
-    }
-    if (full) {
-        head_tiles<kHeadTokens>(rec.ra0, rec.ra1, rec.rb0, rec.rb1, &i, &j, &o);
-        decide();
-    }
+    const int32_t A[kHeadTokens] = {(int32_t)rec.ra0.z, (int32_t)rec.ra0.w, (int32_t)rec.ra1.x,
+                                    (int32_t)rec.ra1.y, (int32_t)rec.ra1.z, (int32_t)rec.ra1.w};
+    const int32_t B[kHeadTokens] = {(int32_t)rec.rb0.z, (int32_t)rec.rb0.w, (int32_t)rec.rb1.x,
+                                    (int32_t)rec.rb1.y, (int32_t)rec.rb1.z, (int32_t)rec.rb1.w};
+    head_tiles(A, B, &i, &j, &o);
+    decide();
     // pairs of the deferred classes that the record tokens leave undecided
     const bool defer = act && deferring && cls >= a.defer_from;
     act = act && !defer;
     bool spill = false;
-    if constexpr (F == 0) {
+    if constexpr (M == kWide) {
+        spill = act;
+    } else if constexpr (F == 0) {
         const uint32_t budget = deferring ? a.spill_iters : 0xffffffffu;
-        if constexpr (S) {
+        if constexpr (M == kRing) {
             if (act)
                 pass = merge_ring(a.tok, rec.ra0.x, na, a.tok_s, rec.rb0.x, nb, alpha, i, j, o, budget, &spill,
                                   ring, lane);
@@ -659,6 +685,227 @@ __device__ __forceinline__ void finish_hard(const LaunchArgs& a, const Request& 
     wave_sync();
 }
 
+// The walk of a wavefront over its chunks, a lane per pair.  A chunk's pairs
+// meet their signatures first, which reject nearly every pair that is not
+// similar (of 3.1M candidates of sets of about 12 tokens at 3/5 they leave
+// 0.05%, of 620,000 of long sets at 7/10 the wide ones 0.8%, the narrow ones
+// 60%).  What they leave is gathered in LDS and verified from the set records
+// 64 pairs at a time (chunk_thread_pairs), where no lane idles.  The records
+// alone decided so few pairs of a wavefront that every one of them walked
+// tokens: two collections 67 -> 40 us, four thresholds 44 -> 34, grouped
+// 58 -> 42, 620,000 pairs of long sets 85 -> 36 (their new context's plan
+// 198 -> 36), 168M candidates of heavy-tailed sizes 920 -> 768.
+//
+// What bounds it now is the gather of the signatures.  A 64-lane gather costs
+// 2.4 cycles of a compute unit per distinct 128-byte line that the L2 holds and
+// 9.4 per line that it does not (measured; a second load from the same line
+// 0.7), and the chunks of heavy-tailed sizes meet 31 lines each, of short sets
+// 63: hence 16 bytes per set where they do, sets of more than 40 tokens on
+// average excepted, whose bitmap of 96 bits would be nearly full.  For the same
+// reason chunks and record loads are not split further, and four wavefronts per
+// SIMD do as well as six.
+//
+// Loads never wait for the newest one: candidates are requested three chunks
+// ahead and signatures one, into registers that two copies of the step take in
+// turn (rotating them by moves waits for the loads), and with the constants of
+// the request in scalar registers a chunk takes 92 vector and 71 scalar
+// instructions instead of 117 and 115.
+template <int F, bool D, bool C, int M, bool GR>
+__device__ __forceinline__ void walk(const LaunchArgs& a, uint32_t first, uint32_t nw, uint32_t n_chunks,
+                                     int2* w_out, uint32_t* w_defer, unsigned long long& dc, int2* w_hpr,
+                                     uint32_t* w_hst, int2* w_list, uint32_t* w_list_k, uint32_t* w_marks,
+                                     uint4* w_ring, uint32_t* s_only, uint32_t& ocnt, int& r_last) {
+    constexpr int U = M == kWide ? kWideUnits : kNarrowUnits;
+    // Signatures while they leave at most this many pairs of a chunk on average;
+    // otherwise they are tried again on every sixteenth chunk.  (The 18% of the
+    // chunks of heavy-tailed sizes that are left many pairs are left 29 of 64:
+    // with 24 here the walk took 866 us, with 40 it took 775.)
+    constexpr uint32_t kMostLeft = 40;
+    if (first >= n_chunks) return;
+    const int lane = lane_id();
+    const bool deferring = D && (a.defer_from < kClasses || spilling(a));
+    const bool have = a.sig != nullptr && a.sig_s != nullptr;
+    const uint4* sig = have ? a.sig : a.heads;
+    const uint4* sig_s = have ? a.sig_s : a.heads_s;
+    const uint32_t last_r = a.n_sets != 0u ? a.n_sets - 1u : 0u, last_s = a.n_sets_s != 0u ? a.n_sets_s - 1u : 0u;
+    const uint32_t share = (n_chunks - 1u - first) / nw + 1u;
+
+    // the request of the chunks whose candidates are requested, and its chunks
+    int ri = 0;
+    uint32_t bi = 0, ei = a.tile_off[1], ni = a.req[0].n;
+    const int2* ci = a.req[0].cand;
+    uint32_t ord = 0;  // ordinal of the next chunk to request
+    uint32_t vbase = 0, vg = load_chunk_groups<GR>(a, first, nw, n_chunks, 0u, lane);
+    // requests the candidates of the next chunk (past the last one: of the last)
+    auto issue = [&](CandLoad& c, int& r, uint32_t& kb) {
+        const uint32_t q = min(ord++, share - 1u);
+        const uint32_t T = first + q * nw;
+        while (T >= ei) {
+            ++ri;
+            bi = ei;
+            ei = a.tile_off[ri + 1];
+            ni = a.req[ri].n;
+            ci = a.req[ri].cand;
+        }
+        r = ri;
+        kb = (T - bi) * (uint32_t)kWave;
+        if constexpr (GR) {
+            if (q - vbase >= (uint32_t)kWave) {
+                vbase = q;
+                vg = load_chunk_groups<GR>(a, first, nw, n_chunks, vbase, lane);
+            }
+            c = issue_cand<GR>(a, a.req[ri], kb, lane, (uint32_t)__builtin_amdgcn_readlane((int)vg, (int)(q - vbase)));
+        } else {
+            c.p = load_pair(ci, min(kb + (uint32_t)lane, ni - 1u));
+        }
+    };
+
+    // the request of the chunk being verified
+    int rc = 0;
+    uint32_t n = 0, num = 0, add = 0, den = 0;
+    bool cosine = false;
+    uint32_t full = 0;                  // staged pairs that have to leave before more come
+    uint32_t left = 0;                  // pairs in the list
+    uint32_t left8 = 0;                 // eight times the pairs that recent chunks left
+    unsigned long long bad = 0ull;      // lanes that met an id out of range
+    auto open_request = [&](int r) {
+        rc = r;
+        const Request& R = a.req[rc];
+        n = R.n;
+        num = R.small_num;
+        add = R.small_add;
+        den = R.small_den;
+        if (C && R.rule == kCosine && R.cosine_ratio != 0.0f) {
+            cosine = true;
+            num = (uint32_t)R.num;
+            den = (uint32_t)R.den;
+        } else {
+            cosine = false;
+        }
+        full = R.cap == 0 ? 0xffffffffu : wave_stage(M) - kWave;
+    };
+    // verifies the last m (at most kWave) pairs of the list
+    auto finish_list = [&](uint32_t m) {
+        wave_sync();
+        const bool valid = (uint32_t)lane < m;
+        const uint32_t at = left - m + min((uint32_t)lane, m - 1u);
+        const int2 pr = w_list[at];
+        const uint32_t k = D ? w_list_k[at] : 0u;
+        left -= m;
+        const Request& R = a.req[rc];
+        LaneRecords rec;
+        issue_records(a, pr, rec);
+        uint32_t hcnt = 0;
+        chunk_thread_pairs<F, C, M, GR>(a, R, rc, k, valid, pr, rec, deferring, w_defer, dc, w_out, ocnt, w_hpr, w_hst,
+                                        hcnt, w_ring);
+        if constexpr (F > 0)
+            if (hcnt != 0u) finish_hard<F, C>(a, R, hcnt, w_hpr, w_hst, w_out, ocnt);
+        wave_sync();
+    };
+
+    // candidates are requested three chunks ahead, signatures one
+    int2 p0;
+    int r0, rx, ry;
+    uint32_t kb0, kbx, kby;
+    CandLoad cx, cy;
+    Signatures<U> qa, qb;
+    bool with0 = have;
+    {
+        CandLoad c0;
+        issue(c0, r0, kb0);
+        issue(cx, rx, kbx);
+        p0 = resolve_cand<GR>(a, a.req[r0], kb0, lane, c0, w_marks);
+        issue_signatures<U>(sig, sig_s, with0 ? last_r : 0u, with0 ? last_s : 0u, p0, qa);
+        issue(cy, ry, kby);
+    }
+    uint32_t done = 0;
+    // one chunk: its signatures are in cur, the next chunk's go to nxt; c
+    // holds the next chunk's candidates and takes those of the third one
+    auto step = [&](Signatures<U>& cur, Signatures<U>& nxt, CandLoad& c, int& rn, uint32_t& kbn) {
+        ++done;
+        const int2 p1 = resolve_cand<GR>(a, a.req[rn], kbn, lane, c, w_marks);
+        const int r1 = rn;
+        const uint32_t kb1 = kbn;
+        const bool with1 = have && (left8 <= 8u * kMostLeft || (done & 15u) == 0u);
+        issue_signatures<U>(sig, sig_s, with1 ? last_r : 0u, with1 ? last_s : 0u, p1, nxt);
+        issue(c, rn, kbn);
+        const bool valid = kb0 + (uint32_t)lane < n;
+        const bool ok = valid && (uint32_t)p0.x < a.n_sets && (uint32_t)p0.y < a.n_sets_s;
+        bad |= ballot(valid && !ok);
+        bool act = ok;
+        if (with0) {
+            const uint32_t na = cur.r[0].x, nb = cur.s[0].x, most = most_shared<U>(cur);
+            if (C && cosine) {
+                // (sizes below 2^16, terms below 2^15)
+                const uint32_t x = most * den, y = num * num, z = na * nb;
+                act = ok && (unsigned long long)x * x >= (unsigned long long)y * z;
+            } else if (den != 0u) {
+                act = ok && __umul24(most, den) >= __umul24(num, na + nb) + add;
+            } else {
+                act = ok && most >= (ok ? required_overlap<C>(na, nb, a.req[rc]) : 0u);
+            }
+        }
+        const unsigned long long m = ballot(act);
+        const uint32_t more = (uint32_t)__popcll(m);
+        if (with0) left8 = left8 - (left8 >> 3) + more;
+        if (m != 0ull) {
+            if (act) {
+                const uint32_t at = left + mbcnt(m);
+                w_list[at] = p0;
+                if constexpr (D) w_list_k[at] = kb0 + (uint32_t)lane;
+            }
+            left += more;
+        }
+        p0 = p1;
+        r0 = r1;
+        kb0 = kb1;
+        with0 = with1;
+    };
+    // work between chunks: the list is full, another request begins
+    auto stop = [&]() {
+        return done == share || r0 != rc || left >= (uint32_t)kWave;
+    };
+    auto between = [&]() {
+        const bool close = done == share || r0 != rc;
+        while (left >= (close ? 1u : (uint32_t)kWave)) {
+            finish_list(min(left, (uint32_t)kWave));
+            // (at most kWave staged pairs and entries per queue come at a time)
+            if (ocnt > full) {
+                wave_flush_out(a, rc, ocnt, w_out, s_only);
+                ocnt = 0;
+            }
+            if (deferring) {
+                for (int q = a.defer_from; q < queue_end(a); ++q) {
+                    const uint32_t c = dcount(dc, q);
+                    if (c > a.defer_cap - kWave) {
+                        wave_flush_deferred(a, q, c, w_defer);
+                        dc &= ~(0xffull << (8 * q));
+                    }
+                }
+            }
+        }
+        if (close && bad != 0ull) {
+            if (lane == 0) atomicOr(&a.ctr->err[rc], 1u);
+            bad = 0ull;
+        }
+        if (close && done != share) {
+            if (ocnt != 0u) wave_flush_out(a, rc, ocnt, w_out, s_only);
+            ocnt = 0;
+            open_request(r0);
+        }
+    };
+    open_request(r0);
+    for (;;) {
+        step(qa, qb, cx, rx, kbx);
+        if (stop()) between();
+        if (done == share) break;
+        step(qb, qa, cy, ry, kby);
+        if (stop()) between();
+        if (done == share) break;
+    }
+    r_last = rc;
+}
+
 // ---------------------------------------------------------------------------
 // In-order kernel.  Every wavefront takes chunks of kWave consecutive pairs
 // of one request, grid-stride over all wavefronts of the grid.  G == 1: a
@@ -667,14 +914,14 @@ __device__ __forceinline__ void finish_hard(const LaunchArgs& a, const Request& 
 // fewer registers).  S (G == 1, F == 0): merges through the window ring
 // (merge_ring).  GR: a grouped launch (every request's candidates read in
 // place from its groups and s ids).
-template <int G, int F, bool D, bool C, bool S, bool GR>
+template <int G, int F, bool D, bool C, int M, bool GR>
 __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     constexpr int GPW = kWave / G;
     constexpr uint32_t kWaves = (uint32_t)(kBlock / kWave);
     // staged output pairs per wavefront: every flush is one atomic on the
     // request's counter, and same-address atomics from all wavefronts are
     // serialised, so flushes carry at least kWStage - kWave pairs
-    constexpr uint32_t kWStage = wave_stage(S);
+    constexpr uint32_t kWStage = wave_stage(M);
     // the wavefront index is uniform in the wavefront: taken through a scalar
     // register for the chunk walk (which then stays scalar); the LDS
     // addresses use the per-lane copy (vector registers are the cheaper ones)
@@ -697,12 +944,15 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     __shared__ uint32_t s_hst[F > 0 ? kWaves * kWave : 1];
     int2* w_hpr = s_hpr + (F > 0 ? wl * kWave : 0u);
     uint32_t* w_hst = s_hst + (F > 0 ? wl * kWave : 0u);
+    // pairs that the signatures leave, and their indices in the request
+    __shared__ int2 s_list[G == 1 ? kWaves * 2 * kWave : 1];
+    __shared__ uint32_t s_list_k[G == 1 && D ? kWaves * 2 * kWave : 1];
     // group search scratch of grouped launches (resolve_cand)
     __shared__ uint32_t s_marks[GR ? kWaves * kWave : 1];
     uint32_t* w_marks = s_marks + (GR ? wl * kWave : 0u);
     // the window rings of merge_ring
-    __shared__ uint4 s_ring[S ? kWaves * kRingSlots : 1];
-    uint4* w_ring = s_ring + (S ? wl * kRingSlots : 0u);
+    __shared__ uint4 s_ring[M == kRing ? kWaves * kRingSlots : 1];
+    uint4* w_ring = s_ring + (M == kRing ? wl * kRingSlots : 0u);
     // pairs of the requests without an output buffer, and the wavefronts that
     // have finished
     __shared__ uint32_t s_only[kMaxReq], s_finished, s_staged[kWaves], s_staged_req[kWaves];
@@ -710,93 +960,30 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     if (threadIdx.x < (unsigned)kMaxReq) s_only[threadIdx.x] = 0u;
     if (threadIdx.x == 0) s_finished = 0u;
     __syncthreads();
-    uint32_t ocnt = 0, hcnt = 0;
+    uint32_t ocnt = 0;
     unsigned long long dc = 0ull;  // deferred queue fill counts (dcount)
     const uint32_t n_chunks = a.tile_off[a.n_req];
     const uint32_t nw = gridDim.x * kWaves;
     const uint32_t first = blockIdx.x * kWaves + (uint32_t)w;
-    // G == 1: a two-stage pipeline.  While chunk T is verified, the records of
-    // chunk T + nw and the pairs of chunk T + 2 nw are in flight (memory
-    // operations complete in issue order, so the records of T, issued one
-    // iteration earlier, are waited for without draining the newer loads).
-    int2 p0 = make_int2(0, 0);
-    CandLoad c1{};
-    LaneRecords rec0{}, rec1{};
-    int r_cur = 0, r1 = 0;
-    uint32_t kb_cur = 0, kb1 = 0;
-    // grouped: first groups of this wavefront's chunks with ordinals
-    // vbase .. vbase + 63, one per lane
-    uint32_t vbase = 0, vg = 0;
-    auto group_of_ord = [&](uint32_t q) -> uint32_t {
-        if constexpr (!GR) return 0u;
-        if (q - vbase >= (uint32_t)kWave) {
-            vbase = q;
-            vg = load_chunk_groups<GR>(a, first, nw, n_chunks, vbase, lane);
-        }
-        return (uint32_t)__builtin_amdgcn_readlane((int)vg, (int)(q - vbase));
-    };
-    if (first < n_chunks) {
-        chunk_origin(a, first, &r_cur, &kb_cur);
-        if constexpr (G == 1) {
-            // loads beyond the last chunk are clamped to it (results unused),
-            // so every iteration issues the same loads in the same order
-            vg = load_chunk_groups<GR>(a, first, nw, n_chunks, 0u, lane);
-            p0 = resolve_cand<GR>(a, a.req[r_cur], kb_cur, lane,
-                                  issue_cand<GR>(a, a.req[r_cur], kb_cur, lane, group_of_ord(0u)), w_marks);
-            issue_records(a, p0, rec0);
-            chunk_origin(a, min(first + nw, n_chunks - 1), &r1, &kb1);
-            c1 = issue_cand<GR>(a, a.req[r1], kb1, lane, group_of_ord(1u));
-        }
-    }
-    const uint32_t share = first < n_chunks ? (n_chunks - 1u - first) / nw + 1u : 1u;
-    const uint32_t quarter[3] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)((share + 3u) / 4u)),
-                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)((2u * share + 3u) / 4u)),
-                                 (uint32_t)__builtin_amdgcn_readfirstlane((int)((3u * share + 3u) / 4u))};
-    uint32_t done = 0, level = 3;
-    // thread-per-pair head step: four tokens per side first while that
-    // decides whole chunks often enough.  h4est tracks 256 times the share of
-    // recent tries that still needed the six-token step; the four-token step
-    // costs about 60% of the six-token one, so trying it first pays while
-    // that share stays below about 3/8, and it is tried again on every
-    // eighth chunk
-    uint32_t h4est = 96u;
-    __builtin_amdgcn_s_setprio(3);
-    for (uint32_t T = first; T < n_chunks; T += nw) {
-        progress_priority(done++, quarter, level);
-        const int r = r_cur;
-        const uint32_t kb = kb_cur;
-        const uint32_t Tn = T + nw;
-        const Request& R = a.req[r];
-        if constexpr (G == 1) {
-            const int2 p1 = resolve_cand<GR>(a, a.req[r1], kb1, lane, c1, w_marks);
-            issue_records(a, p1, rec1);
-            int r2 = 0;
-            uint32_t kb2 = 0;
-            chunk_origin(a, min(Tn + nw, n_chunks - 1), &r2, &kb2);
-            const CandLoad c2 = issue_cand<GR>(a, a.req[r2], kb2, lane, group_of_ord(done + 1u));
-            // (only in the plain thread-per-pair instances: with the deferral
-            // code it spills scalar registers, with the window ring it costs
-            // a wavefront per SIMD)
-            const bool try4 = !D && !S && (h4est < 96u || ((done - 1u) & 7u) == 0u);
-            bool need6 = false;
-            chunk_thread_pairs<F, C, S, GR>(a, R, r, kb, p0, rec0, deferring, w_defer, dc, w_out, ocnt,
-                                            w_hpr, w_hst, hcnt, w_ring, try4, need6);
-            if (try4) h4est = h4est - (h4est >> 3) + (need6 ? 32u : 0u);
-            if constexpr (F > 0) {
-                if (hcnt > 0) {
-                    finish_hard<F, C>(a, R, hcnt, w_hpr, w_hst, w_out, ocnt);
-                    hcnt = 0;
-                }
-            }
-            // rotate the pipeline
-            p0 = p1;
-            c1 = c2;
-            rec0 = rec1;
-            r_cur = r1;
-            kb_cur = kb1;
-            r1 = r2;
-            kb1 = kb2;
-        } else {
+    if constexpr (G == 1) {
+        walk<F, D, C, M, GR>(a, first, nw, n_chunks, w_out, w_defer, dc, w_hpr, w_hst, s_list + wl * 2 * kWave,
+                             s_list_k + (D ? wl * 2 * kWave : 0u), w_marks, w_ring, s_only, ocnt, r_last);
+    } else {
+        int r_cur = 0;
+        uint32_t kb_cur = 0;
+        if (first < n_chunks) chunk_origin(a, first, &r_cur, &kb_cur);
+        const uint32_t share = first < n_chunks ? (n_chunks - 1u - first) / nw + 1u : 1u;
+        const uint32_t quarter[3] = {(uint32_t)__builtin_amdgcn_readfirstlane((int)((share + 3u) / 4u)),
+                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)((2u * share + 3u) / 4u)),
+                                     (uint32_t)__builtin_amdgcn_readfirstlane((int)((3u * share + 3u) / 4u))};
+        uint32_t done = 0, level = 3;
+        __builtin_amdgcn_s_setprio(3);
+        for (uint32_t T = first; T < n_chunks; T += nw) {
+            progress_priority(done++, quarter, level);
+            const int r = r_cur;
+            const uint32_t kb = kb_cur;
+            const uint32_t Tn = T + nw;
+            const Request& R = a.req[r];
             if (Tn < n_chunks) chunk_origin(a, Tn, &r_cur, &kb_cur);
             // sub-rounds of 64/G pairs, software-pipelined: while sub-round s
             // is merged, the first tiles of s + 1, the set descriptors of s + 2
@@ -864,23 +1051,23 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
                 wb0 = wb1;
             }
             if (ballot(bad) != 0ull && lane == 0) atomicOr(&a.ctr->err[r], 1u);
-        }
-        // at most kWave pairs are staged per chunk: flush when fewer than that
-        // fit, or when the next chunk belongs to another request (what is
-        // staged after the last chunk goes out with the workgroup's)
-        r_last = r;
-        const bool other_next = Tn < n_chunks && r_cur != r;
-        if (ocnt > 0 && ((R.cap != 0 && ocnt > kWStage - kWave) || other_next)) {
-            wave_flush_out(a, r, ocnt, w_out, s_only);
-            ocnt = 0;
-        }
-        if (deferring) {
-            // the same bound holds for each queue
-            for (int q = a.defer_from; q < queue_end(a); ++q) {
-                const uint32_t c = dcount(dc, q);
-                if (c > a.defer_cap - kWave) {
-                    wave_flush_deferred(a, q, c, w_defer);
-                    dc &= ~(0xffull << (8 * q));
+            // at most kWave pairs are staged per chunk: flush when fewer than that
+            // fit, or when the next chunk belongs to another request (what is
+            // staged after the last chunk goes out with the workgroup's)
+            r_last = r;
+            const bool other_next = Tn < n_chunks && r_cur != r;
+            if (ocnt > 0 && ((R.cap != 0 && ocnt > kWStage - kWave) || other_next)) {
+                wave_flush_out(a, r, ocnt, w_out, s_only);
+                ocnt = 0;
+            }
+            if (deferring) {
+                // the same bound holds for each queue
+                for (int q = a.defer_from; q < queue_end(a); ++q) {
+                    const uint32_t c = dcount(dc, q);
+                    if (c > a.defer_cap - kWave) {
+                        wave_flush_deferred(a, q, c, w_defer);
+                        dc &= ~(0xffull << (8 * q));
+                    }
                 }
             }
         }
@@ -1150,7 +1337,9 @@ __global__ __launch_bounds__(kBlock, 4) void k_verify_deferred(LaunchArgs a) {
         if (q < a.defer_from && q != kSpillQ) break;
         const uint32_t cnt = load_agent(&a.ctr->tail[q]);
         if (cnt == 0) continue;
-        switch (lanes_of_queue(a, q)) {
+        // (of wide signatures: a wavefront each for few pairs, 16 lanes for many)
+        const int lanes = a.mode != kWide ? lanes_of_queue(a, q) : cnt < gridDim.x * kWaves * 4u ? kBlock : 16;
+        switch (lanes) {
             case 1: drain_static<1, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
             case 4: drain_static<4, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
             case 8: drain_static<8, C, GR>(a, s_reqs, q, cnt, stage, sb); break;
@@ -1245,6 +1434,56 @@ __global__ void k_build_heads(const int64_t* __restrict__ off, const uint32_t* _
     }
 }
 
+// Signatures of the sets, narrow and where WIDE wide ones, from the set records:
+// 16 lanes per set walk its 16-byte windows and collect its bits in LDS.  (One
+// kernel for these and the set records, 16 lanes per set, took 100 us more for
+// an upload of 50,000 short sets, this one takes 25.)
+template <bool WIDE>
+__global__ __launch_bounds__(kBlock) void k_build_signatures(const uint4* __restrict__ heads,
+                                                             const int32_t* __restrict__ tok,
+                                                             uint4* __restrict__ narrow, uint4* __restrict__ wide,
+                                                             int64_t n) {
+    constexpr int kLanes = 16, kSets = kBlock / kLanes;
+    constexpr uint32_t kNarrowBits = signature_bits(kNarrowUnits), kWideBits = signature_bits(kWideUnits);
+    static_assert(4 * kWideUnits <= kLanes, "a lane per word of a signature");
+    __shared__ uint32_t s_narrow[kSets][4 * kNarrowUnits], s_wide[WIDE ? kSets : 1][4 * kWideUnits];
+    const int w = (int)threadIdx.x / kLanes, g = (int)threadIdx.x % kLanes;
+    const uint4* t4 = reinterpret_cast<const uint4*>(tok);
+    for (int64_t b = (int64_t)blockIdx.x * kSets; b < n; b += (int64_t)gridDim.x * kSets) {
+        const int64_t i = b + w;
+        const uint4 h = i < n ? heads[2 * i] : make_uint4(0u, 0u, 0u, 0u);
+        const uint32_t len = h.y;
+        if (g < 4 * kNarrowUnits) s_narrow[w][g] = g == 0 ? len : 0u;
+        if constexpr (WIDE) s_wide[w][g] = g == 0 ? len : 0u;
+        wave_sync();
+        for (uint32_t x = (uint32_t)g; 4u * x < len; x += kLanes) {
+            const uint4 v = t4[(h.x >> 2) + x];
+            const uint32_t t[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+            for (uint32_t k = 0; k < 4u; ++k) {
+                if (4u * x + k >= len) break;
+                // (multiplicative hashing: Knuth, The Art of Computer Programming, vol. 3, 6.4)
+                const uint32_t hash = t[k] * 2654435761u, a = __umulhi(hash, kNarrowBits);
+                atomicOr(&s_narrow[w][1u + a / 32u], 1u << (a % 32u));
+                if constexpr (WIDE) {
+                    const uint32_t c = __umulhi(hash, kWideBits);
+                    atomicOr(&s_wide[w][1u + c / 32u], 1u << (c % 32u));
+                }
+            }
+        }
+        wave_sync();
+        if (i < n && g < kNarrowUnits)
+            narrow[i * kNarrowUnits + g] = make_uint4(s_narrow[w][4 * g], s_narrow[w][4 * g + 1], s_narrow[w][4 * g + 2],
+                                                      s_narrow[w][4 * g + 3]);
+        if constexpr (WIDE) {
+            if (i < n && g < kWideUnits)
+                wide[i * kWideUnits + g] = make_uint4(s_wide[w][4 * g], s_wide[w][4 * g + 1], s_wide[w][4 * g + 2],
+                                                      s_wide[w][4 * g + 3]);
+        }
+        wave_sync();
+    }
+}
+
 }  // namespace
 
 bool lanes_supported(int lanes) {
@@ -1254,50 +1493,52 @@ bool lanes_supported(int lanes) {
     }
 }
 
-bool inline_supported(int lanes, int hard_lanes, bool staged) {
-    return kernel_verify_tiles(lanes, hard_lanes, staged, false, false, false) != nullptr;
+bool inline_supported(int lanes, int hard_lanes) {
+    return kernel_verify_tiles(lanes, hard_lanes, kNarrow, false, false, false) != nullptr;
 }
 
 template <bool D, bool C, bool GR>
-const void* verify_tiles_instance(int lanes, int hard_lanes, bool staged) {
+const void* verify_tiles_instance(int lanes, int hard_lanes, int mode) {
+    if (mode != kNarrow) {
+        if (lanes != 1 || hard_lanes != 0) return nullptr;
+        // (wide signatures always queue pairs; no grouped launch has the ring)
+        if constexpr (D)
+            if (mode == kWide) return (const void*)&k_verify_tiles<1, 0, D, C, kWide, GR>;
+        if constexpr (!GR)
+            if (mode == kRing) return (const void*)&k_verify_tiles<1, 0, D, C, kRing, GR>;
+        return nullptr;
+    }
     if (lanes == 1) {
-        if constexpr (!GR) {
-            if (staged) return hard_lanes == 0 ? (const void*)&k_verify_tiles<1, 0, D, C, true, GR> : nullptr;
-        }
         switch (hard_lanes) {
-            case 0: return (const void*)&k_verify_tiles<1, 0, D, C, false, GR>;
-            case 8: return (const void*)&k_verify_tiles<1, 8, D, C, false, GR>;
-            case 16: return (const void*)&k_verify_tiles<1, 16, D, C, false, GR>;
+            case 0: return (const void*)&k_verify_tiles<1, 0, D, C, kNarrow, GR>;
+            case 8: return (const void*)&k_verify_tiles<1, 8, D, C, kNarrow, GR>;
+            case 16: return (const void*)&k_verify_tiles<1, 16, D, C, kNarrow, GR>;
             default: return nullptr;
         }
     }
-    if (hard_lanes != 0 || staged) return nullptr;
+    if (hard_lanes != 0) return nullptr;
     switch (lanes) {
-        case 4: return (const void*)&k_verify_tiles<4, 0, D, C, false, GR>;
-        case 8: return (const void*)&k_verify_tiles<8, 0, D, C, false, GR>;
-        case 16: return (const void*)&k_verify_tiles<16, 0, D, C, false, GR>;
-        case 32: return (const void*)&k_verify_tiles<32, 0, D, C, false, GR>;
-        case 64: return (const void*)&k_verify_tiles<64, 0, D, C, false, GR>;
+        case 4: return (const void*)&k_verify_tiles<4, 0, D, C, kNarrow, GR>;
+        case 8: return (const void*)&k_verify_tiles<8, 0, D, C, kNarrow, GR>;
+        case 16: return (const void*)&k_verify_tiles<16, 0, D, C, kNarrow, GR>;
+        case 32: return (const void*)&k_verify_tiles<32, 0, D, C, kNarrow, GR>;
+        case 64: return (const void*)&k_verify_tiles<64, 0, D, C, kNarrow, GR>;
         default: return nullptr;
     }
 }
 
 template <bool GR>
-const void* verify_tiles_by_flags(int lanes, int hard_lanes, bool staged, bool deferring, bool cosine) {
+const void* verify_tiles_by_flags(int lanes, int hard_lanes, int mode, bool deferring, bool cosine) {
     if (cosine)
-        return deferring ? verify_tiles_instance<true, true, GR>(lanes, hard_lanes, staged)
-                         : verify_tiles_instance<false, true, GR>(lanes, hard_lanes, staged);
-    return deferring ? verify_tiles_instance<true, false, GR>(lanes, hard_lanes, staged)
-                     : verify_tiles_instance<false, false, GR>(lanes, hard_lanes, staged);
+        return deferring ? verify_tiles_instance<true, true, GR>(lanes, hard_lanes, mode)
+                         : verify_tiles_instance<false, true, GR>(lanes, hard_lanes, mode);
+    return deferring ? verify_tiles_instance<true, false, GR>(lanes, hard_lanes, mode)
+                     : verify_tiles_instance<false, false, GR>(lanes, hard_lanes, mode);
 }
 
-// Grouped launches run the plain window merge whatever staged says: their
-// instances hold about ten more registers than the flat ones, and with the
-// window ring that costs a wavefront per SIMD (on the offline grouped step
-// the plain instance runs 12-14% faster).
-const void* kernel_verify_tiles(int lanes, int hard_lanes, bool staged, bool deferring, bool cosine, bool grouped) {
-    return grouped ? verify_tiles_by_flags<true>(lanes, hard_lanes, false, deferring, cosine)
-                   : verify_tiles_by_flags<false>(lanes, hard_lanes, staged, deferring, cosine);
+const void* kernel_verify_tiles(int lanes, int hard_lanes, int mode, bool deferring, bool cosine, bool grouped) {
+    return grouped ? verify_tiles_by_flags<true>(lanes, hard_lanes, mode, deferring, cosine)
+                   : verify_tiles_by_flags<false>(lanes, hard_lanes, mode, deferring, cosine);
 }
 
 const void* kernel_verify_deferred(bool cosine, bool grouped) {
@@ -1324,16 +1565,29 @@ hipError_t launch_build_heads(const int64_t* d_offsets, const uint32_t* d_start,
     return hipGetLastError();
 }
 
+hipError_t launch_build_signatures(const uint4* d_heads, const int32_t* d_tok, uint4* d_narrow, uint4* d_wide,
+                                   int64_t n_sets, hipStream_t st) {
+    if (n_sets <= 0) return hipSuccess;
+    const unsigned blocks = (unsigned)std::min<int64_t>((n_sets + 15) / 16, 65536);
+    if (d_wide)
+        hipLaunchKernelGGL((k_build_signatures<true>), dim3(blocks), dim3(kBlock), 0, st, d_heads, d_tok, d_narrow,
+                           d_wide, n_sets);
+    else
+        hipLaunchKernelGGL((k_build_signatures<false>), dim3(blocks), dim3(kBlock), 0, st, d_heads, d_tok, d_narrow,
+                           d_wide, n_sets);
+    return hipGetLastError();
+}
+
 size_t tiles_lds_bytes(const LaunchArgs& a) {
     // per wavefront: wave_stage staged output pairs, then defer_cap entries
     // per queue (a multiple of 16 bytes)
-    const size_t stage = (size_t)wave_stage(a.staged != 0) * sizeof(int2);
+    const size_t stage = (size_t)wave_stage(a.mode) * sizeof(int2);
     const size_t defer = (size_t)wave_queues(a.defer_from, spilling(a)) * a.defer_cap * 4u;
     return (size_t)(kBlock / kWave) * (stage + defer);
 }
 
 hipError_t launch_verify_tiles(const LaunchArgs& a, int grid, hipStream_t st) {
-    const void* f = kernel_verify_tiles(a.inline_lanes, a.hard_lanes, a.staged != 0,
+    const void* f = kernel_verify_tiles(a.inline_lanes, a.hard_lanes, a.mode,
                                         a.defer_from < kClasses || spilling(a), a.cosine != 0, a.grouped != 0);
     if (!f) return hipErrorInvalidValue;
     LaunchArgs args = a;

@@ -54,6 +54,7 @@ constexpr int kMaxDevices = 64;
 constexpr int64_t kMaxLaunchPairs = ((int64_t)1 << 31) - 1;  // pairs per launch
 constexpr int kMaxSpillIters = 1 << 20;
 constexpr int kMaxWgPerCu = 64;
+constexpr int64_t kWideMean = 40;  // mean set size above which a collection has wide signatures
 // device bytes per candidate pair of a request: the pair, a worst-case output
 // pair, and its queue entries
 constexpr size_t kBytesPerPair = 8 + 8 + 4 * ssj::kQueues;
@@ -130,6 +131,15 @@ void overlap_rule(int sim, int64_t t_num, int64_t t_den, int64_t max_r, int64_t 
     }
     // every den here is below 2^32 (thresholds below 2^31)
     division_magic(R.den, R);
+    // the same rule without a division where small numbers hold it
+    const unsigned __int128 small = 1u << 24, word = (unsigned __int128)1 << 32;
+    const unsigned __int128 most = (unsigned __int128)max_r + (unsigned __int128)max_s;
+    if (R.rule != ssj::kCosine && R.num < small && R.den < small && most < small &&
+        R.num * most < word && R.den * most < word) {
+        R.small_num = R.rule == ssj::kLinear ? (uint32_t)R.num : 0u;
+        R.small_add = R.rule == ssj::kLinear ? 0u : (uint32_t)R.num;
+        R.small_den = (uint32_t)R.den;
+    }
 }
 
 template <class T>
@@ -174,10 +184,10 @@ struct Scratch {
 };
 
 struct GraphKey {
-    int inline_lanes, hard_lanes, staged, defer_from, spill, cosine, grid1, grid2;
+    int inline_lanes, hard_lanes, mode, defer_from, spill, cosine, grid1, grid2;
     bool operator<(const GraphKey& o) const {
-        return std::tie(inline_lanes, hard_lanes, staged, defer_from, spill, cosine, grid1, grid2) <
-               std::tie(o.inline_lanes, o.hard_lanes, o.staged, o.defer_from, o.spill, o.cosine, o.grid1,
+        return std::tie(inline_lanes, hard_lanes, mode, defer_from, spill, cosine, grid1, grid2) <
+               std::tie(o.inline_lanes, o.hard_lanes, o.mode, o.defer_from, o.spill, o.cosine, o.grid1,
                         o.grid2);
     }
 };
@@ -211,6 +221,8 @@ struct ssj_coll {
     ssj_ctx* ctx = nullptr;
     int32_t* d_tok = nullptr;
     uint4* d_heads = nullptr;  // 32-byte record per set: start, len, first tokens
+    uint4* d_narrow = nullptr;  // signatures of the sets (in d_heads' allocation; null where
+    uint4* d_wide = nullptr;    // memory was too short, d_wide also where sets are not long)
     const uint4* d_classes = nullptr;  // with size_sorted, after the records: per set size {first set, size,
                                        // start of its tokens}, then {n_sets}
     int64_t n_sets = 0;
@@ -237,7 +249,7 @@ struct ssj_ctx {
     // in-order kernel workgroups per CU, limited by registers and by its
     // dynamic LDS: [4 * mapping index + 2 * cosine + deferring][deferred classes]
     // [8 * mapping + 4 * grouped + 2 * cosine + deferring][LDS queues per wavefront]
-    int occ_tiles[8 * 9][ssj::kQueues + 1] = {};
+    int occ_tiles[8 * 10][ssj::kQueues + 1] = {};
     int occ_deferred2[4] = {0};  // [2 * grouped + cosine]
     ssj_plan plan{};
     std::mutex mu;  // default scratch, host staging, collections, plan, graphs
@@ -329,8 +341,8 @@ int hip_fail(ssj_ctx* ctx, const char* what, hipError_t e) {
     } while (0)
 
 // index of an in-order mapping in occ_tiles
-int inline_index(int lanes, int hard_lanes, int staged) {
-    if (staged) return 8;
+int inline_index(int lanes, int hard_lanes, int mode) {
+    if (mode != ssj::kNarrow) return 7 + mode;
     if (lanes == 1) return hard_lanes == 0 ? 0 : (hard_lanes == 8 ? 6 : 7);
     switch (lanes) {
         case 4: return 1;
@@ -342,11 +354,12 @@ int inline_index(int lanes, int hard_lanes, int staged) {
     }
 }
 
-// in-order mappings: by lanes, hard lanes and staging (the window ring)
-constexpr int kMappings = 9;
-const int kInlineLanes[kMappings] = {1, 4, 8, 16, 32, 64, 1, 1, 1};
-const int kInlineHard[kMappings] = {0, 0, 0, 0, 0, 0, 8, 16, 0};
-const int kInlineStaged[kMappings] = {0, 0, 0, 0, 0, 0, 0, 0, 1};
+// in-order mappings by lanes, hard lanes and mode; a plan has all but that of
+// the wide signatures
+constexpr int kMappings = 10;
+const int kInlineLanes[kMappings] = {1, 4, 8, 16, 32, 64, 1, 1, 1, 1};
+const int kInlineHard[kMappings] = {0, 0, 0, 0, 0, 0, 8, 16, 0, 0};
+const int kInlineMode[kMappings] = {0, 0, 0, 0, 0, 0, 0, 0, ssj::kWide, ssj::kRing};
 
 int scratch_init(ssj_ctx* ctx, Scratch& s) {
     HIP_OR_FAIL(ctx, hipMalloc((void**)&s.d_ctr, sizeof(ssj::Counters)));
@@ -379,7 +392,8 @@ void default_plan(ssj_plan& p) {
 
 bool plan_valid(const ssj_plan& p) {
     if (p.staged != 0 && p.staged != 1) return false;
-    if (!ssj::inline_supported(p.inline_lanes, p.hard_lanes, p.staged != 0)) return false;
+    if (!ssj::inline_supported(p.inline_lanes, p.hard_lanes)) return false;
+    if (p.staged != 0 && (p.inline_lanes != 1 || p.hard_lanes != 0)) return false;
     if (p.defer_from < 0 || p.defer_from > ssj::kClasses) return false;
     for (int q = 0; q < ssj::kClasses; ++q)
         if (!ssj::lanes_supported(p.lanes[q])) return false;
@@ -399,13 +413,24 @@ bool plan_two_kernels(const ssj_plan& p) { return p.defer_from < ssj::kClasses |
 // Without either the launch is the in-order kernel alone, whose instance has
 // no queueing code (206 pairs of sets of about 12 tokens with a new context's
 // plan: 16.7 -> 11.1 us; with sets of 2,000 tokens both kernels run as before).
-ssj_plan plan_for(const ssj_plan& plan, int64_t max_r, int64_t max_s) {
+// With wide signatures the pairs that they and the record tokens leave, few but
+// often neighbours in the list and the longest of all, go to the deferred
+// kernel, which spreads them over the grid: 620,000 pairs of long sets 36 us
+// whatever the plan was (merged where they are found, by groups of 32 lanes,
+// 81 us, by the lanes of the former plans 64, 103 and 296).
+ssj_plan plan_for(const ssj_plan& plan, int64_t max_r, int64_t max_s, bool wide) {
     constexpr uint32_t bounds[ssj::kClasses] = SSJ_CLASS_BOUNDS;
     ssj_plan p = plan;
     int longest = 0;
     while (longest < ssj::kClasses - 1 && max_r + max_s > (int64_t)bounds[longest]) ++longest;
     if (longest < p.defer_from) p.defer_from = ssj::kClasses;
     if ((max_r + 3) / 4 + (max_s + 3) / 4 <= p.spill_iters) p.spill_iters = 0;
+    if (wide) {
+        p.hard_lanes = 0;
+        p.defer_from = ssj::kClasses;
+        p.spill_iters = 1;
+        p.spill_lanes = ssj::kBlock;
+    }
     return p;
 }
 
@@ -461,17 +486,17 @@ int vgpr_limited_blocks(const void* f) {
 
 // Workgroups of the in-order kernel that the device holds at once per
 // compute unit.
-int tiles_occupancy(const ssj_ctx* ctx, const ssj_plan& plan, bool cosine, bool grouped = false) {
+int tiles_occupancy(const ssj_ctx* ctx, const ssj_plan& plan, int mode, bool cosine, bool grouped = false) {
     const bool deferring = plan_two_kernels(plan);
     const int nq = ssj::wave_queues(plan.defer_from, plan.spill_iters > 0);
-    return std::max(1, ctx->occ_tiles[8 * inline_index(plan.inline_lanes, plan.hard_lanes, plan.staged) +
+    return std::max(1, ctx->occ_tiles[8 * inline_index(plan.inline_lanes, plan.hard_lanes, mode) +
                                       (grouped ? 4 : 0) + (cosine ? 2 : 0) + (deferring ? 1 : 0)][nq]);
 }
 
 // Workgroups of the in-order kernel: one per kBlock / kWave chunks, at most
 // plan.wg_per_cu per compute unit, or what the device holds at once.
-int grid_tiles(const ssj_ctx* ctx, const ssj_plan& plan, bool cosine, bool grouped, int64_t n_chunks) {
-    const int per_cu = plan.wg_per_cu > 0 ? plan.wg_per_cu : tiles_occupancy(ctx, plan, cosine, grouped);
+int grid_tiles(const ssj_ctx* ctx, const ssj_plan& plan, int mode, bool cosine, bool grouped, int64_t n_chunks) {
+    const int per_cu = plan.wg_per_cu > 0 ? plan.wg_per_cu : tiles_occupancy(ctx, plan, mode, cosine, grouped);
     const int64_t cap = (int64_t)ctx->n_cu * per_cu;
     const int64_t per_wg = ssj::kBlock / ssj::kWave;
     return (int)std::max<int64_t>(1, std::min<int64_t>((n_chunks + per_wg - 1) / per_wg, cap));
@@ -483,7 +508,7 @@ int grid_deferred(const ssj_ctx* ctx, bool cosine, bool grouped) {
 
 int launch_graph(ssj_ctx* ctx, const ssj::LaunchArgs& a, int g1, int g2, bool two,
                  hipStream_t st) {
-    GraphKey key{a.inline_lanes, a.hard_lanes, (int)a.staged, a.defer_from, ssj::spilling(a) ? 1 : 0,
+    GraphKey key{a.inline_lanes, a.hard_lanes, a.mode, a.defer_from, ssj::spilling(a) ? 1 : 0,
                  (int)a.cosine, g1, two ? g2 : 0};
     ssj::LaunchArgs args = a;
     void* kparams[] = {&args};
@@ -492,7 +517,7 @@ int launch_graph(ssj_ctx* ctx, const ssj::LaunchArgs& a, int g1, int g2, bool tw
         GraphEntry ge;
         HIP_OR_FAIL(ctx, hipGraphCreate(&ge.graph, 0));
         // (grouped launches do not use graphs)
-        const void* funcs[2] = {ssj::kernel_verify_tiles(a.inline_lanes, a.hard_lanes, a.staged != 0, two,
+        const void* funcs[2] = {ssj::kernel_verify_tiles(a.inline_lanes, a.hard_lanes, a.mode, two,
                                                          a.cosine != 0, false),
                                 ssj::kernel_verify_deferred(a.cosine != 0, false)};
         const int grids[2] = {g1, g2};
@@ -524,18 +549,60 @@ int launch_graph(ssj_ctx* ctx, const ssj::LaunchArgs& a, int g1, int g2, bool tw
     return SSJ_OK;
 }
 
+// The mode of a launch without wide signatures: staged plans have the window
+// ring where sets are long.  (The narrow signatures decide nearly every pair of
+// short sets, and the ring's LDS then only costs wavefronts; grouped instances
+// hold about ten more registers than the flat ones, and with the ring that
+// costs a wavefront per SIMD.)
+int plan_mode(const ssj_plan& plan, const ssj_coll* coll, const ssj_coll* cs, bool grouped) {
+    return plan.staged && !grouped && coll->d_wide && cs->d_wide ? ssj::kRing : ssj::kNarrow;
+}
+
+// Whether a launch of all pairs takes the wide signatures: both collections
+// have them, the plan has a lane per pair, every request asks two sets of mean
+// size to share half of it, and there are queues for the pairs that they leave.  (Memory that is short, or a stream being captured, which
+// rules out an allocation, leaves the launch to the plan.)
+bool wide_launch(const ssj_plan& plan, const ssj_coll* coll, const ssj_coll* cs, Scratch& sc, const Req* reqs,
+                 int n_req, hipStream_t st) {
+    if (plan.inline_lanes != 1 || !coll->d_wide || !cs->d_wide) return false;
+    const double mean = ((double)coll->n_tokens / (double)coll->n_sets + (double)cs->n_tokens / (double)cs->n_sets) / 2;
+    const bool grouped = reqs[0].grouped;
+    uint64_t all = 1;
+    for (int r = 0; r < n_req; ++r) {
+        ssj::Request R{};
+        overlap_rule(reqs[r].sim, reqs[r].t_num, reqs[r].t_den, coll->max_len, cs->max_len, R);
+        const double share = R.rule == ssj::kConstant ? (double)R.num / mean
+                             : R.rule == ssj::kCosine ? (double)R.num / (double)R.den
+                                                      : 2.0 * (double)R.num / (double)R.den;
+        if (share < 0.5) return false;
+        all += (uint64_t)std::max<int64_t>(reqs[r].n, 0);
+    }
+    const uint64_t words = (uint64_t)ssj::kQueues * all;
+    if (sc.d_queues && sc.q_cap >= words && (!grouped || (sc.d_probes && sc.probes_cap >= all))) return true;
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    hipError_t e = grow(sc.d_queues, sc.q_cap, (size_t)words);
+    if (e == hipSuccess && grouped) e = grow(sc.d_probes, sc.probes_cap, (size_t)all);
+    if (e != hipSuccess) (void)hipGetLastError();
+    return e == hipSuccess;
+}
+
 // Enqueues one launch verifying up to kMaxReq requests already on the device:
 // r ids index coll, s ids coll_s (null: coll, a self-join).
 int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* reqs, int n_req,
                    hipStream_t st, const ssj_plan& ctx_plan, bool allow_graph = true,
                    const ssj_coll* coll_s = nullptr, bool allow_timing = true) {
     const ssj_coll* cs = coll_s ? coll_s : coll;
-    const ssj_plan plan = plan_for(ctx_plan, coll->max_len, cs->max_len);
+    const bool wide = wide_launch(ctx_plan, coll, cs, sc, reqs, n_req, st);
+    const ssj_plan plan = plan_for(ctx_plan, coll->max_len, cs->max_len, wide);
     ssj::LaunchArgs a{};
     a.tok = coll->d_tok;
     a.heads = coll->d_heads;
     a.tok_s = cs->d_tok;
     a.heads_s = cs->d_heads;
+    a.mode = wide ? ssj::kWide : plan_mode(plan, coll, cs, reqs[0].grouped);
+    a.sig = wide ? coll->d_wide : coll->d_narrow;
+    a.sig_s = wide ? cs->d_wide : cs->d_narrow;
     a.ctr = sc.d_ctr;
     a.n_sets = (uint32_t)coll->n_sets;
     a.n_sets_s = (uint32_t)cs->n_sets;
@@ -545,7 +612,6 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     a.hard_lanes = plan.hard_lanes;
     a.spill_iters = plan.spill_iters > 0 ? (uint32_t)plan.spill_iters : 0xffffffffu;
     a.spill_lanes = plan.spill_lanes;
-    a.staged = plan.staged ? 1u : 0u;
     // in-order work unit: a chunk of kWave pairs of one request per wavefront
     const uint64_t tile_pairs = (uint64_t)ssj::kWave;
     a.defer_cap = (uint32_t)(2 * tile_pairs);
@@ -557,7 +623,6 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     // a launch is grouped when its requests are (callers never mix the two);
     // grouped launches have no window-ring instance
     a.grouped = n_req > 0 && reqs[0].grouped ? 1u : 0u;
-    if (a.grouped) a.staged = 0u;
     uint64_t tiles = 0, pairs = 0, groups = 0;
     for (int r = 0; r < n_req; ++r) {
         const Req& q = reqs[r];
@@ -591,7 +656,7 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     if (two) {
         HIP_OR_FAIL(ctx, grow(sc.d_queues, sc.q_cap, (size_t)ssj::kQueues * std::max<uint64_t>(pairs, 1)));
     }
-    if (two && sc.resume && ssj::spilling(a)) {
+    if (two && sc.resume && ssj::spilling(a) && !wide) {
         HIP_OR_FAIL(ctx, grow(sc.d_spill, sc.spill_cap, (size_t)std::max<uint64_t>(pairs, 1)));
         a.spill_state = sc.d_spill;
     }
@@ -606,7 +671,7 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     }
     a.queues = sc.d_queues;
     a.qcap = (uint32_t)(sc.q_cap / ssj::kQueues);
-    const int g1 = grid_tiles(ctx, plan, a.cosine != 0, a.grouped != 0, (int64_t)tiles);
+    const int g1 = grid_tiles(ctx, plan, a.mode, a.cosine != 0, a.grouped != 0, (int64_t)tiles);
     const int g2 = grid_deferred(ctx, a.cosine != 0, a.grouped != 0);
 
     std::array<hipEvent_t, 4> ev{nullptr, nullptr, nullptr, nullptr};
@@ -1148,8 +1213,9 @@ int ssj_init(const ssj_opts* opts, ssj_ctx** out) {
         for (int k = 0; k < 8 * kMappings && rc == SSJ_OK; ++k) {
             const bool deferring = (k & 1) != 0;
             const void* f = ssj::kernel_verify_tiles(kInlineLanes[k / 8], kInlineHard[k / 8],
-                                                     kInlineStaged[k / 8] != 0, deferring, (k & 2) != 0,
+                                                     kInlineMode[k / 8], deferring, (k & 2) != 0,
                                                      (k & 4) != 0);
+            if (!f) continue;
             // by the number of LDS queues per wavefront (deferred classes,
             // plus the spill queue)
             for (int nd = deferring ? 1 : 0; nd <= (deferring ? ssj::kQueues : 0) && rc == SSJ_OK; ++nd) {
@@ -1157,7 +1223,7 @@ int ssj_init(const ssj_opts* opts, ssj_ctx** out) {
                 la.defer_from = nd <= ssj::kClasses ? ssj::kClasses - nd : 0;
                 la.spill_iters = nd <= ssj::kClasses ? 0xffffffffu : 1u;
                 la.defer_cap = 2 * ssj::kWave;
-                la.staged = (uint32_t)kInlineStaged[k / 8];
+                la.mode = kInlineMode[k / 8];
                 la.inline_lanes = kInlineLanes[k / 8];
                 int occ = 0;
                 if ((e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, f, ssj::kBlock, ssj::tiles_lds_bytes(la))) != hipSuccess)
@@ -1368,7 +1434,15 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
     do {
         if ((e = hipMalloc((void**)&c->d_tok, padded.size() * 4)) != hipSuccess) break;
         const size_t n_rec = (size_t)std::max<int64_t>(n_sets, 1) * 2;
-        if ((e = hipMalloc((void**)&c->d_heads, (n_rec + classes.size()) * sizeof(uint4))) != hipSuccess) break;
+        const size_t n_narrow = n_rec / 2 * ssj::kNarrowUnits;
+        const size_t n_wide = n_tokens > n_sets * kWideMean ? n_rec / 2 * ssj::kWideUnits : 0;
+        if (hipMalloc((void**)&c->d_heads, (n_rec + classes.size() + n_narrow + n_wide) * sizeof(uint4)) == hipSuccess) {
+            c->d_narrow = c->d_heads + n_rec + classes.size();
+            if (n_wide) c->d_wide = c->d_narrow + n_narrow;
+        } else {
+            (void)hipGetLastError();
+            if ((e = hipMalloc((void**)&c->d_heads, (n_rec + classes.size()) * sizeof(uint4))) != hipSuccess) break;
+        }
         if (!classes.empty()) {
             c->d_classes = c->d_heads + n_rec;
             if ((e = hipMemcpyAsync(c->d_heads + n_rec, classes.data(), classes.size() * sizeof(uint4),
@@ -1380,6 +1454,8 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
         if ((e = hipMemcpyAsync(d_off, offsets, (size_t)(n_sets + 1) * 8, hipMemcpyHostToDevice, ctx->stream)) != hipSuccess) break;
         if ((e = hipMemcpyAsync(d_start, start.data(), start.size() * 4, hipMemcpyHostToDevice, ctx->stream)) != hipSuccess) break;
         if ((e = ssj::launch_build_heads(d_off, d_start, c->d_tok, c->d_heads, n_sets, ctx->stream)) != hipSuccess) break;
+        if (c->d_narrow && (e = ssj::launch_build_signatures(c->d_heads, c->d_tok, c->d_narrow, c->d_wide, n_sets,
+                                                             ctx->stream)) != hipSuccess) break;
         if ((e = hipStreamSynchronize(ctx->stream)) != hipSuccess) break;
     } while (0);
     if (d_off) (void)hipFree(d_off);
@@ -2296,6 +2372,7 @@ int ssj_autotune(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand, int
     ssj_plan staged_best = ctx->plan;  // best plan with the window ring
     double staged_ms = 1e30;
     for (int k = 0; k < kMappings && rc == SSJ_OK; ++k) {
+        if (kInlineMode[k] == ssj::kWide || (kInlineMode[k] == ssj::kRing && !coll->d_wide)) continue;
         for (int d = ssj::kClasses; d >= 1 && rc == SSJ_OK; --d) {
             // each at the resident grid and at twice that (a larger grid
             // evens out wavefronts that start late or issue slowly)
@@ -2303,12 +2380,12 @@ int ssj_autotune(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand, int
                 ssj_plan p = ctx->plan;
                 p.inline_lanes = kInlineLanes[k];
                 p.hard_lanes = kInlineHard[k];
-                p.staged = kInlineStaged[k];
+                p.staged = kInlineMode[k] == ssj::kRing ? 1 : 0;
                 p.defer_from = d;
                 p.spill_iters = 0;
                 p.wg_per_cu = 0;
                 for (int q = 0; q < ssj::kClasses; ++q) p.lanes[q] = kDeferredDefault[q];
-                if (twice) p.wg_per_cu = std::min(kMaxWgPerCu, 2 * tiles_occupancy(ctx, p, false));
+                if (twice) p.wg_per_cu = std::min(kMaxWgPerCu, 2 * tiles_occupancy(ctx, p, plan_mode(p, coll, coll, false), false));
                 double ms = 0;
                 if ((rc = measure(p, &ms)) != SSJ_OK) break;
                 if (ms < cur_ms) {
@@ -2319,7 +2396,7 @@ int ssj_autotune(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand, int
                     thread_ms = ms;
                     thread_best = p;
                 }
-                if (kInlineStaged[k] && kInlineLanes[k] == 1 && ms < staged_ms) {
+                if (p.staged && ms < staged_ms) {
                     staged_ms = ms;
                     staged_best = p;
                 }
@@ -2331,7 +2408,9 @@ int ssj_autotune(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand, int
     //    thread-per-pair plan and the best window-ring plan, each with and
     //    without its deferred classes
     static const int kSpillIters[6] = {4, 8, 12, 16, 24, 32};
-    for (const ssj_plan& base : {thread_best, staged_best}) {
+    std::vector<ssj_plan> bases{thread_best};
+    if (staged_ms < 1e30) bases.push_back(staged_best);
+    for (const ssj_plan& base : bases) {
         for (int nodefer = 0; nodefer < 2 && rc == SSJ_OK; ++nodefer) {
             if (nodefer && base.defer_from == ssj::kClasses) break;
             for (int it : kSpillIters) {
@@ -2380,7 +2459,7 @@ int ssj_autotune(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand, int
     // 4) the in-order grid: fewer or more workgroups per compute unit than
     //    fit at once
     if (rc == SSJ_OK) {
-        const int occ = cur.wg_per_cu > 0 ? cur.wg_per_cu : tiles_occupancy(ctx, cur, false);
+        const int occ = cur.wg_per_cu > 0 ? cur.wg_per_cu : tiles_occupancy(ctx, cur, plan_mode(cur, coll, coll, false), false);
         const ssj_plan base = cur;
         for (int wg : {occ - 1, occ + 1, occ + 2, (3 * occ) / 2}) {
             if (wg < 1 || wg > kMaxWgPerCu) continue;

@@ -13,11 +13,17 @@ constexpr int kBlock = 256;      // threads per workgroup of every verify kernel
 constexpr int kWave = 64;        // CDNA wavefront width
 constexpr int kMaxReq = 16;      // requests per launch
 constexpr int kHeadTokens = 6;   // leading tokens kept in each 32-byte set record
-// Staged output pairs per wavefront (in-order kernel).  The window ring takes
-// 24 KiB of LDS per workgroup, which with 512 pairs leaves four workgroups per
-// compute unit; with 256 there are five (620,000 pairs of long sets, with the
-// count published by the last kernel: 137 -> 128 us).
-__host__ __device__ constexpr unsigned wave_stage(bool staged) { return staged ? 4u * kWave : 8u * kWave; }
+// Signatures: a set's size and a bitmap with the bit of every token's hash
+// (96 or 480 bits), in 16-byte units; the narrow one of every collection, the
+// wide one of those with long sets.
+constexpr int kNarrowUnits = 1, kWideUnits = 4;
+constexpr uint32_t signature_bits(int units) { return 32u * (4u * (uint32_t)units - 1u); }
+// Modes of the in-order kernel with a lane per pair: narrow signatures, wide
+// ones (every pair that they and the record tokens leave is queued), narrow
+// ones and merges through the window ring in LDS.
+enum Mode : int { kNarrow = 0, kWide = 1, kRing = 2 };
+// Staged output pairs per wavefront (in-order kernel).
+__host__ __device__ constexpr unsigned wave_stage(int mode) { return (mode == kRing ? 4u : 6u) * kWave; }
 
 // How a request turns set sizes into its required overlap alpha (the
 // equivalent overlap of paper Table 1).
@@ -57,6 +63,10 @@ struct Request {
     uint32_t dmagic;
     uint32_t dshift;
     float cosine_ratio;        // kCosine in 64-bit arithmetic: num / den (0: it needs 128 bits)
+    // o >= alpha as o * small_den >= small_num * (|r| + |s|) + small_add, with
+    // factors below 2^24 and results below 2^32 for every pair of the launch's
+    // collections (small_den 0: not so, or not a linear rule)
+    uint32_t small_num, small_add, small_den;
 };
 
 constexpr unsigned kSlots = 32;  // counters that the workgroups of a kernel spread over: an atomic
@@ -82,6 +92,8 @@ struct LaunchArgs {
     const uint4* heads;                  // its set records: {start, len, tok0, tok1}, {tok2..tok5}
     const int32_t* tok_s;                // the same for the s side (an R-S join's second
     const uint4* heads_s;                // collection; the same collection in a self-join)
+    const uint4* sig;                    // signatures of the two (wide: the wide ones; null: none,
+    const uint4* sig_s;                  // every pair reads its set records)
     Counters* ctr;
     uint32_t* queues;                    // kQueues queues of qcap global pair indices
     uint32_t qcap;
@@ -97,9 +109,7 @@ struct LaunchArgs {
                                          // in-order kernel before it is queued for the deferred
                                          // kernel (0xffffffff: no limit)
     int spill_lanes;                     // lanes per pair of the spill queue
-    uint32_t staged;                     // != 0: thread-per-pair merges through the window
-                                         // ring in LDS, their loads two steps ahead
-                                         // (merge_ring); spill_iters counts window steps
+    int mode;                            // Mode (kNarrow if inline_lanes > 1)
     uint32_t grouped;                    // != 0: every request of the launch is grouped
     uint32_t two_kernels;                // != 0: the deferred kernel follows (and publishes the counts)
     uint32_t* probes;                    // grouped launches that defer: the probe id of every
@@ -124,6 +134,9 @@ struct LaunchArgs {
 // array.
 hipError_t launch_build_heads(const int64_t* d_offsets, const uint32_t* d_start, const int32_t* d_tok,
                               uint4* d_heads, int64_t n_sets, hipStream_t st);
+// Signatures of the sets (d_wide: null for none) from their records and tokens.
+hipError_t launch_build_signatures(const uint4* d_heads, const int32_t* d_tok, uint4* d_narrow, uint4* d_wide,
+                                   int64_t n_sets, hipStream_t st);
 // Group pre-pass of a grouped launch (a.grouped): writes every request's
 // chunk_g and checks its group ends (not decreasing, none above n, the last
 // one n); malformed ends set the request's error flag, which the launch
@@ -144,11 +157,9 @@ size_t tiles_lds_bytes(const LaunchArgs& a);
 // Zeroes n 32-bit words of device memory with a fill kernel.
 hipError_t launch_clear_words(uint32_t* d_words, size_t n, hipStream_t st);
 
-// The in-order kernel of a mapping: lanes per pair and hard lanes, or the
-// window-ring thread-per-pair merge (staged, lanes 1, hard_lanes 0); for a
-// flat or a grouped launch (grouped launches have no window-ring instance:
-// staged selects the plain one).
-const void* kernel_verify_tiles(int lanes, int hard_lanes, bool staged, bool deferring, bool cosine, bool grouped);
+// The in-order kernel of a mapping: lanes per pair, hard lanes and mode, for a
+// flat or a grouped launch (nullptr: there is none).
+const void* kernel_verify_tiles(int lanes, int hard_lanes, int mode, bool deferring, bool cosine, bool grouped);
 const void* kernel_verify_deferred(bool cosine, bool grouped);
 
 // LDS queues of a wavefront of the in-order kernel: one per deferred class,
@@ -157,7 +168,6 @@ __host__ __device__ inline int wave_queues(int defer_from, bool spill) { return 
 __host__ __device__ inline bool spilling(const LaunchArgs& a) { return a.spill_iters != 0xffffffffu; }
 
 bool lanes_supported(int lanes);              // deferred classes: 1..64 or kBlock
-bool inline_supported(int lanes, int hard_lanes, bool staged);  // in-order kernel: 1..64; 0/8/16 hard
-                                                                 // lanes with 1; staged with 1 and 0
+bool inline_supported(int lanes, int hard_lanes);  // in-order kernel: 1..64; 0/8/16 hard lanes with 1
 
 }  // namespace ssj

@@ -158,3 +158,60 @@ def test_tiles_of_four_tokens_per_lane(S, ctx, lanes):
                 assert np.array_equal(oracle.sort_pairs(S.ssj_verify(ctx, h, cand, tn, td)), want), (plan, tn, td)
     finally:
         S.ssj_free_collection(ctx, h)
+
+
+def _similar_at(n, most, seed, step):
+    """Sets of n tokens in pairs that share exactly k of them, k = 0, step, ..., n."""
+    rng = np.random.default_rng(seed)
+    sets = []
+    for k in list(range(0, n, step)) + [n]:
+        t = rng.choice(most, 2 * n - k, replace=False)
+        sets += [np.sort(t[:n]).tolist(), np.sort(t[n - k:]).tolist()]
+    return sets
+
+
+@pytest.mark.parametrize("n, most", [(1, 2**31 - 1), (3, 60), (12, 2**31 - 1), (40, 10**6), (41, 2**31 - 1),
+                                     (130, 10**6), (600, 5000)])
+def test_signatures_keep_every_similar_pair(S, ctx, n, most):
+    """Pairs of every overlap at the sizes where signatures are sparse, full and
+    change their width, all pairs of the collection as candidates, under each
+    rule and on both sides of the thresholds that long sets have them for."""
+    sets = _similar_at(n, most, n, max(1, n // 25))
+    c = synth.collection_from_sets(sorted(sets, key=len))
+    r, s = np.tril_indices(c.n_sets, 0)
+    cand = np.stack([r, s], axis=1).astype(np.int32)
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        for plan in [{}, dict(inline_lanes=1, defer_from=5), dict(defer_from=5, spill_iters=2), dict(defer_from=5, staged=1),
+                     dict(defer_from=5, hard_lanes=8)]:
+            S.ssj_set_plan(ctx, S.make_plan(**plan))
+            for sim, a, b in [("jaccard", 1, 3), ("jaccard", 33, 100), ("jaccard", 7, 10), ("jaccard", 1, 1),
+                              ("dice", 1, 2), ("dice", 4, 5), ("cosine", 1, 2), ("cosine", 49999, 100000),
+                              ("overlap", 1, 1), ("overlap", max(1, n // 2), 1), ("overlap", n, 1), ("overlap", 2**31 - 1, 1)]:
+                want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, a, b, sim=sim))
+                got = oracle.sort_pairs(S.ssj_verify_sim(ctx, h, cand, sim, a, b))
+                assert np.array_equal(got, want), (n, plan, sim, a, b)
+                got = oracle.sort_pairs(S.ssj_verify_groups(ctx, h, h, *S.groups_of(cand), sim, a, b))
+                assert np.array_equal(got, want), (n, plan, sim, a, b, "groups")
+    finally:
+        S.ssj_set_plan(ctx, S.make_plan())
+        S.ssj_free_collection(ctx, h)
+
+
+@pytest.mark.parametrize("n_r, n_s", [(12, 12), (12, 130), (130, 12), (130, 200)])
+def test_signatures_of_two_collections(S, ctx, n_r, n_s):
+    """Collections with equal and with different signatures."""
+    rng = np.random.default_rng(n_r + n_s)
+    base = np.sort(rng.choice(400, n_s, replace=False))
+    def some(n, k):
+        return [np.sort(rng.choice(base if i % 2 else 400, min(n, n_s if i % 2 else 400), replace=False)).tolist() for i in range(k)]
+    cr, cs = (synth.collection_from_sets(sorted(x, key=len)) for x in (some(n_r, 40), some(n_s, 50)))
+    cand = np.stack(np.meshgrid(np.arange(40), np.arange(50)), axis=-1).reshape(-1, 2).astype(np.int32)
+    hr, hs = (S.ssj_upload_collection(ctx, c.offsets, c.tokens) for c in (cr, cs))
+    try:
+        for sim, a, b in [("jaccard", 1, 4), ("jaccard", 2, 5), ("jaccard", 7, 10), ("cosine", 3, 5), ("dice", 3, 5), ("overlap", 9, 1)]:
+            want = oracle.sort_pairs(oracle.select_rs(cr.offsets, cr.tokens, cs.offsets, cs.tokens, cand, a, b, sim=sim))
+            assert np.array_equal(oracle.sort_pairs(S.ssj_verify_rs(ctx, hr, hs, cand, sim, a, b)), want), (sim, a, b)
+    finally:
+        S.ssj_free_collection(ctx, hr)
+        S.ssj_free_collection(ctx, hs)
