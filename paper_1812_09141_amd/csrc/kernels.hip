@@ -305,6 +305,38 @@ struct CandLoad {
     uint32_t g0;  // the window's first group (wave-uniform)
 };
 
+__device__ __forceinline__ int32_t group_end(const int2* groups, uint32_t g) {
+    return reinterpret_cast<const int32_t*>(groups)[2u * g + 1u];
+}
+
+// Group x of all requests of the launch (requests located by the prefix sums
+// group_off): checks its end against its predecessor's and the request's size,
+// and calls write(r, t, g) for every chunk start t * kWave inside its
+// candidates.  With ends that do not decrease, end above n or a last end other
+// than n, the request's error flag is set; only chunks of the request are ever
+// written.
+template <class Write>
+__device__ __forceinline__ void group_chunks(const LaunchArgs& a, uint32_t x, Write write) {
+    int r = 0;
+    for (int q = 1; q < a.n_req; ++q) r += (x >= a.group_off[q]) ? 1 : 0;
+    const Request& R = a.req[r];
+    const uint32_t g = x - a.group_off[r];
+    const int32_t e = group_end(R.groups, g);
+    const int32_t pv = g > 0u ? group_end(R.groups, g - 1u) : 0;
+    if (e < pv || (uint32_t)e > R.n || (g + 1u == R.n_groups && (uint32_t)e != R.n)) {
+        atomicOr(&a.ctr->err[r], 1u);
+        return;
+    }
+    // 0 <= max(pv, 0) <= e <= n: every t written is below the request's chunk count
+    const uint32_t lo = (uint32_t)max(pv, 0), hi = (uint32_t)e;
+    for (uint32_t t = (lo + (uint32_t)kWave - 1u) / (uint32_t)kWave; t * (uint32_t)kWave < hi; ++t) write(r, t, g);
+}
+
+// First group of chunk c: from the pre-pass, or without one from LDS.
+__device__ __forceinline__ uint32_t first_group(const LaunchArgs& a, uint32_t c, const uint32_t* s_chunk) {
+    return a.chunk_g != nullptr ? a.chunk_g[c] : s_chunk[c];
+}
+
 // First groups of a wavefront's upcoming chunks, one per lane: lane L holds
 // chunk_g of the wavefront's chunk with ordinal base + L (its chunk
 // first + (base + L) * nw, clamped to the last chunk as the pipelines clamp
@@ -312,10 +344,11 @@ struct CandLoad {
 // before its loads are issued (one vector load per 64 chunks of a wavefront).
 template <bool GR>
 __device__ __forceinline__ uint32_t load_chunk_groups(const LaunchArgs& a, uint32_t first, uint32_t nw,
-                                                      uint32_t n_chunks, uint32_t base, int lane) {
+                                                      uint32_t n_chunks, uint32_t base, int lane,
+                                                      const uint32_t* s_chunk) {
     if constexpr (!GR) return 0u;
     const unsigned long long c = (unsigned long long)first + (unsigned long long)(base + (uint32_t)lane) * nw;
-    return a.chunk_g[c < n_chunks ? (uint32_t)c : n_chunks - 1u];
+    return first_group(a, c < n_chunks ? (uint32_t)c : n_chunks - 1u, s_chunk);
 }
 
 // Issues the loads of the lane's candidate of the chunk at candidate kb of
@@ -714,7 +747,7 @@ template <int F, bool D, bool C, int M, bool GR>
 __device__ __forceinline__ void walk(const LaunchArgs& a, uint32_t first, uint32_t nw, uint32_t n_chunks,
                                      int2* w_out, uint32_t* w_defer, unsigned long long& dc, int2* w_hpr,
                                      uint32_t* w_hst, int2* w_list, uint32_t* w_list_k, uint32_t* w_marks,
-                                     uint4* w_ring, uint32_t* s_only, uint32_t& ocnt, int& r_last) {
+                                     const uint32_t* s_chunk, uint4* w_ring, uint32_t* s_only, uint32_t& ocnt, int& r_last) {
     constexpr int U = M == kWide ? kWideUnits : kNarrowUnits;
     // Signatures while they leave at most this many pairs of a chunk on average;
     // otherwise they are tried again on every sixteenth chunk.  (The 18% of the
@@ -735,7 +768,7 @@ __device__ __forceinline__ void walk(const LaunchArgs& a, uint32_t first, uint32
     uint32_t bi = 0, ei = a.tile_off[1], ni = a.req[0].n;
     const int2* ci = a.req[0].cand;
     uint32_t ord = 0;  // ordinal of the next chunk to request
-    uint32_t vbase = 0, vg = load_chunk_groups<GR>(a, first, nw, n_chunks, 0u, lane);
+    uint32_t vbase = 0, vg = load_chunk_groups<GR>(a, first, nw, n_chunks, 0u, lane, s_chunk);
     // requests the candidates of the next chunk (past the last one: of the last)
     auto issue = [&](CandLoad& c, int& r, uint32_t& kb) {
         const uint32_t q = min(ord++, share - 1u);
@@ -752,7 +785,7 @@ __device__ __forceinline__ void walk(const LaunchArgs& a, uint32_t first, uint32
         if constexpr (GR) {
             if (q - vbase >= (uint32_t)kWave) {
                 vbase = q;
-                vg = load_chunk_groups<GR>(a, first, nw, n_chunks, vbase, lane);
+                vg = load_chunk_groups<GR>(a, first, nw, n_chunks, vbase, lane, s_chunk);
             }
             c = issue_cand<GR>(a, a.req[ri], kb, lane, (uint32_t)__builtin_amdgcn_readlane((int)vg, (int)(q - vbase)));
         } else {
@@ -950,6 +983,8 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     // group search scratch of grouped launches (resolve_cand)
     __shared__ uint32_t s_marks[GR ? kWaves * kWave : 1];
     uint32_t* w_marks = s_marks + (GR ? wl * kWave : 0u);
+    // the chunks' first groups in a small grouped launch
+    __shared__ uint32_t s_chunk[GR ? kOwnChunks : 1];
     // the window rings of merge_ring
     __shared__ uint4 s_ring[M == kRing ? kWaves * kRingSlots : 1];
     uint4* w_ring = s_ring + (M == kRing ? wl * kRingSlots : 0u);
@@ -959,6 +994,15 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     int r_last = 0;
     if (threadIdx.x < (unsigned)kMaxReq) s_only[threadIdx.x] = 0u;
     if (threadIdx.x == 0) s_finished = 0u;
+    if constexpr (GR) {
+        if (a.chunk_g == nullptr) {
+            // (chunks of a malformed request may get no group: any will do)
+            for (uint32_t x = threadIdx.x; x < kOwnChunks; x += (uint32_t)kBlock) s_chunk[x] = 0u;
+            __syncthreads();
+            for (uint32_t x = threadIdx.x; x < a.group_off[a.n_req]; x += (uint32_t)kBlock)
+                group_chunks(a, x, [&](int r, uint32_t t, uint32_t g) { s_chunk[a.tile_off[r] + t] = g; });
+        }
+    }
     __syncthreads();
     uint32_t ocnt = 0;
     unsigned long long dc = 0ull;  // deferred queue fill counts (dcount)
@@ -967,7 +1011,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     const uint32_t first = blockIdx.x * kWaves + (uint32_t)w;
     if constexpr (G == 1) {
         walk<F, D, C, M, GR>(a, first, nw, n_chunks, w_out, w_defer, dc, w_hpr, w_hst, s_list + wl * 2 * kWave,
-                             s_list_k + (D ? wl * 2 * kWave : 0u), w_marks, w_ring, s_only, ocnt, r_last);
+                             s_list_k + (D ? wl * 2 * kWave : 0u), w_marks, s_chunk, w_ring, s_only, ocnt, r_last);
     } else {
         int r_cur = 0;
         uint32_t kb_cur = 0;
@@ -992,7 +1036,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
             // a grouped chunk's pairs are found once, lane k holding pair
             // kb + k, and handed to the groups by permutes
             int2 cp = make_int2(0, 0);
-            if constexpr (GR) cp = resolve_cand<GR>(a, R, kb, lane, issue_cand<GR>(a, R, kb, lane, a.chunk_g[T]), w_marks);
+            if constexpr (GR) cp = resolve_cand<GR>(a, R, kb, lane, issue_cand<GR>(a, R, kb, lane, first_group(a, T, s_chunk)), w_marks);
             auto pair_at = [&](int sub) -> int2 {
                 const int src = min(sub, G - 1) * GPW + grp;
                 if constexpr (GR) return make_int2(bperm(cp.x, src), bperm(cp.y, src));
@@ -1380,37 +1424,12 @@ __global__ __launch_bounds__(kBlock, 4) void k_verify_deferred(LaunchArgs a) {
 // {probe id, exclusive end}, and its candidates are the s ids
 // sids[end(g-1) .. end(g)) with end(-1) = 0.  The verification kernels read
 // them in place (issue_cand / resolve_cand); this pre-pass gives each chunk
-// of kWave candidates its first group.
-
-__device__ __forceinline__ int32_t group_end(const int2* groups, uint32_t g) {
-    return reinterpret_cast<const int32_t*>(groups)[2u * g + 1u];
-}
-
-// One thread per group of all requests of the launch (requests located by
-// the prefix sums group_off): checks the group's end against its
-// predecessor's and the request's size, and writes chunk_g[t] = g for every
-// chunk start t * kWave inside the group's candidates.  With ends that do not
-// decrease, end above n or a last end other than n, the request's error flag
-// is set; only in-range entries of chunk_g are ever written.
+// of kWave candidates its first group (group_chunks), in launches too large for
+// every workgroup to find them itself.
 __global__ void k_group_chunks(LaunchArgs a) {
     const uint32_t total = a.group_off[a.n_req];
-    for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < total; x += gridDim.x * blockDim.x) {
-        int r = 0;
-        for (int q = 1; q < a.n_req; ++q) r += (x >= a.group_off[q]) ? 1 : 0;
-        const Request& R = a.req[r];
-        const uint32_t g = x - a.group_off[r];
-        const int32_t e = group_end(R.groups, g);
-        const int32_t pv = g > 0u ? group_end(R.groups, g - 1u) : 0;
-        const bool bad = e < pv || (uint32_t)e > R.n || (g + 1u == R.n_groups && (uint32_t)e != R.n);
-        if (bad) {
-            atomicOr(&a.ctr->err[r], 1u);
-            continue;
-        }
-        // 0 <= max(pv, 0) <= e <= n: every t written is below the request's chunk count
-        const uint32_t lo = (uint32_t)max(pv, 0), hi = (uint32_t)e;
-        for (uint32_t t = (lo + (uint32_t)kWave - 1u) / (uint32_t)kWave; t * (uint32_t)kWave < hi; ++t)
-            R.chunk_g[t] = g;
-    }
+    for (uint32_t x = blockIdx.x * blockDim.x + threadIdx.x; x < total; x += gridDim.x * blockDim.x)
+        group_chunks(a, x, [&](int r, uint32_t t, uint32_t g) { a.req[r].chunk_g[t] = g; });
 }
 
 // Zeroes n 32-bit words (a fill kernel: usable where a memset node is not).

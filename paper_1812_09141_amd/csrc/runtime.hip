@@ -660,10 +660,13 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
         HIP_OR_FAIL(ctx, grow(sc.d_spill, sc.spill_cap, (size_t)std::max<uint64_t>(pairs, 1)));
         a.spill_state = sc.d_spill;
     }
+    const bool own_chunks = groups <= ssj::kOwnGroups && tiles <= ssj::kOwnChunks;
     if (a.grouped) {
-        HIP_OR_FAIL(ctx, grow(sc.d_chunk_g, sc.chunk_cap, (size_t)std::max<uint64_t>(tiles, 1)));
-        a.chunk_g = sc.d_chunk_g;
-        for (int r = 0; r < n_req; ++r) a.req[r].chunk_g = sc.d_chunk_g + a.tile_off[r];
+        if (!own_chunks) {
+            HIP_OR_FAIL(ctx, grow(sc.d_chunk_g, sc.chunk_cap, (size_t)std::max<uint64_t>(tiles, 1)));
+            a.chunk_g = sc.d_chunk_g;
+            for (int r = 0; r < n_req; ++r) a.req[r].chunk_g = sc.d_chunk_g + a.tile_off[r];
+        }
         if (two) {
             HIP_OR_FAIL(ctx, grow(sc.d_probes, sc.probes_cap, (size_t)std::max<uint64_t>(pairs, 1)));
             a.probes = sc.d_probes;
@@ -686,7 +689,7 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     }
     // grouped launches start with the group pre-pass (outside the graph and
     // the timing events, which cover the verification kernels)
-    if (a.grouped) HIP_OR_FAIL(ctx, ssj::launch_group_chunks(a, st));
+    if (a.grouped && !own_chunks) HIP_OR_FAIL(ctx, ssj::launch_group_chunks(a, st));
     if (plan.use_graph && allow_graph && !timing && !a.grouped) {
         int rc = launch_graph(ctx, a, g1, g2, two, st);
         if (rc != SSJ_OK) return rc;

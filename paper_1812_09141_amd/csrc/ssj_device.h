@@ -38,6 +38,12 @@ enum OverlapRule : uint32_t {
 constexpr long long kCosineSizes = 1ll << 16;
 constexpr long long kCosineTerms = 1ll << 15;
 
+// Grouped launches of at most this many groups and chunks go without the
+// pre-pass: every workgroup finds the chunks' first groups itself, a launch
+// less on the way to the result (700 candidates of short sets in 4 requests:
+// 16.0 -> 14.2 us, 4,200 candidates 15.4 -> 14.6; with 13,000 both take 16.7).
+constexpr uint32_t kOwnGroups = 2048, kOwnChunks = 512;
+
 // One verification request inside a launch.
 struct Request {
     const int2* cand;          // (r, s) pairs
@@ -118,7 +124,8 @@ struct LaunchArgs {
                                          // spilled merge by global pair index, from which the
                                          // deferred kernel resumes it (nullptr: it restarts)
     const uint32_t* chunk_g;             // grouped launches: every request's chunk_g, by global
-                                         // chunk index (req[r].chunk_g = chunk_g + tile_off[r])
+                                         // chunk index (req[r].chunk_g = chunk_g + tile_off[r]);
+                                         // nullptr: every workgroup finds them itself
     uint32_t group_off[kMaxReq + 1];     // grouped launches: prefix sums of per-request groups
     uint32_t tile_off[kMaxReq + 1];      // prefix sums of per-request chunks (of kWave pairs)
     uint32_t pair_off[kMaxReq + 1];      // prefix sums of per-request pairs

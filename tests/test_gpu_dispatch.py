@@ -215,3 +215,37 @@ def test_signatures_of_two_collections(S, ctx, n_r, n_s):
     finally:
         S.ssj_free_collection(ctx, hr)
         S.ssj_free_collection(ctx, hs)
+
+
+@pytest.mark.parametrize("n_groups, n_cand", [(1, 1), (1, 512 * 64), (2048, 512 * 64), (2048, 512 * 64 + 1),
+                                              (2049, 512 * 64), (2048, 64), (3000, 2048), (1, 512 * 64 + 1)])
+def test_small_grouped_launches_with_and_without_a_pre_pass(S, ctx, n_groups, n_cand):
+    """Groups and chunks at the bounds up to which the workgroups find their
+    groups themselves, with empty groups, and with malformed ends."""
+    import torch
+    rng = np.random.default_rng(n_cand)
+    c = synth.collection_from_sets([np.sort(rng.choice(40, n, replace=False)).tolist()
+                                    for n in np.sort(rng.integers(2, 20, 300))])
+    probes = rng.integers(0, c.n_sets, n_groups).astype(np.int32)
+    ends = np.sort(rng.integers(0, n_cand + 1, n_groups)).astype(np.int32)
+    ends[-1] = n_cand
+    groups = np.stack([probes, ends], axis=1)
+    sids = rng.integers(0, c.n_sets, n_cand).astype(np.int32)
+    flat = np.stack([np.repeat(probes, np.diff(ends, prepend=0)), sids], axis=1)
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        for plan in [dict(defer_from=5), dict(defer_from=1), dict(inline_lanes=8, defer_from=5)]:
+            S.ssj_set_plan(ctx, S.make_plan(**plan))
+            want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, flat, 1, 3))
+            got = oracle.sort_pairs(S.ssj_verify_groups(ctx, h, h, groups, sids, "jaccard", 1, 3))
+            assert np.array_equal(got, want), plan
+            d_s, d_n = torch.from_numpy(sids).cuda(), torch.zeros(1, dtype=torch.int64, device="cuda:0")
+            for at, end in [(n_groups - 1, n_cand - 1), (n_groups // 2, n_cand + 1), (n_groups // 2, -1), (0, ends[0])]:
+                bad = groups.copy()
+                bad[at, 1] = end
+                S.ssj_verify_groups_device(ctx, h, h, torch.from_numpy(bad).cuda(), d_s, "jaccard", 1, 3, None, d_n)
+                torch.cuda.synchronize()
+                assert int(d_n) == (want.shape[0] if end == ends[at] else -1), (plan, at, end)
+    finally:
+        S.ssj_set_plan(ctx, S.make_plan())
+        S.ssj_free_collection(ctx, h)
