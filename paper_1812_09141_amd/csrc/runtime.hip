@@ -26,6 +26,7 @@
 #include <vector>
 
 #include "ssj.h"
+#include "copy_pool.h"
 #include "ssj_device.h"
 #include "filter.h"
 #include "join.h"
@@ -62,6 +63,9 @@ constexpr size_t kBytesPerPair = 8 + 8 + 4 * ssj::kQueues;
 // buffers of kRingPiece pairs, at most kMaxPieces pieces per device batch
 constexpr int64_t kRingPiece = (int64_t)1 << 20;
 constexpr int64_t kMaxPieces = 64;
+// Pairs from which a single piece goes through a pinned buffer (97,000 pairs 89 us so,
+// 82 straight from the caller's; 153,000 pairs 103 and 115).
+constexpr int64_t kRingLeast = (int64_t)1 << 17;
 // pairs that ssj_join copies along with the count
 constexpr int64_t kEarlyPairs = 4096;
 // a stream slot may always hold this many pairs, whatever the budget leaves
@@ -274,6 +278,7 @@ struct ssj_ctx {
     hipEvent_t ring_ev[2] = {nullptr, nullptr};
     long long* d_counts = nullptr;  // kMaxPieces
     long long* h_counts = nullptr;  // pinned, kMaxPieces
+    int2* h_early = nullptr;        // pinned, kEarlyPairs: first pairs of ssj_verify and ssj_join
     uint64_t ring_seq = 0;
     // grouped candidates: host-call staging of groups and s ids, and the
     // flat pairs they expand to (with one word per 64 candidates)
@@ -306,7 +311,6 @@ struct ssj_ctx {
                temp_cap = 0;
         ssj::JoinCtl* ctl = nullptr;                 // zero between joins
         unsigned long long* h_meets = nullptr;       // pinned
-        int2* h_pairs = nullptr;                     // pinned, kEarlyPairs: ssj_join's first pairs
         hipEvent_t ev = nullptr;                     // the number of meetings is on the host
     } join;
     std::atomic<bool> failed{false};
@@ -324,6 +328,7 @@ struct ssj_ctx {
     double t_inorder_ms = 0.0, t_deferred_ms = 0.0;
     int64_t t_launches = 0;
     std::unique_ptr<StreamEngine> engine;
+    ssj::CopyPool copies;  // copies of candidates to pinned memory
     Scratch noalloc;  // views into this device's copy of scratch (owned by nobody)
 };
 
@@ -1318,7 +1323,7 @@ int ssj_shutdown(ssj_ctx* ctx) {
                         (void*)ctx->join.temp, (void*)ctx->join.ctl})
             if (q) (void)hipFree(q);
         if (ctx->join.h_meets) (void)hipHostFree(ctx->join.h_meets);
-        if (ctx->join.h_pairs) (void)hipHostFree(ctx->join.h_pairs);
+        if (ctx->h_early) (void)hipHostFree(ctx->h_early);
         if (ctx->join.ev) (void)hipEventDestroy(ctx->join.ev);
         if (ctx->d_count) (void)hipFree(ctx->d_count);
         if (ctx->h_count) (void)hipHostFree(ctx->h_count);
@@ -1969,12 +1974,12 @@ int ssj_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     if (done) {
         // the count is stored in pinned memory by the join's last kernel, and
         // the first pairs come with it
-        if (out_cap > 0 && !ctx->join.h_pairs)
-            HIP_OR_FAIL(ctx, hipHostMalloc((void**)&ctx->join.h_pairs, kEarlyPairs * sizeof(int2),
+        if (out_cap > 0 && !ctx->h_early)
+            HIP_OR_FAIL(ctx, hipHostMalloc((void**)&ctx->h_early, kEarlyPairs * sizeof(int2),
                                            hipHostMallocDefault));
         early = std::min<int64_t>({kEarlyPairs, out_cap, (int64_t)ctx->out_cap});
         if (early > 0)
-            HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->join.h_pairs, ctx->d_out, (size_t)early * sizeof(int2),
+            HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_early, ctx->d_out, (size_t)early * sizeof(int2),
                                             hipMemcpyDeviceToHost, st));
     } else {
         int64_t n = 0;
@@ -1989,7 +1994,7 @@ int ssj_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     if (k < 0) return set_error(SSJ_EDEVICE, "id error in generated candidates");
     const int64_t take = std::min<int64_t>(k, out_cap);
     early = std::min(early, take);
-    if (early > 0) std::memcpy(out, ctx->join.h_pairs, (size_t)early * sizeof(int2));
+    if (early > 0) std::memcpy(out, ctx->h_early, (size_t)early * sizeof(int2));
     if (take > early) {
         HIP_OR_FAIL(ctx, hipMemcpyAsync(out + early, ctx->d_out + early, (size_t)(take - early) * 8,
                                         hipMemcpyDeviceToHost, st));
@@ -2029,34 +2034,6 @@ int ssj_verify_device_noalloc(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair
 
 namespace {
 
-// Host-buffer verification of flat pairs, r ids in coll, s ids in coll_s, in
-// chunks that fit the HBM budget.
-// Copies bytes from pageable to pinned host memory, in up to four threads
-// for large copies (one thread copies at a fraction of what PCIe takes).
-void host_copy(void* dst, const void* src, size_t bytes) {
-    constexpr size_t kSplit = (size_t)4 << 20;
-    const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
-    const unsigned T = bytes >= kSplit ? std::min(4u, hw) : 1u;
-    if (T <= 1) {
-        std::memcpy(dst, src, bytes);
-        return;
-    }
-    const size_t part = ((bytes + T - 1) / T + 63) & ~(size_t)63;
-    auto copy_part = [=](unsigned t) {
-        const size_t b = (size_t)t * part;
-        if (b < bytes) std::memcpy((char*)dst + b, (const char*)src + b, std::min(bytes - b, part));
-    };
-    std::vector<std::thread> th;
-    unsigned t = 1;
-    try {
-        for (; t < T; ++t) th.emplace_back(copy_part, t);
-    } catch (...) {  // no thread: the rest in this one
-        for (; t < T; ++t) copy_part(t);
-    }
-    copy_part(0);
-    for (auto& x : th) x.join();
-}
-
 // The pinned ring and per-piece counts of the host-buffer path (ctx->mu held).
 hipError_t ring_init(ssj_ctx* ctx) {
     hipError_t e = hipSuccess;
@@ -2069,6 +2046,8 @@ hipError_t ring_init(ssj_ctx* ctx) {
     if (e == hipSuccess && !ctx->d_counts) e = hipMalloc((void**)&ctx->d_counts, sizeof(long long) * kMaxPieces);
     if (e == hipSuccess && !ctx->h_counts)
         e = hipHostMalloc((void**)&ctx->h_counts, sizeof(long long) * kMaxPieces, hipHostMallocDefault);
+    if (e == hipSuccess && !ctx->h_early)
+        e = hipHostMalloc((void**)&ctx->h_early, kEarlyPairs * sizeof(int2), hipHostMallocDefault);
     return e;
 }
 
@@ -2078,8 +2057,10 @@ hipError_t ring_init(ssj_ctx* ctx) {
 // is copied to the device on the copy stream and piece k - 1 is verified on
 // the launch stream (one launch per piece, its own count slot, started once
 // its piece's copy is done), so copies and kernels overlap.  A batch of one
-// piece is copied straight from the caller's buffer.  The counts of a batch
-// come back in one copy, then each piece's passing pairs.
+// piece goes through such a buffer in one copy, a small one straight from the
+// caller's (613,000 pairs: 260 us straight, 228 in parts of 2 MiB, each of which
+// costs a copy's start, 213 in one).  The counts of a batch come
+// back first, with the first pairs of a single piece, then what else passes.
 int verify_host(ssj_ctx* ctx, const ssj_coll* coll, const ssj_coll* coll_s, const ssj_pair* cand,
                 int64_t n_cand, int sim, int64_t t_num, int64_t t_den, ssj_pair* out, int64_t out_cap,
                 int64_t* out_n) {
@@ -2106,20 +2087,34 @@ int verify_host(ssj_ctx* ctx, const ssj_coll* coll, const ssj_coll* coll_s, cons
         HIP_OR_FAIL(ctx, grow(ctx->d_cand, ctx->cand_cap, (size_t)n));
         HIP_OR_FAIL(ctx, grow(ctx->d_out, ctx->out_cap, (size_t)n));
         const int64_t pieces = (n + kRingPiece - 1) / kRingPiece;  // <= kMaxPieces
+        int64_t early = 0;  // pairs that come with the counts
         if (pieces == 1) {
-            // nothing to overlap: one copy straight from the caller's buffer
-            HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->d_cand, cand + done, (size_t)n * sizeof(int2),
-                                            hipMemcpyHostToDevice, st));
-            Req r{ctx->d_cand, n, t_num, t_den, ctx->d_out, n, ctx->d_counts, sim};
+            const int2* from = reinterpret_cast<const int2*>(cand + done);
+            const int slot = (int)(ctx->ring_seq & 1u);
+            const bool staged = n >= kRingLeast;
+            if (staged) {
+                ++ctx->ring_seq;
+                HIP_OR_FAIL(ctx, hipEventSynchronize(ctx->ring_ev[slot]));
+                ctx->copies.copy(ctx->h_ring[slot], from, (size_t)n * sizeof(int2));
+                from = ctx->h_ring[slot];
+            }
+            HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->d_cand, from, (size_t)n * sizeof(int2), hipMemcpyHostToDevice, st));
+            if (staged) HIP_OR_FAIL(ctx, hipEventRecord(ctx->ring_ev[slot], st));
+            // (the launch stores its count in pinned memory)
+            Req r{ctx->d_cand, n, t_num, t_den, ctx->d_out, n, ctx->h_counts, sim};
             rc = enqueue_launch(ctx, coll, ctx->def, &r, 1, st, ctx->plan, true, coll_s);
             if (rc != SSJ_OK) return rc;
+            early = std::min<int64_t>({kEarlyPairs, out_cap - std::min(out_cap, total), n});
+            if (early > 0)
+                HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_early, ctx->d_out, (size_t)early * sizeof(int2),
+                                                hipMemcpyDeviceToHost, st));
         }
         for (int64_t k = 0; k < pieces && pieces > 1; ++k) {
             const int64_t off = k * kRingPiece, m = std::min(kRingPiece, n - off);
             const int slot = (int)(ctx->ring_seq++ & 1u);
             // the copy out of this buffer issued two pieces ago has finished
             HIP_OR_FAIL(ctx, hipEventSynchronize(ctx->ring_ev[slot]));
-            host_copy(ctx->h_ring[slot], cand + done + off, (size_t)m * sizeof(int2));
+            ctx->copies.copy(ctx->h_ring[slot], cand + done + off, (size_t)m * sizeof(int2));
             HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->d_cand + off, ctx->h_ring[slot], (size_t)m * sizeof(int2),
                                             hipMemcpyHostToDevice, ctx->copy_stream));
             // the event both releases the pinned buffer to the host (two
@@ -2130,20 +2125,26 @@ int verify_host(ssj_ctx* ctx, const ssj_coll* coll, const ssj_coll* coll_s, cons
             rc = enqueue_launch(ctx, coll, ctx->def, &r, 1, st, ctx->plan, true, coll_s);
             if (rc != SSJ_OK) return rc;
         }
-        HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_counts, ctx->d_counts, sizeof(long long) * (size_t)pieces,
-                                        hipMemcpyDeviceToHost, st));
+        if (pieces > 1)
+            HIP_OR_FAIL(ctx, hipMemcpyAsync(ctx->h_counts, ctx->d_counts, sizeof(long long) * (size_t)pieces,
+                                            hipMemcpyDeviceToHost, st));
         HIP_OR_FAIL(ctx, hipStreamSynchronize(st));
         for (int64_t k = 0; k < pieces; ++k) bad_id |= ctx->h_counts[k] < 0;
         if (bad_id) break;
+        bool rest = false;
         for (int64_t k = 0; k < pieces; ++k) {
             const long long c = ctx->h_counts[k];
             const int64_t take = std::min<int64_t>(std::max<int64_t>(0, out_cap - total), c);
-            if (take > 0)
-                HIP_OR_FAIL(ctx, hipMemcpyAsync(out + total, ctx->d_out + k * kRingPiece, (size_t)take * sizeof(int2),
-                                                hipMemcpyDeviceToHost, st));
+            const int64_t have = std::min(early, take);
+            if (have > 0) std::memcpy(out + total, ctx->h_early, (size_t)have * sizeof(int2));
+            if (take > have) {
+                HIP_OR_FAIL(ctx, hipMemcpyAsync(out + total + have, ctx->d_out + k * kRingPiece + have,
+                                                (size_t)(take - have) * sizeof(int2), hipMemcpyDeviceToHost, st));
+                rest = true;
+            }
             total += c;
         }
-        HIP_OR_FAIL(ctx, hipStreamSynchronize(st));
+        if (rest) HIP_OR_FAIL(ctx, hipStreamSynchronize(st));
         done += n;
     }
     if (bad_id) {
@@ -2551,7 +2552,7 @@ int ssj_stream_submit_sim(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* ca
         }
         r->h_cand = (int2*)p;
     }
-    if (n_cand > 0) std::memcpy(r->h_cand, cand, (size_t)n_cand * 8);
+    if (n_cand > 0) ctx->copies.copy(r->h_cand, cand, (size_t)n_cand * 8);
     lk.lock();
     --E->reserved;
     E->table.emplace(r->ticket, r);
