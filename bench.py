@@ -148,8 +148,9 @@ def kernel_source_hash():
 
 
 def kernel_name_of(plan):
-    """The verification kernels a plan runs (as rocprofv3 names their instances,
-    flat launches)."""
+    """The verification kernels a plan names for a flat launch: lanes, hard lanes,
+    deferral, the Cosine rule, the window ring, groups.  (The launch drops what
+    its sets cannot need; long sets are queued for the deferred kernel.)"""
     deferred = plan.defer_from < 5 or plan.spill_iters > 0
     tf = lambda v: "true" if v else "false"  # noqa: E731
     first = (f"k_verify_tiles<{plan.inline_lanes},{plan.hard_lanes},{tf(deferred)},false,"

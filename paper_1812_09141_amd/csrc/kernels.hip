@@ -618,13 +618,14 @@ __device__ __forceinline__ bool merge_ring(const int32_t* __restrict__ tok_a, ui
     }
 }
 
-// Thread-per-pair verification of the lane's pair (chunk index kb + lane)
-// from its records: first the head tiles (head_tiles); a pair they leave
-// undecided continues from that merge state.  F == 0: it
-// continues in the same lane over 16-byte windows of the token array
-// (merge_windows).  F > 0: it is appended, with
-// its merge state, to the wavefront's list of hard pairs (hcnt entries), which
-// groups of F lanes finish (finish_hard), so that no lane walks the token
+// Thread-per-pair verification of the lane's pair (candidate k of request r)
+// from its set records: first the head tiles (head_tiles); a pair they leave
+// undecided continues from that merge state.  M == kWide: it is queued for the
+// deferred kernel.  F == 0: it continues in the same lane over 16-byte windows
+// of the token array (merge_windows, or with M == kRing merge_ring, its loads
+// two steps ahead through the wavefront's window ring).  F > 0: it is appended,
+// with its merge state, to the wavefront's list of hard pairs (hcnt entries),
+// which groups of F lanes finish (finish_hard), so that no lane walks the token
 // array alone while the rest of its wavefront waits.
 template <int F, bool C, int M, bool GR>
 __device__ __forceinline__ void chunk_thread_pairs(const LaunchArgs& a, const Request& R, int r,
@@ -942,11 +943,10 @@ __device__ __forceinline__ void walk(const LaunchArgs& a, uint32_t first, uint32
 // ---------------------------------------------------------------------------
 // In-order kernel.  Every wavefront takes chunks of kWave consecutive pairs
 // of one request, grid-stride over all wavefronts of the grid.  G == 1: a
-// lane per pair.  G > 1: 64/G pairs at a time, G lanes each.  D: whether
-// the instance can defer length classes (an instance without that code needs
-// fewer registers).  S (G == 1, F == 0): merges through the window ring
-// (merge_ring).  GR: a grouped launch (every request's candidates read in
-// place from its groups and s ids).
+// lane per pair (walk).  G > 1: 64/G pairs at a time, G lanes each.  D: whether
+// the instance can queue pairs for the deferred kernel (an instance without
+// that code needs fewer registers).  M: the Mode (G == 1).  GR: a grouped
+// launch (every request's candidates read in place from its groups and s ids).
 template <int G, int F, bool D, bool C, int M, bool GR>
 __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     constexpr int GPW = kWave / G;
