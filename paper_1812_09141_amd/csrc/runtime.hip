@@ -572,7 +572,7 @@ bool wide_launch(const ssj_plan& plan, const ssj_coll* coll, const ssj_coll* cs,
     if (plan.inline_lanes != 1 || !coll->d_wide || !cs->d_wide) return false;
     const double mean = ((double)coll->n_tokens / (double)coll->n_sets + (double)cs->n_tokens / (double)cs->n_sets) / 2;
     const bool grouped = reqs[0].grouped;
-    uint64_t all = 1;
+    uint64_t all = 0;
     for (int r = 0; r < n_req; ++r) {
         ssj::Request R{};
         overlap_rule(reqs[r].sim, reqs[r].t_num, reqs[r].t_den, coll->max_len, cs->max_len, R);
@@ -582,10 +582,16 @@ bool wide_launch(const ssj_plan& plan, const ssj_coll* coll, const ssj_coll* cs,
         if (share < 0.5) return false;
         all += (uint64_t)std::max<int64_t>(reqs[r].n, 0);
     }
+    all = std::max<uint64_t>(all, 1);
     const uint64_t words = (uint64_t)ssj::kQueues * all;
     if (sc.d_queues && sc.q_cap >= words && (!grouped || (sc.d_probes && sc.probes_cap >= all))) return true;
+    if (!sc.resume) return false;  // (only the context's own scratch grows here)
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return false;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    if (cap != hipStreamCaptureStatusNone) return false;
     hipError_t e = grow(sc.d_queues, sc.q_cap, (size_t)words);
     if (e == hipSuccess && grouped) e = grow(sc.d_probes, sc.probes_cap, (size_t)all);
     if (e != hipSuccess) (void)hipGetLastError();

@@ -249,3 +249,43 @@ def test_small_grouped_launches_with_and_without_a_pre_pass(S, ctx, n_groups, n_
     finally:
         S.ssj_set_plan(ctx, S.make_plan())
         S.ssj_free_collection(ctx, h)
+
+
+def test_wide_signatures_at_the_scratch_of_the_allocation_free_call(S):
+    """SSJ_NOALLOC_MAX_PAIRS pairs of long sets, whose queue then fills that
+    call's scratch exactly, under a plan that queues nothing by itself; and a
+    context that has never grown a queue, on a captured stream."""
+    import torch
+    rng = np.random.default_rng(12)
+    base = np.sort(rng.choice(5000, 90, replace=False))
+    sets = [np.sort(np.r_[rng.choice(base, 80, replace=False), 5000 + i]).tolist() if i % 2 else
+            np.sort(rng.choice(5000, 80, replace=False)).tolist() for i in range(200)]
+    c = synth.collection_from_sets(sorted(sets, key=len))
+    n = 1 << 20
+    cand = rng.integers(0, c.n_sets, (n, 2)).astype(np.int32)
+    want = oracle.select(c.offsets, c.tokens, cand, 7, 10).shape[0]
+    assert 0 < want < n
+    ctx = S.ssj_init(0)
+    try:
+        S.ssj_set_plan(ctx, S.make_plan(inline_lanes=1, defer_from=5))
+        h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+        d = torch.from_numpy(cand).cuda()
+        count = torch.zeros(1, dtype=torch.int64, device="cuda:0")
+        S.ssj_verify_device_noalloc(ctx, h, d, 7, 10, None, count)
+        torch.cuda.synchronize()
+        assert int(count) == want
+        g, st = torch.cuda.CUDAGraph(), torch.cuda.Stream()
+        with torch.cuda.graph(g, stream=st):
+            S.ssj_verify_device(ctx, h, d, 7, 10, None, count, stream=st)
+        for _ in range(3):
+            count.zero_()
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            assert int(count) == want
+        S.ssj_verify_device(ctx, h, d, 7, 10, None, count)
+        torch.cuda.synchronize()
+        assert int(count) == want
+        del g
+    finally:
+        S.ssj_shutdown(ctx)
