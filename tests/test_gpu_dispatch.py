@@ -289,3 +289,43 @@ def test_wide_signatures_at_the_scratch_of_the_allocation_free_call(S):
         del g
     finally:
         S.ssj_shutdown(ctx)
+
+
+@pytest.mark.parametrize("n", [1, 64 * 4, 64 * 4 + 1, 128 * 4 * 64 - 64, 128 * 4 * 64, 128 * 4 * 64 + 1])
+def test_the_end_of_small_launches(S, ctx, n):
+    """Launches of one request and of five, with pairs and with counts alone,
+    around the grid up to which a workgroup ends with one atomic per request;
+    an id out of range is the error of its request alone, and leaves nothing."""
+    import torch
+    rng = np.random.default_rng(n)
+    c = synth.collection_from_sets([np.sort(rng.choice(30, k, replace=False)).tolist() for k in np.sort(rng.integers(2, 15, 200))])
+    sizes = [n, 0, max(1, n // 3), 65, n - n // 3]
+    cands = [rng.integers(0, c.n_sets, (k, 2)).astype(np.int32) for k in sizes]
+    want = [oracle.sort_pairs(oracle.select(c.offsets, c.tokens, k, 1, 2)) for k in cands]
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        for plan in [dict(inline_lanes=1, defer_from=5), dict(inline_lanes=8, defer_from=5)]:
+            S.ssj_set_plan(ctx, S.make_plan(**plan))
+            for some in ([0], [0, 1, 2], [4, 3, 2, 1, 0], [3, 3, 3, 3]):
+                for bad in (None, 0, len(some) - 1, None):
+                    d_cand, out, count = [], [], []
+                    for at, k in enumerate(some):
+                        x = cands[k].copy()
+                        if at == bad and len(x):
+                            x[-1, 1] = c.n_sets
+                        d_cand.append(torch.from_numpy(x).cuda())
+                        out.append(torch.empty((max(len(x), 1), 2), dtype=torch.int32, device="cuda:0") if at % 2 == 0 else None)
+                        count.append(torch.full((1,), -7, dtype=torch.int64, device="cuda:0"))
+                    S.ssj_verify_batch_device(ctx, h, [(a, 1, 2, o, m) for a, o, m in zip(d_cand, out, count)])
+                    torch.cuda.synchronize()
+                    for at, k in enumerate(some):
+                        m = int(count[at])
+                        if at == bad and len(cands[k]):
+                            assert m == -1
+                        else:
+                            assert m == len(want[k]), (plan, some, bad, at)
+                            if out[at] is not None:
+                                assert np.array_equal(oracle.sort_pairs(out[at][:m].cpu().numpy()), want[k])
+    finally:
+        S.ssj_set_plan(ctx, S.make_plan())
+        S.ssj_free_collection(ctx, h)
