@@ -180,6 +180,7 @@ def test_signatures_keep_every_similar_pair(S, ctx, n, most):
     c = synth.collection_from_sets(sorted(sets, key=len))
     r, s = np.tril_indices(c.n_sets, 0)
     cand = np.stack([r, s], axis=1).astype(np.int32)
+    cand = np.tile(cand, (1 + 33_000 // cand.shape[0], 1))  # more chunks than launches without signatures have
     h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
     try:
         for plan in [{}, dict(inline_lanes=1, defer_from=5), dict(defer_from=5, spill_iters=2), dict(defer_from=5, staged=1),
@@ -207,6 +208,7 @@ def test_signatures_of_two_collections(S, ctx, n_r, n_s):
         return [np.sort(rng.choice(base if i % 2 else 400, min(n, n_s if i % 2 else 400), replace=False)).tolist() for i in range(k)]
     cr, cs = (synth.collection_from_sets(sorted(x, key=len)) for x in (some(n_r, 40), some(n_s, 50)))
     cand = np.stack(np.meshgrid(np.arange(40), np.arange(50)), axis=-1).reshape(-1, 2).astype(np.int32)
+    cand = np.tile(cand, (17, 1))
     hr, hs = (S.ssj_upload_collection(ctx, c.offsets, c.tokens) for c in (cr, cs))
     try:
         for sim, a, b in [("jaccard", 1, 4), ("jaccard", 2, 5), ("jaccard", 7, 10), ("cosine", 3, 5), ("dice", 3, 5), ("overlap", 9, 1)]:
