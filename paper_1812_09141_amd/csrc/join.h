@@ -20,6 +20,7 @@ struct alignas(128) JoinCtl {
     unsigned int spilled;          // merges cut off by the step budget
     unsigned int drained;          // workgroups of k_join_drain that have finished
     unsigned int pad[2];
+    unsigned long long pieces;     // of join_pieces, which the host zeroes
     struct alignas(128) {
         unsigned long long sum;    // meetings << 16, plus the workgroups that counted them
         unsigned int extra;        // units in the extra list of this number
@@ -32,14 +33,23 @@ constexpr uint32_t kSortBits = 10;                           // most bits per pa
 constexpr uint32_t kLut = 1024;                              // coarse index of the set sizes
 constexpr uint32_t kSpillCap = 1u << 18;                     // cut-off merges that are queued
 
-// Whether a probe pass over m prefix entries with this many meetings is one
-// that a join takes.  Besides the meetings it bounds those of a walk over whole
-// lists in pieces of 64 entries: the sets of a list of n entries whose sizes
-// differ by less than the factor t all meet, so with sizes in at most groups
-// such groups the list has n^2 / (2 groups) - n / 2 meetings at least, and whole
-// lists have groups (meets + m / 2) entries at most.
-__host__ __device__ inline bool join_fits(unsigned long long meets, uint32_t groups, uint32_t m) {
-    return meets <= kMaxMeets && (unsigned long long)m + groups * (meets + m / 2ull) / 64ull < 0x80000000ull;
+// Whether a join with this many meetings is one that the probe kernel takes.
+// Host and kernels decide by this alone; m prefix entries have m (m - 1) / 2
+// meetings at most.
+__host__ __device__ inline bool join_fits(unsigned long long meets) { return meets <= kMaxMeets; }
+
+// A join is refused where its lists, each entry's part below it cut into pieces
+// of 64 entries, have 2^31 pieces or more (the work items of the candidates'
+// path).  Upper bounds of the pieces: a list of n entries has n + n^2 / 128 at
+// most and no more entries than there are sets; and the sets of a list whose
+// sizes differ by less than the factor t all meet, so with sizes in at most
+// groups such groups it has n^2 / (2 groups) - n / 2 meetings at least.
+constexpr unsigned long long kMaxPieces = 1ull << 31;
+__host__ inline unsigned long long pieces_of_entries(unsigned long long m, unsigned long long n_sets) {
+    return m + m * (m < n_sets ? m : n_sets) / 128ull + 1ull;
+}
+__host__ inline unsigned long long pieces_of_meetings(unsigned long long meets, uint32_t groups, unsigned long long m) {
+    return m + groups * (meets + m / 2ull) / 64ull + 1ull;
 }
 
 // Work units besides the first of every group of 64 entries that a join of m
@@ -67,7 +77,6 @@ struct JoinArgs {
     uint4* cls;           // n_classes + 1: {first entry, first set, size, entries per set}
     uint4* cls2;          // n_classes: {first token's index, first entry of the sets met, division by the
                           // entries per set: multiplier and shifts}
-    uint32_t size_groups; // groups of sizes within the factor t (1 where whole lists are walked)
     uint32_t* lut;        // kLut
     unsigned long long num, den;  // t
     Request req;          // overlap rule, output (out, cap, d_count)
@@ -92,8 +101,11 @@ struct JoinArgs {
 // once it has finished.  With d_temp null it only sets *temp_bytes to the temporary storage
 // it needs.
 hipError_t join_index(const JoinArgs& a, void* d_temp, size_t* temp_bytes, int n_cu, hipStream_t st);
-// Probes, verification, count (nothing but the count -1 where the totals do
+// Probes, verification, count (nothing but the count -1 where the meetings do
 // not fit join_fits).
 hipError_t join_probe(const JoinArgs& a, int n_cu, hipStream_t st);
+// Adds the pieces of 64 entries of all lists that join_index has made to
+// a.ctl->pieces.
+hipError_t join_pieces(const JoinArgs& a, int n_cu, hipStream_t st);
 
 }  // namespace ssj

@@ -537,7 +537,7 @@ __global__ __launch_bounds__(kBlock) void k_join_probe(JoinArgs a) {
     int2* w_out = s_out + wl * kStage;
     uint2* queue = s_queue + wl * kQueue;
     uint32_t* marks = s_marks + wl * kWave;
-    if (!join_fits(load_agent(&a.ctl->meets) >> 16, a.size_groups, a.m)) return;
+    if (!join_fits(load_agent(&a.ctl->meets) >> 16)) return;
     const uint32_t n_groups = (a.m + kWave - 1u) / kWave;
     const uint32_t wave = (uint32_t)__builtin_amdgcn_readfirstlane((int)(blockIdx.x * kWaves + wl));
     // extra units of each list (lane k: list k), and up to its end
@@ -713,7 +713,7 @@ __global__ __launch_bounds__(kDrainBlock) void k_join_drain(JoinArgs a) {
     memory_wait();
     __syncthreads();
     if (threadIdx.x != 0 || atomicAdd(&a.ctl->drained, 1u) != gridDim.x - 1u) return;
-    const bool fits = join_fits(load_agent(&a.ctl->meets) >> 16, a.size_groups, a.m);
+    const bool fits = join_fits(load_agent(&a.ctl->meets) >> 16);
     *a.req.d_count = fits ? (long long)load_agent(&a.ctl->out_count) : -1ll;
     a.ctl->meets = a.ctl->out_count = 0ull;
     a.ctl->spilled = a.ctl->drained = 0u;
@@ -721,6 +721,33 @@ __global__ __launch_bounds__(kDrainBlock) void k_join_drain(JoinArgs a) {
         a.ctl->slot[k].sum = 0ull;
         a.ctl->slot[k].extra = 0u;
     }
+}
+
+// The pieces of every list, counted by the thread at its last entry: entry
+// number k of a list has ceil(k / 64), at least one.  Run only where bounds of
+// their number do not settle whether the join is refused.
+__global__ __launch_bounds__(kBlock) void k_join_pieces(JoinArgs a, const uint2* __restrict__ list) {
+    __shared__ unsigned long long s_sum;
+    if (threadIdx.x == 0) s_sum = 0ull;
+    __syncthreads();
+    unsigned long long sum = 0ull;
+    for (uint32_t q = blockIdx.x * kBlock + threadIdx.x; q < a.m; q += gridDim.x * kBlock) {
+        const uint32_t w = list[q].x;
+        if (q + 1u < a.m && list[q + 1u].x == w) continue;
+        uint32_t lo = 0, hi = q;  // the list's first entry
+        while (lo < hi) {
+            const uint32_t mid = lo + (hi - lo) / 2u;
+            if (list[mid].x < w)
+                lo = mid + 1u;
+            else
+                hi = mid;
+        }
+        const unsigned long long full = (q - lo) / 64u, rest = (q - lo) % 64u;
+        sum += 1ull + 32ull * full * (full + 1ull) + rest * (full + 1ull);
+    }
+    atomicAdd(&s_sum, sum);
+    __syncthreads();
+    if (threadIdx.x == 0) atomicAdd(&a.ctl->pieces, s_sum);
 }
 
 }  // namespace
@@ -788,6 +815,13 @@ hipError_t join_probe(const JoinArgs& a, int n_cu, hipStream_t st) {
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_join_drain, dim3((unsigned)n_cu), dim3(kDrainBlock), 0, st, a);
+    return hipGetLastError();
+}
+
+hipError_t join_pieces(const JoinArgs& a, int n_cu, hipStream_t st) {
+    const uint2* list = a.pairs[(join_passes(a.key_bits) - 1u) & 1u];
+    const uint32_t b = (a.m + kBlock - 1u) / kBlock, most = 8u * (uint32_t)n_cu;
+    hipLaunchKernelGGL(k_join_pieces, dim3(b < most ? b : most), dim3(kBlock), 0, st, a, list);
     return hipGetLastError();
 }
 

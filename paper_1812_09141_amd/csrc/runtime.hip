@@ -1802,8 +1802,9 @@ int gpu_candidates(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_
 // in d_out and their number in d_count.  *done: whether it was run; a join
 // whose probes meet more list entries than that path takes is left to the
 // general one (candidates, then verification), which refuses what is too
-// large.  The host waits for the totals only (and not at all where the number
-// of prefix entries alone bounds them); the probes run meanwhile.  With d_out
+// large, and so is one that it refuses for its lists.  The host waits for the
+// meetings only (and not at all where the number of prefix entries alone bounds
+// them); the probes run meanwhile.  With d_out
 // null the pairs go to ctx->d_out, grown to hold them (out_cap at most).
 // ctx->mu held.
 int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, int2* d_out, int64_t out_cap,
@@ -1880,14 +1881,6 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     a.spill_o = J.spill_o;
     a.ctl = J.ctl;
     a.h_meets = J.h_meets;
-    // sizes 1 .. max_len in groups that differ by less than the factor t (at
-    // most as many as there are sizes)
-    a.size_groups = 1;
-    if (n_classes) {
-        const double f = (double)t_num / (double)t_den;
-        const double g = f < 1.0 ? std::log((double)coll->max_len) / -std::log(f) + 2.0 : (double)n_classes;
-        a.size_groups = (uint32_t)std::min(g, (double)n_classes);
-    }
     size_t tb = 0;
     HIP_OR_FAIL(ctx, ssj::join_index(a, nullptr, &tb, ctx->n_cu, st));
     HIP_OR_FAIL(ctx, grow(J.temp, J.temp_cap, std::max<size_t>(tb, 1)));
@@ -1895,7 +1888,7 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     HIP_OR_FAIL(ctx, ssj::join_index(a, J.temp, &tb, ctx->n_cu, st));
     // m (m - 1) / 2 meetings at most
     const uint64_t most = m64 * (m64 - 1) / 2;
-    const bool bounded = most <= ssj::kMaxMeets;
+    const bool bounded = ssj::join_fits(most);
     bool waited = bounded;
     if (!bounded) HIP_OR_FAIL(ctx, hipEventRecord(J.ev, st));
     if (!d_out && out_cap > 0) {
@@ -1913,7 +1906,22 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     }
     HIP_OR_FAIL(ctx, ssj::join_probe(a, ctx->n_cu, st));
     if (!waited) HIP_OR_FAIL(ctx, hipEventSynchronize(J.ev));
-    *done = bounded || ssj::join_fits(*J.h_meets, a.size_groups, a.m);
+    *done = bounded || ssj::join_fits(*J.h_meets);
+    if (!*done || ssj::pieces_of_entries(m64, (uint64_t)coll->n_sets) < ssj::kMaxPieces) return SSJ_OK;
+    // sizes 1 .. max_len in groups that differ by less than the factor t (at
+    // most as many as there are sizes; one where whole lists are walked)
+    uint32_t groups = 1;
+    if (n_classes) {
+        const double f = (double)t_num / (double)t_den;
+        const double g = f < 1.0 ? std::log((double)coll->max_len) / -std::log(f) + 2.0 : (double)n_classes;
+        groups = (uint32_t)std::min(g, (double)n_classes);
+    }
+    if (ssj::pieces_of_meetings(*J.h_meets, groups, m64) < ssj::kMaxPieces) return SSJ_OK;
+    HIP_OR_FAIL(ctx, hipMemsetAsync(&J.ctl->pieces, 0, sizeof(J.ctl->pieces), st));
+    HIP_OR_FAIL(ctx, ssj::join_pieces(a, ctx->n_cu, st));
+    HIP_OR_FAIL(ctx, hipMemcpyAsync(J.h_meets, &J.ctl->pieces, sizeof(J.ctl->pieces), hipMemcpyDeviceToHost, st));
+    HIP_OR_FAIL(ctx, hipStreamSynchronize(st));
+    *done = *J.h_meets < ssj::kMaxPieces;  // (the candidates' path refuses it)
     return SSJ_OK;
 }
 
