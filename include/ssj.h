@@ -156,7 +156,10 @@ int ssj_verify_sim(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* cand, int
  * Synchronous argument errors (bad threshold, negative sizes, n_cand >= 2^31)
  * return SSJ_EINVAL without enqueuing anything.  Calls that share a context
  * share its device scratch: they must be ordered on one stream (or
- * otherwise serialised) by the caller.
+ * otherwise serialised) by the caller.  A call captured into a graph allocates
+ * nothing where an earlier one of the same size and plan has made room; of the
+ * context's scratch the graph holds what the plan itself uses (nothing that
+ * grows for a plan that queues nothing and cuts no merges off).
  */
 int ssj_verify_device(ssj_ctx* ctx, const ssj_coll* coll, const ssj_pair* d_cand,
                       int64_t n_cand, int64_t t_num, int64_t t_den, ssj_pair* d_out,

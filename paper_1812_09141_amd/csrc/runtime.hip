@@ -563,10 +563,23 @@ int plan_mode(const ssj_plan& plan, const ssj_coll* coll, const ssj_coll* cs, bo
     return plan.staged && !grouped && coll->d_wide && cs->d_wide ? ssj::kRing : ssj::kNarrow;
 }
 
+// Whether work enqueued on st is being captured into a graph (or cannot be told).
+bool capturing(hipStream_t st) {
+    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
+        (void)hipGetLastError();
+        return true;
+    }
+    return cap != hipStreamCaptureStatusNone;
+}
+
 // Whether a launch of all pairs takes the wide signatures: both collections
 // have them, the plan has a lane per pair, every request asks two sets of mean
-// size to share half of it, and there are queues for the pairs that they leave.  (Memory that is short, or a stream being captured, which
-// rules out an allocation, leaves the launch to the plan.)
+// size to share half of it, and there are queues for the pairs that they leave.
+// A stream being captured rules out an allocation, and the context's own queues
+// where the plan would use none: a later call may replace them, and a replay
+// would write to what was freed.  (Such a launch, or one for which memory is
+// short, is left to the plan.)
 bool wide_launch(const ssj_plan& plan, const ssj_coll* coll, const ssj_coll* cs, Scratch& sc, const Req* reqs,
                  int n_req, hipStream_t st) {
     if (plan.inline_lanes != 1 || !coll->d_wide || !cs->d_wide) return false;
@@ -584,14 +597,11 @@ bool wide_launch(const ssj_plan& plan, const ssj_coll* coll, const ssj_coll* cs,
     }
     all = std::max<uint64_t>(all, 1);
     const uint64_t words = (uint64_t)ssj::kQueues * all;
-    if (sc.d_queues && sc.q_cap >= words && (!grouped || (sc.d_probes && sc.probes_cap >= all))) return true;
+    const bool have = sc.d_queues && sc.q_cap >= words && (!grouped || (sc.d_probes && sc.probes_cap >= all));
+    if (have && (!sc.resume || plan_two_kernels(plan_for(plan, coll->max_len, cs->max_len, false)))) return true;
     if (!sc.resume) return false;  // (only the context's own scratch grows here)
-    hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-    if (hipStreamIsCapturing(st, &cap) != hipSuccess) {
-        (void)hipGetLastError();
-        return false;
-    }
-    if (cap != hipStreamCaptureStatusNone) return false;
+    if (capturing(st)) return false;
+    if (have) return true;
     hipError_t e = grow(sc.d_queues, sc.q_cap, (size_t)words);
     if (e == hipSuccess && grouped) e = grow(sc.d_probes, sc.probes_cap, (size_t)all);
     if (e != hipSuccess) (void)hipGetLastError();
@@ -667,7 +677,8 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     if (two) {
         HIP_OR_FAIL(ctx, grow(sc.d_queues, sc.q_cap, (size_t)ssj::kQueues * std::max<uint64_t>(pairs, 1)));
     }
-    if (two && sc.resume && ssj::spilling(a) && !wide) {
+    // (a captured launch makes no room for states: its merges restart)
+    if (two && sc.resume && ssj::spilling(a) && !wide && (sc.spill_cap >= std::max<uint64_t>(pairs, 1) || !capturing(st))) {
         HIP_OR_FAIL(ctx, grow(sc.d_spill, sc.spill_cap, (size_t)std::max<uint64_t>(pairs, 1)));
         a.spill_state = sc.d_spill;
     }
