@@ -285,8 +285,9 @@ int ssj_verify_groups_batch_device(ssj_ctx* ctx, const ssj_coll* coll_r, const s
  * verification.  ssj_candidates_device synchronises the stream three times to
  * size its buffers (the prefix index, the probe work items and the candidate
  * count), ssj_join_device waits once, for the number of entries met, or not
- * at all where the sets have at most 65,536 prefix tokens together.  All
- * three share the context's device scratch.
+ * at all where the sets have at most 65,536 prefix tokens together.  Neither
+ * can be captured into a graph (ssj_join_device: SSJ_EINVAL, nothing is
+ * enqueued).  All three share the context's device scratch.
  */
 int ssj_candidates_device(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den,
                           int positional, ssj_pair* d_out, int64_t out_cap, int64_t* d_count,

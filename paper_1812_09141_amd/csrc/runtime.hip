@@ -1973,6 +1973,8 @@ int ssj_join_device(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t
     std::lock_guard<std::mutex> g(ctx->mu);
     HIP_OR_FAIL(ctx, hipSetDevice(ctx->device));
     hipStream_t st = (hipStream_t)hip_stream;
+    // (it may wait for its totals, and its scratch grows with later joins)
+    if (coll->n_sets > 0 && capturing(st)) return set_error(SSJ_EINVAL, "a join cannot be captured into a graph");
     bool done = false;
     if ((rc = gpu_join(ctx, coll, t_num, t_den, reinterpret_cast<int2*>(d_out), out_cap,
                        reinterpret_cast<long long*>(d_count), st, &done)) != SSJ_OK || done)

@@ -155,3 +155,35 @@ def test_a_budget_plan_captured_without_its_states(S):
     finally:
         g.close()
         S.ssj_shutdown(ctx)
+
+
+def test_joins_are_not_captured(S):
+    """A join small enough to run without waiting for its totals, with all its
+    scratch made, is refused on a stream being captured; nothing is enqueued and
+    the context goes on."""
+    import torch
+    c = synth.near_duplicate_collection(np.random.default_rng(3), n_base=100, copies=3, max_size=20, universe=300)
+    ctx = S.ssj_init(0)
+    g = Graph()
+    try:
+        h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+        n = torch.zeros(1, dtype=torch.int64, device="cuda:0")
+        S.ssj_join_device(ctx, h, 7, 10, True, None, n)
+        torch.cuda.synchronize()
+        want = int(n)
+        assert want > 0
+
+        def call(stream):
+            with pytest.raises(S.SsjError) as e:
+                S.ssj_join_device(ctx, h, 7, 10, True, None, n, stream=stream)
+            assert e.value.code == S.SSJ_EINVAL
+
+        g.capture(call)
+        assert g.nodes() == 0
+        n.zero_()
+        S.ssj_join_device(ctx, h, 7, 10, True, None, n)
+        torch.cuda.synchronize()
+        assert int(n) == want
+    finally:
+        g.close()
+        S.ssj_shutdown(ctx)
