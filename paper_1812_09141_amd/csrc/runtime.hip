@@ -300,18 +300,30 @@ struct ssj_ctx {
                range_cap = 0;
     } flt;
     // the whole self-join on the GPU (join.h), grown to the largest one
-    struct {
-        uint32_t *pre = nullptr, *keys = nullptr, *counts = nullptr, *lut = nullptr, *lo = nullptr, *at = nullptr,
-                 *spill_o = nullptr;
-        uint4 *cls = nullptr, *cls2 = nullptr, *ent = nullptr, *sent = nullptr, *spill = nullptr;
-        uint2 *pairs0 = nullptr, *pairs1 = nullptr, *extra = nullptr;
-        unsigned char* temp = nullptr;
-        size_t pre_cap = 0, keys_cap = 0, counts_cap = 0, lut_cap = 0, lo_cap = 0, at_cap = 0, spill_o_cap = 0, cls_cap = 0,
-               cls2_cap = 0, pairs0_cap = 0, pairs1_cap = 0, ent_cap = 0, sent_cap = 0, spill_cap = 0, extra_cap = 0,
-               temp_cap = 0;
+    struct Join {
+        template <class T>
+        struct Buffer {
+            T* p = nullptr;
+            size_t cap = 0;
+        };
+        Buffer<uint32_t> pre, keys, counts, lut, lo, at, spill_o;
+        Buffer<uint4> cls, cls2, ent, sent, spill;
+        Buffer<uint2> pairs0, pairs1, extra;
+        Buffer<unsigned char> temp;
         ssj::JoinCtl* ctl = nullptr;                 // zero between joins
         unsigned long long* h_meets = nullptr;       // pinned
         hipEvent_t ev = nullptr;                     // the number of meetings is on the host
+        // frees the buffers (no work that uses them may be left)
+        void release() {
+            auto drop = [](auto& b) {
+                if (b.p) (void)hipFree(b.p);
+                b.p = nullptr;
+                b.cap = 0;
+            };
+            drop(pre), drop(keys), drop(counts), drop(lut), drop(lo), drop(at), drop(spill_o);
+            drop(cls), drop(cls2), drop(ent), drop(sent), drop(spill);
+            drop(pairs0), drop(pairs1), drop(extra), drop(temp);
+        }
     } join;
     std::atomic<bool> failed{false};
     std::vector<ssj_coll*> colls;
@@ -1333,12 +1345,8 @@ int ssj_shutdown(ssj_ctx* ctx) {
                         (void*)ctx->flt.keys2, (void*)ctx->flt.probes, (void*)ctx->flt.temp,
                         (void*)ctx->flt.items, (void*)ctx->flt.istart, (void*)ctx->flt.range})
             if (q) (void)hipFree(q);
-        for (void* q : {(void*)ctx->join.pre, (void*)ctx->join.keys, (void*)ctx->join.counts, (void*)ctx->join.lut,
-                        (void*)ctx->join.lo, (void*)ctx->join.at, (void*)ctx->join.spill_o, (void*)ctx->join.cls, (void*)ctx->join.cls2,
-                        (void*)ctx->join.pairs0, (void*)ctx->join.pairs1, (void*)ctx->join.ent,
-                        (void*)ctx->join.sent, (void*)ctx->join.spill, (void*)ctx->join.extra,
-                        (void*)ctx->join.temp, (void*)ctx->join.ctl})
-            if (q) (void)hipFree(q);
+        ctx->join.release();
+        if (ctx->join.ctl) (void)hipFree(ctx->join.ctl);
         if (ctx->join.h_meets) (void)hipHostFree(ctx->join.h_meets);
         if (ctx->h_early) (void)hipHostFree(ctx->h_early);
         if (ctx->join.ev) (void)hipEventDestroy(ctx->join.ev);
@@ -1813,9 +1821,10 @@ int gpu_candidates(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_
 // in d_out and their number in d_count.  *done: whether it was run; a join
 // whose probes meet more list entries than that path takes is left to the
 // general one (candidates, then verification), which refuses what is too
-// large, and so is one that it refuses for its lists.  The host waits for the
-// meetings only (and not at all where the number of prefix entries alone bounds
-// them); the probes run meanwhile.  With d_out
+// large, and so is one that it refuses for its lists, and one for whose scratch
+// or pairs device memory is too short (its buffers are released then).  The host
+// waits for the meetings only (and not at all where the number of prefix entries
+// alone bounds them); the probes run meanwhile.  With d_out
 // null the pairs go to ctx->d_out, grown to hold them (out_cap at most).
 // ctx->mu held.
 int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, int2* d_out, int64_t out_cap,
@@ -1827,11 +1836,21 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
         m64 += (s.first - ((uint64_t)t_num * s.first + (uint64_t)t_den - 1) / (uint64_t)t_den + 1) * s.second;
     if (coll->n_sets == 0 || m64 >= (1ull << 30)) return SSJ_OK;
     const size_t m = (size_t)m64;
+    // whether memory is too short for this join (then its buffers are released)
+    auto short_of = [&](hipError_t e) {
+        if (e != hipErrorOutOfMemory) return false;
+        (void)hipGetLastError();
+        (void)hipDeviceSynchronize();
+        J.release();
+        return true;
+    };
+    if (!J.h_meets) HIP_OR_FAIL(ctx, hipHostMalloc((void**)&J.h_meets, sizeof(unsigned long long), hipHostMallocDefault));
+    if (!J.ev) HIP_OR_FAIL(ctx, hipEventCreateWithFlags(&J.ev, hipEventDisableTiming));
     if (!J.ctl) {
-        HIP_OR_FAIL(ctx, hipHostMalloc((void**)&J.h_meets, sizeof(unsigned long long), hipHostMallocDefault));
-        HIP_OR_FAIL(ctx, hipEventCreateWithFlags(&J.ev, hipEventDisableTiming));
         ssj::JoinCtl* ctl = nullptr;
-        HIP_OR_FAIL(ctx, hipMalloc((void**)&ctl, sizeof(ssj::JoinCtl)));
+        const hipError_t e = hipMalloc((void**)&ctl, sizeof(ssj::JoinCtl));
+        if (short_of(e)) return SSJ_OK;
+        HIP_OR_FAIL(ctx, e);
         J.ctl = ctl;
         HIP_OR_FAIL(ctx, hipMemset(J.ctl, 0, sizeof(ssj::JoinCtl)));
         HIP_OR_FAIL(ctx, hipDeviceSynchronize());
@@ -1841,26 +1860,36 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     a.key_bits = 1;
     while (a.key_bits < 32 && (coll->max_token >> a.key_bits) != 0) ++a.key_bits;
     const size_t digits = (size_t)1 << std::min(a.key_bits, ssj::kSortBits);
-    if (n_classes) {
-        HIP_OR_FAIL(ctx, grow(J.cls, J.cls_cap, (size_t)n_classes + 1));
-        HIP_OR_FAIL(ctx, grow(J.cls2, J.cls2_cap, n_classes));
-        HIP_OR_FAIL(ctx, grow(J.lut, J.lut_cap, ssj::kLut));
-    } else {
-        HIP_OR_FAIL(ctx, grow(J.pre, J.pre_cap, (size_t)coll->n_sets + 1));
-        HIP_OR_FAIL(ctx, grow(J.ent, J.ent_cap, m));
-    }
-    HIP_OR_FAIL(ctx, grow(J.keys, J.keys_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.pairs0, J.pairs0_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.pairs1, J.pairs1_cap, m));
-    // the digit counts per tile, then the digit totals
-    HIP_OR_FAIL(ctx, grow(J.counts, J.counts_cap, digits * ((size_t)ssj::join_tiles((uint32_t)m) + 1)));
-    HIP_OR_FAIL(ctx, grow(J.sent, J.sent_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.at, J.at_cap, m));
-    HIP_OR_FAIL(ctx, grow(J.lo, J.lo_cap, m));
     a.extra_cap = ssj::join_extra_cap((uint32_t)m);
-    HIP_OR_FAIL(ctx, grow(J.extra, J.extra_cap, (size_t)ssj::kExtraLists * a.extra_cap));
-    HIP_OR_FAIL(ctx, grow(J.spill, J.spill_cap, ssj::kSpillCap));
-    HIP_OR_FAIL(ctx, grow(J.spill_o, J.spill_o_cap, ssj::kSpillCap));
+    auto room = [&]() -> hipError_t {
+        hipError_t e = hipSuccess;
+        auto get = [&](auto& b, size_t need) {
+            if (e == hipSuccess) e = grow(b.p, b.cap, need);
+        };
+        if (n_classes) {
+            get(J.cls, (size_t)n_classes + 1);
+            get(J.cls2, n_classes);
+            get(J.lut, ssj::kLut);
+        } else {
+            get(J.pre, (size_t)coll->n_sets + 1);
+            get(J.ent, m);
+        }
+        get(J.keys, m);
+        get(J.pairs0, m);
+        get(J.pairs1, m);
+        // the digit counts per tile, then the digit totals
+        get(J.counts, digits * ((size_t)ssj::join_tiles((uint32_t)m) + 1));
+        get(J.sent, m);
+        get(J.at, m);
+        get(J.lo, m);
+        get(J.extra, (size_t)ssj::kExtraLists * a.extra_cap);
+        get(J.spill, ssj::kSpillCap);
+        get(J.spill_o, ssj::kSpillCap);
+        return e;
+    };
+    hipError_t e = room();
+    if (short_of(e)) return SSJ_OK;
+    HIP_OR_FAIL(ctx, e);
     a.heads = coll->d_heads;
     a.tok = coll->d_tok;
     a.n = (uint32_t)coll->n_sets;
@@ -1874,29 +1903,31 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
     a.classes = coll->d_classes;
     a.n_classes = n_classes;
     while (((a.m - 1u) >> a.lut_shift) >= ssj::kLut) ++a.lut_shift;
-    a.cls = J.cls;
-    a.cls2 = J.cls2;
-    a.lut = J.lut;
-    a.pre = J.pre;
-    a.ent = J.ent;
-    a.keys = J.keys;
-    a.pairs[0] = J.pairs0;
-    a.pairs[1] = J.pairs1;
-    a.totals = J.counts;
-    a.counts = J.counts + digits;
-    a.sent = J.sent;
-    a.at = J.at;
-    a.lo = J.lo;
-    a.extra = J.extra;
-    a.spill = J.spill;
-    a.spill_o = J.spill_o;
+    a.cls = J.cls.p;
+    a.cls2 = J.cls2.p;
+    a.lut = J.lut.p;
+    a.pre = J.pre.p;
+    a.ent = J.ent.p;
+    a.keys = J.keys.p;
+    a.pairs[0] = J.pairs0.p;
+    a.pairs[1] = J.pairs1.p;
+    a.totals = J.counts.p;
+    a.counts = J.counts.p + digits;
+    a.sent = J.sent.p;
+    a.at = J.at.p;
+    a.lo = J.lo.p;
+    a.extra = J.extra.p;
+    a.spill = J.spill.p;
+    a.spill_o = J.spill_o.p;
     a.ctl = J.ctl;
     a.h_meets = J.h_meets;
     size_t tb = 0;
     HIP_OR_FAIL(ctx, ssj::join_index(a, nullptr, &tb, ctx->n_cu, st));
-    HIP_OR_FAIL(ctx, grow(J.temp, J.temp_cap, std::max<size_t>(tb, 1)));
-    tb = J.temp_cap;
-    HIP_OR_FAIL(ctx, ssj::join_index(a, J.temp, &tb, ctx->n_cu, st));
+    e = grow(J.temp.p, J.temp.cap, std::max<size_t>(tb, 1));
+    if (short_of(e)) return SSJ_OK;
+    HIP_OR_FAIL(ctx, e);
+    tb = J.temp.cap;
+    HIP_OR_FAIL(ctx, ssj::join_index(a, J.temp.p, &tb, ctx->n_cu, st));
     // m (m - 1) / 2 meetings at most
     const uint64_t most = m64 * (m64 - 1) / 2;
     const bool bounded = ssj::join_fits(most);
@@ -1911,7 +1942,16 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
             waited = true;
             want = std::min<uint64_t>(want, std::min<uint64_t>(std::max<uint64_t>(*J.h_meets, 1), ssj::kMaxMeets));
         }
-        HIP_OR_FAIL(ctx, grow(ctx->d_out, ctx->out_cap, (size_t)want));
+        e = grow(ctx->d_out, ctx->out_cap, (size_t)want);
+        if (e == hipErrorOutOfMemory) {
+            // (a probe that stores nothing returns the counters to zero)
+            (void)hipGetLastError();
+            a.req.cap = 0;
+            HIP_OR_FAIL(ctx, ssj::join_probe(a, ctx->n_cu, st));
+            short_of(e);
+            return SSJ_OK;
+        }
+        HIP_OR_FAIL(ctx, e);
         a.req.out = ctx->d_out;
         a.req.cap = want;
     }

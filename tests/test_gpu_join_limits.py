@@ -141,3 +141,38 @@ def test_prefixes_that_too_many_sets_share_are_refused(S, ctx):
                 assert S.ssj_join(ctx, h, 1, 1).shape[0] == want
         finally:
             S.ssj_free_collection(ctx, h)
+
+
+def test_short_device_memory_leaves_a_join_to_the_candidates(S):
+    """45,000 sets that share their first token, sizes in no order, and an output
+    for as many pairs as they meet, with 4 GiB of the device left: neither 8 GiB
+    for the 1.0e9 meetings' pairs nor a failure; with memory the same result."""
+    import torch
+    rng = np.random.default_rng(32)
+    n = 45_000
+    sizes = rng.integers(2, 42, n)
+    kind = rng.integers(0, 400, n)  # equal size and kind: equal sets
+    off = np.zeros(n + 1, dtype=np.int64)
+    np.cumsum(sizes, out=off[1:])
+    at = np.arange(off[-1]) - np.repeat(off[:-1], sizes)
+    tok = np.where(at == 0, 0, np.repeat(1 + 100 * kind, sizes) + at)
+    _, c = np.unique(sizes * 1000 + kind, return_counts=True)
+    want = int((c.astype(np.int64) * (c - 1) // 2).sum())
+    ctx = S.ssj_init(0)
+    try:
+        h = S.ssj_upload_collection(ctx, off, tok.astype(np.int32))
+        torch.cuda.empty_cache()
+        rest = torch.empty(torch.cuda.mem_get_info()[0] - (4 << 30), dtype=torch.uint8, device="cuda:0")
+        got = S.ssj_join(ctx, h, 1, 1, out_cap=1 << 30)
+        assert got.shape[0] == want
+        del rest
+        torch.cuda.empty_cache()
+        again = S.ssj_join(ctx, h, 1, 1, out_cap=1 << 30)
+        key = [np.sort(x[:, 0].astype(np.int64) << 32 | x[:, 1]) for x in (got, again)]
+        assert np.array_equal(*key)
+        for x in key[:1]:
+            assert (x[1:] != x[:-1]).all()
+        assert (sizes[got[:, 0]] == sizes[got[:, 1]]).all() and (kind[got[:, 0]] == kind[got[:, 1]]).all()
+        assert S.ssj_join(ctx, h, 1, 1).shape[0] == want
+    finally:
+        S.ssj_shutdown(ctx)
