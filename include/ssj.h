@@ -69,7 +69,9 @@ typedef struct {
                              the candidate chunks of each call and their
                              worst-case output (the paper's M_c, Sec. 3.3.1):
                              collections must fit it together, and what they
-                             leave bounds the chunks; 0 selects 4 GiB */
+                             leave bounds the chunks; a collection's
+                             signatures count too, but no collection is refused
+                             for them (ssj_upload_collection); 0 selects 4 GiB */
     int n_slots;          /* concurrent stream requests on the device (0 -> 4) */
     int queue_depth;      /* stream requests accepted but not yet admitted (0 -> 64) */
 } ssj_opts;
@@ -97,8 +99,15 @@ const char* ssj_last_error(ssj_ctx* ctx);
  * The device copy is the token array (each set padded to a multiple of 4
  * tokens) plus a 32-byte record per set.  SSJ_ENOMEM when that copy and the
  * context's resident collections together exceed hbm_budget (nothing is
- * uploaded then).  The handle is valid until ssj_free_collection /
- * ssj_shutdown.  (The paper transfers each collection once, Sec. 3.3.1.)
+ * uploaded then).  Beside it, where all collections' such data take no more
+ * than half of the budget that the collections leave, the device holds
+ * signatures of 16 bytes per set (80 where sets have more than 40 tokens on
+ * average) and, for sets in ascending size, 16 bytes per size that occurs;
+ * verification and joins are slower without.  They count as taken from the
+ * budget; where a later collection takes that part, half of what is left is
+ * the candidate chunks' all the same.  The handle is valid until
+ * ssj_free_collection / ssj_shutdown.  (The paper transfers each collection
+ * once, Sec. 3.3.1.)
  */
 int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
                           const int32_t* tokens, int64_t n_tokens, ssj_coll** out);

@@ -227,13 +227,13 @@ struct ssj_coll {
     uint4* d_heads = nullptr;  // 32-byte record per set: start, len, first tokens
     uint4* d_narrow = nullptr;  // signatures of the sets (in d_heads' allocation; null where
     uint4* d_wide = nullptr;    // memory was too short, d_wide also where sets are not long)
-    const uint4* d_classes = nullptr;  // with size_sorted, after the records: per set size {first set, size,
-                                       // start of its tokens}, then {n_sets}
+    const uint4* d_classes = nullptr;  // with ascending set sizes, after the records (unless memory was too short):
+                                       // per set size {first set, size, start of its tokens}, then {n_sets}
     int64_t n_sets = 0;
     int64_t n_tokens = 0;
     int64_t max_len = 0;
     uint64_t dev_bytes = 0;  // device bytes of its tokens and set records
-    bool size_sorted = true;   // set sizes do not decrease with the id
+    uint64_t aid_bytes = 0;  // and of its signatures and table of sizes
     uint32_t max_token = 0;
     std::vector<std::pair<uint32_t, uint32_t>> sizes;  // set sizes that occur, with the number of sets
     mutable std::atomic<int> inflight{0};  // stream requests not yet finished
@@ -247,6 +247,7 @@ struct ssj_ctx {
     std::string tune_cache;   // tuning cache file ("" = none)
     uint64_t budget = kDefaultBudget;
     std::atomic<uint64_t> resident{0};  // device bytes of the uploaded collections (within budget)
+    std::atomic<uint64_t> aids{0};      // and of their signatures and tables of sizes
     int n_slots = 4;
     int queue_depth = 64;
     int n_cu = 0;
@@ -744,10 +745,15 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     return SSJ_OK;
 }
 
-// Budget bytes left for candidate buffers next to the resident collections.
+// Budget bytes left for candidate buffers next to the resident collections and
+// their signatures and tables of sizes.  Those are made only where they take no
+// more than half of what the collections leave (ssj_upload_collection); later
+// collections are not refused for them and may take that, so half of what is
+// left then is always the candidates'.
 uint64_t free_budget(const ssj_ctx* ctx) {
-    const uint64_t r = ctx->resident.load();
-    return r < ctx->budget ? ctx->budget - r : 0u;
+    const uint64_t r = ctx->resident.load(), x = ctx->aids.load();
+    const uint64_t left = r < ctx->budget ? ctx->budget - r : 0u;
+    return left - std::min(x, left / 2u);
 }
 
 int check_ctx(ssj_ctx* ctx) {
@@ -1458,7 +1464,6 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
     c->n_sets = n_sets;
     c->n_tokens = n_tokens;
     c->max_len = max_len;
-    c->size_sorted = size_sorted;
     c->max_token = (uint32_t)max_token;
     c->sizes = std::move(sizes);
     int64_t* d_off = nullptr;
@@ -1467,20 +1472,28 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
     do {
         if ((e = hipMalloc((void**)&c->d_tok, padded.size() * 4)) != hipSuccess) break;
         const size_t n_rec = (size_t)std::max<int64_t>(n_sets, 1) * 2;
-        const size_t n_narrow = n_rec / 2 * ssj::kNarrowUnits;
+        // signatures and the table of sizes, as many of them as half of what the
+        // budget leaves, and the device, have room for
+        const size_t n_classes = classes.size(), n_narrow = n_rec / 2 * ssj::kNarrowUnits;
         const size_t n_wide = n_tokens > n_sets * kWideMean ? n_rec / 2 * ssj::kWideUnits : 0;
-        if (hipMalloc((void**)&c->d_heads, (n_rec + classes.size() + n_narrow + n_wide) * sizeof(uint4)) == hipSuccess) {
-            c->d_narrow = c->d_heads + n_rec + classes.size();
-            if (n_wide) c->d_wide = c->d_narrow + n_narrow;
-        } else {
-            (void)hipGetLastError();
-            if ((e = hipMalloc((void**)&c->d_heads, (n_rec + classes.size()) * sizeof(uint4))) != hipSuccess) break;
+        const uint64_t room = (ctx->budget - ctx->resident.load() - bytes) / 2u, taken = ctx->aids.load();
+        for (size_t n : {n_classes + n_narrow + n_wide, n_classes + n_narrow, n_classes, (size_t)0}) {
+            if (n != 0 && taken + n * sizeof(uint4) > room) continue;
+            if ((e = hipMalloc((void**)&c->d_heads, (n_rec + n) * sizeof(uint4))) != hipSuccess) {
+                if (e != hipErrorOutOfMemory || n == 0) break;
+                (void)hipGetLastError();
+                continue;
+            }
+            c->aid_bytes = n * sizeof(uint4);
+            if (n >= n_classes && n_classes != 0) c->d_classes = c->d_heads + n_rec;
+            if (n >= n_classes + n_narrow) c->d_narrow = c->d_heads + n_rec + n_classes;
+            if (n > n_classes + n_narrow) c->d_wide = c->d_narrow + n_narrow;
+            break;
         }
-        if (!classes.empty()) {
-            c->d_classes = c->d_heads + n_rec;
-            if ((e = hipMemcpyAsync(c->d_heads + n_rec, classes.data(), classes.size() * sizeof(uint4),
-                                    hipMemcpyHostToDevice, ctx->stream)) != hipSuccess) break;
-        }
+        if (e != hipSuccess) break;
+        if (c->d_classes &&
+            (e = hipMemcpyAsync(c->d_heads + n_rec, classes.data(), n_classes * sizeof(uint4), hipMemcpyHostToDevice,
+                                ctx->stream)) != hipSuccess) break;
         if ((e = hipMalloc((void**)&d_off, (size_t)(n_sets + 1) * 8)) != hipSuccess) break;
         if ((e = hipMalloc((void**)&d_start, start.size() * 4)) != hipSuccess) break;
         if ((e = hipMemcpyAsync(c->d_tok, padded.data(), padded.size() * 4, hipMemcpyHostToDevice, ctx->stream)) != hipSuccess) break;
@@ -1505,6 +1518,7 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
         if (ctx->engine) ek = std::unique_lock<std::mutex>(ctx->engine->mu);
         ctx->colls.push_back(c);
         ctx->resident += bytes;
+        ctx->aids += c->aid_bytes;
     }
     *out = c;
     return SSJ_OK;
@@ -1526,6 +1540,7 @@ int ssj_free_collection(ssj_ctx* ctx, ssj_coll* coll) {
         if (it == ctx->colls.end()) return set_error(SSJ_EINVAL, "unknown collection");
         ctx->colls.erase(it);
         ctx->resident -= coll->dev_bytes;
+        ctx->aids -= coll->aid_bytes;
     }
     (void)hipSetDevice(ctx->device);
     (void)hipDeviceSynchronize();
@@ -1856,7 +1871,7 @@ int gpu_join(ssj_ctx* ctx, const ssj_coll* coll, int64_t t_num, int64_t t_den, i
         HIP_OR_FAIL(ctx, hipDeviceSynchronize());
     }
     ssj::JoinArgs a{};
-    const uint32_t n_classes = coll->size_sorted ? (uint32_t)coll->sizes.size() : 0u;
+    const uint32_t n_classes = coll->d_classes ? (uint32_t)coll->sizes.size() : 0u;
     a.key_bits = 1;
     while (a.key_bits < 32 && (coll->max_token >> a.key_bits) != 0) ++a.key_bits;
     const size_t digits = (size_t)1 << std::min(a.key_bits, ssj::kSortBits);
