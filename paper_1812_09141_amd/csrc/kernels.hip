@@ -1017,6 +1017,7 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     // pairs of the requests without an output buffer, and the wavefronts that
     // have finished
     __shared__ uint32_t s_only[kMaxReq], s_bad, s_finished, s_staged[kWaves], s_staged_req[kWaves];
+    __shared__ unsigned long long s_queued[D ? kWaves : 1];  // (dcount)
     int r_last = 0;
     if (threadIdx.x < (unsigned)kMaxReq) s_only[threadIdx.x] = 0u;
     if (threadIdx.x == 0) s_finished = s_bad = 0u;
@@ -1146,16 +1147,12 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
             }
         }
     }
-    if (deferring) {
-        for (int q = a.defer_from; q < queue_end(a); ++q) {
-            if (dcount(dc, q) > 0) wave_flush_deferred(a, q, dcount(dc, q), w_defer);
-        }
-    }
-    // the workgroup's last wavefront moves what its wavefronts have staged
-    // (one atomic for those of the same request, nearly always all), adds the
-    // counts and finishes the workgroup.  With an atomic per wavefront, 3.4M
-    // pairs that leave something staged in each of 6,144 wavefronts spent 50
-    // of 117 us on them.
+    // the workgroup's last wavefront moves what its wavefronts have queued (one
+    // atomic per queue) and staged (one for those of the same request, nearly
+    // always all), adds the counts and finishes the workgroup.  With an atomic per
+    // wavefront, 3.4M pairs that leave something staged in each of 6,144
+    // wavefronts spent 50 of 117 us on them, and 636,000 pairs of long sets of
+    // which every wavefront queues some 50-70 us, 26-33 with one per workgroup.
     if (ocnt > 0 && a.req[r_last].cap == 0) {
         if (lane == 0) atomicAdd(&s_only[r_last], ocnt);
         ocnt = 0;
@@ -1163,12 +1160,30 @@ __global__ __launch_bounds__(kBlock) void k_verify_tiles(LaunchArgs a) {
     if (lane == 0) {
         s_staged[wl] = ocnt;
         s_staged_req[wl] = (uint32_t)r_last;
+        if constexpr (D) s_queued[wl] = dc;
     }
     memory_wait();
     uint32_t fin = 0;
     if (lane == 0) fin = atomicAdd(&s_finished, 1u);
     if ((uint32_t)__builtin_amdgcn_readfirstlane((int)fin) != kWaves - 1u) return;
     wave_sync();
+    if (deferring) {
+        for (int q = a.defer_from; q < queue_end(a); ++q) {
+            uint32_t sum = 0;
+            for (uint32_t x = 0; x < kWaves; ++x) sum += dcount(s_queued[x], q);
+            if (__builtin_amdgcn_readfirstlane((int)sum) == 0) continue;
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&a.ctr->tail[q], sum);
+            uint32_t* dst = a.queues + (size_t)q * a.qcap + (uint32_t)__builtin_amdgcn_readfirstlane((int)base);
+            for (uint32_t x = 0; x < kWaves; ++x) {
+                const uint32_t c = dcount(s_queued[x], q);
+                const uint32_t* src = reinterpret_cast<const uint32_t*>(s_dyn + x * wave_words) + 2u * kWStage +
+                                      (uint32_t)(q - a.defer_from) * a.defer_cap;
+                for (uint32_t k = (uint32_t)lane; k < c; k += kWave) dst[k] = src[k];
+                dst += c;
+            }
+        }
+    }
     if (quick_end<GR>(a)) {
         // lane r: request r.  The count's address is in the arguments, in host
         // memory: one scalar load, or a vector load on its way with the atomic.
