@@ -404,8 +404,10 @@ int ssj_stream_stats(ssj_ctx* ctx, ssj_stream_stats_t* out, int reset);
  *     windows of (1), which run faster there.
  * With one thread per pair, (1) to (4) verify what the sets' signatures leave.
  * Where sets are long (more than 40 tokens on average) and every threshold of
- * a launch asks for half of a mean set or more, the second kernel verifies it
- * whatever defer_from, spill_iters and staged say.
+ * a launch asks for half of a mean set or more, it is verified so whatever
+ * defer_from, spill_iters and staged say: what the signatures leave goes to the
+ * second kernel, but for 32 and more pairs of a wavefront that are short
+ * against the launch, which the lanes merge in (1).
  * use_graph != 0 replays the launch through a captured hipGraph whose kernel
  * parameters are updated per call.  wg_per_cu sizes the in-order kernel's
  * grid (its wavefronts split the chunks evenly; more workgroups than fit at

@@ -225,7 +225,10 @@ __device__ void finish_workgroup(const LaunchArgs& a) {
     if (lane < kQueues) {
         a.ctr->tail[lane] = 0u;
     }
-    if (lane < (int)kSlots) a.ctr->slot[lane].done = 0u;
+    if (lane < (int)kSlots) {
+        a.ctr->slot[lane].done = 0u;
+        a.ctr->slot[lane].many = 0u;
+    }
     if (lane == 0) a.ctr->done = 0u;
 }
 
@@ -638,17 +641,18 @@ __device__ __forceinline__ bool merge_ring(const int32_t* __restrict__ tok_a, ui
 
 // Thread-per-pair verification of the lane's pair (candidate k of request r)
 // from its set records: first the head tiles (head_tiles); a pair they leave
-// undecided continues from that merge state.  M == kWide: it is queued for the
-// deferred kernel.  F == 0: it continues in the same lane over 16-byte windows
-// of the token array (merge_windows, or with M == kRing merge_ring, its loads
-// two steps ahead through the wavefront's window ring).  F > 0: it is appended,
+// undecided continues from that merge state.  F == 0: in the same lane over
+// 16-byte windows of the token array (merge_windows, or with M == kRing
+// merge_ring, its loads two steps ahead through the wavefront's window ring);
+// with M == kWide only up to here tokens of both sets, longer pairs are queued
+// for the deferred kernel.  F > 0: it is appended,
 // with its merge state, to the wavefront's list of hard pairs (hcnt entries),
 // which groups of F lanes finish (finish_hard), so that no lane walks the token
 // array alone while the rest of its wavefront waits.
 template <int F, bool C, int M, bool GR>
 __device__ __forceinline__ void chunk_thread_pairs(const LaunchArgs& a, const Request& R, int r,
                                                    uint32_t k, bool valid, int2 pr, const LaneRecords& rec,
-                                                   bool deferring, uint32_t* w_defer,
+                                                   bool deferring, uint32_t here, uint32_t* w_defer,
                                                    unsigned long long& dc, int2* w_out, uint32_t& ocnt,
                                                    int2* w_hpr, uint32_t* w_hst, uint32_t& hcnt, uint4* ring) {
     const int lane = lane_id();
@@ -674,7 +678,10 @@ __device__ __forceinline__ void chunk_thread_pairs(const LaunchArgs& a, const Re
     act = act && !defer;
     bool spill = false;
     if constexpr (M == kWide) {
-        spill = act;
+        spill = act && L > here;
+        bool cut = false;
+        if (act && !spill)
+            pass = merge_windows(a.tok, rec.ra0.x, na, a.tok_s, rec.rb0.x, nb, alpha, i, j, o, 0xffffffffu, &cut);
     } else if constexpr (F == 0) {
         const uint32_t budget = deferring ? a.spill_iters : 0xffffffffu;
         if constexpr (M == kRing) {
@@ -778,6 +785,24 @@ __device__ __forceinline__ void walk(const LaunchArgs& a, uint32_t first, uint32
     // two collections, one call after the other's result: 13.6 us with them, 13.1
     // without; 177,000 candidates of short sets 12.9 and 13.0).
     constexpr uint32_t kFewChunks = 512;
+    // Wide signatures: what they leave is queued, few pairs as a rule, or the long
+    // ones at the end of a list whose sets ascend.  A list most of whose pairs are
+    // similar is another matter, since a queue takes an atomic per 64 to 128 pairs
+    // and the deferred kernel 0.5 ns a pair.  So once a launch has met 2 pairs per
+    // chunk, 3%, in lists of kManyPairs and more (counted on kSlots addresses), the
+    // lanes merge such a list where it is, except for its pairs of more than a
+    // sixteenth of the launch's chunks in tokens: those a lane merges well only
+    // while the launch is long against them.  Similar pairs of 130 tokens a set:
+    // 20,000 take 48 us queued, and 82 with pairs up to 512 tokens merged here;
+    // 600,000 took 371 queued, 217 with up to 256 tokens, 188 with 512, 217 with
+    // 1,024; 4,000,000 took 2,140, 1,149, 954 and 843.  600,000 of which half are
+    // similar 250 queued, 227 with full lists merged, 156 with those of 32 pairs.
+    // Without the count the ends of lists of 620,000 pairs merged here, 70 us
+    // instead of 35.  Launches below kManyChunks queue all (their few full lists
+    // would only wait for the count: 100,000 pairs 31 us, 35 with it).
+    constexpr uint32_t kManyPairs = (uint32_t)kWave / 2u, kManyChunks = 4096;
+    const uint32_t sixteenth = n_chunks / 16u;
+    bool many = false;
     if (first >= n_chunks) return;
     const int lane = lane_id();
     const bool deferring = D && (a.defer_from < kClasses || spilling(a));
@@ -853,45 +878,59 @@ __device__ __forceinline__ void walk(const LaunchArgs& a, uint32_t first, uint32
         LaneRecords rec;
         issue_records(a, pr, rec);
         uint32_t hcnt = 0;
-        chunk_thread_pairs<F, C, M, GR>(a, R, rc, k, valid, pr, rec, deferring, w_defer, dc, w_out, ocnt, w_hpr, w_hst,
-                                        hcnt, w_ring);
+        if (M == kWide && m >= kManyPairs && !many && n_chunks >= kManyChunks) {
+            uint32_t met = 0;
+            if (lane == 0) met = atomicAdd(&a.ctr->slot[blockIdx.x % kSlots].many, m);
+            many = (uint32_t)__builtin_amdgcn_readfirstlane((int)met) >= sixteenth;
+        }
+        chunk_thread_pairs<F, C, M, GR>(a, R, rc, k, valid, pr, rec, deferring, many && m >= kManyPairs ? sixteenth : 0u,
+                                        w_defer, dc, w_out, ocnt, w_hpr, w_hst, hcnt, w_ring);
         if constexpr (F > 0)
             if (hcnt != 0u) finish_hard<F, C>(a, R, hcnt, w_hpr, w_hst, w_out, ocnt);
         wave_sync();
     };
 
-    // candidates are requested three chunks ahead, signatures one
+    // candidates are requested three chunks ahead, narrow signatures one (wide ones
+    // when they are needed: a wavefront has few such chunks, and the 64 registers
+    // of two chunks' would leave room for four wavefronts per SIMD instead of five)
     int2 p0;
     int r0, rx, ry;
     uint32_t kb0, kbx, kby;
     CandLoad cx, cy;
-    Signatures<U> qa, qb;
+    Signatures<kNarrowUnits> qa, qb;
     bool with0 = have;
     {
         CandLoad c0;
         issue(c0, r0, kb0);
         issue(cx, rx, kbx);
         p0 = resolve_cand<GR>(a, a.req[r0], kb0, lane, c0, w_marks);
-        issue_signatures<U>(sig, sig_s, with0 ? last_r : 0u, with0 ? last_s : 0u, p0, qa);
+        if constexpr (M != kWide) issue_signatures<U>(sig, sig_s, with0 ? last_r : 0u, with0 ? last_s : 0u, p0, qa);
         issue(cy, ry, kby);
     }
     uint32_t done = 0;
-    // one chunk: its signatures are in cur, the next chunk's go to nxt; c
+    // one chunk: its narrow signatures are in cur, the next chunk's go to nxt; c
     // holds the next chunk's candidates and takes those of the third one
-    auto step = [&](Signatures<U>& cur, Signatures<U>& nxt, CandLoad& c, int& rn, uint32_t& kbn) {
+    auto step = [&](Signatures<kNarrowUnits>& cur, Signatures<kNarrowUnits>& nxt, CandLoad& c, int& rn, uint32_t& kbn) {
         ++done;
         const int2 p1 = resolve_cand<GR>(a, a.req[rn], kbn, lane, c, w_marks);
         const int r1 = rn;
         const uint32_t kb1 = kbn;
         const bool with1 = have && (left8 <= 8u * kMostLeft || (done & 15u) == 0u);
-        issue_signatures<U>(sig, sig_s, with1 ? last_r : 0u, with1 ? last_s : 0u, p1, nxt);
+        if constexpr (M != kWide) issue_signatures<U>(sig, sig_s, with1 ? last_r : 0u, with1 ? last_s : 0u, p1, nxt);
         issue(c, rn, kbn);
         const bool valid = kb0 + (uint32_t)lane < n;
         const bool ok = valid && (uint32_t)p0.x < a.n_sets && (uint32_t)p0.y < a.n_sets_s;
         bad |= ballot(valid && !ok);
         bool act = ok;
         if (with0) {
-            const uint32_t na = cur.r[0].x, nb = cur.s[0].x, most = most_shared<U>(cur);
+            uint32_t na, nb, most;
+            if constexpr (M == kWide) {
+                Signatures<U> q;
+                issue_signatures<U>(sig, sig_s, last_r, last_s, p0, q);
+                na = q.r[0].x, nb = q.s[0].x, most = most_shared<U>(q);
+            } else {
+                na = cur.r[0].x, nb = cur.s[0].x, most = most_shared<U>(cur);
+            }
             if (C && cosine) {
                 // (sizes below 2^16, terms below 2^15)
                 const uint32_t x = most * den, y = num * num, z = na * nb;

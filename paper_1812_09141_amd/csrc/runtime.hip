@@ -431,11 +431,12 @@ bool plan_two_kernels(const ssj_plan& p) { return p.defer_from < ssj::kClasses |
 // Without either the launch is the in-order kernel alone, whose instance has
 // no queueing code (206 pairs of sets of about 12 tokens with a new context's
 // plan: 16.7 -> 11.1 us; with sets of 2,000 tokens both kernels run as before).
-// With wide signatures the pairs that they and the record tokens leave, few but
-// often neighbours in the list and the longest of all, go to the deferred
+// With wide signatures the pairs that they and the record tokens leave, few as a
+// rule but often neighbours in the list and the longest of all, go to the deferred
 // kernel, which spreads them over the grid: 620,000 pairs of long sets 36 us
 // whatever the plan was (merged where they are found, by groups of 32 lanes,
-// 81 us, by the lanes of the former plans 64, 103 and 296).
+// 81 us, by the lanes of the former plans 64, 103 and 296).  Where they are many,
+// the lanes that found them merge the shorter ones (walk).
 ssj_plan plan_for(const ssj_plan& plan, int64_t max_r, int64_t max_s, bool wide) {
     constexpr uint32_t bounds[ssj::kClasses] = SSJ_CLASS_BOUNDS;
     ssj_plan p = plan;

@@ -19,8 +19,8 @@ constexpr int kHeadTokens = 6;   // leading tokens kept in each 32-byte set reco
 constexpr int kNarrowUnits = 1, kWideUnits = 4;
 constexpr uint32_t signature_bits(int units) { return 32u * (4u * (uint32_t)units - 1u); }
 // Modes of the in-order kernel with a lane per pair: narrow signatures, wide
-// ones (every pair that they and the record tokens leave is queued), narrow
-// ones and merges through the window ring in LDS.
+// ones (long or few pairs that they and the record tokens leave are queued),
+// narrow ones and merges through the window ring in LDS.
 enum Mode : int { kNarrow = 0, kWide = 1, kRing = 2 };
 // Staged output pairs per wavefront (in-order kernel).
 __host__ __device__ constexpr unsigned wave_stage(int mode) { return (mode == kRing ? 4u : 6u) * kWave; }
@@ -89,6 +89,7 @@ struct alignas(256) Counters {
     unsigned int pad[63 - kMaxReq - kQueues];
     struct alignas(128) {
         unsigned int done;                  // workgroups that have finished
+        unsigned int many;                  // pairs in lists that wide signatures leave many of
     } slot[kSlots];
 };
 

@@ -331,3 +331,50 @@ def test_the_end_of_small_launches(S, ctx, n):
     finally:
         S.ssj_set_plan(ctx, S.make_plan())
         S.ssj_free_collection(ctx, h)
+
+
+@pytest.mark.parametrize("left", [0, 1, 31, 32, 33, 64])
+def test_long_sets_where_signatures_leave_many_pairs(S, ctx, left):
+    """Chunks of long sets of which left of 64 pairs are similar: lists of a few
+    pairs and of enough to be merged where they are found, pairs shorter and longer
+    than the launch merges there (a sixteenth of its chunks), results with and
+    without an output buffer, flat and grouped."""
+    import torch
+    rng = np.random.default_rng(60 + left)
+    sets, sim = [], []
+    for k in range(60):  # two similar sets of 48 tokens, now and then of 60 or 300
+        m = 300 if k % 12 == 5 else 60 if k % 4 == 3 else 48
+        base = np.sort(rng.choice(6000, m + 4, replace=False))
+        for _ in range(2):
+            sets.append(np.sort(rng.choice(base, m, replace=False)).tolist())
+    order = np.argsort([len(x) for x in sets], kind="stable")
+    where = np.empty(120, dtype=np.int64)
+    where[order] = np.arange(120)
+    c = synth.collection_from_sets([sets[i] for i in order])
+    assert c.n_tokens > 40 * c.n_sets
+    sim = np.stack([where[1::2], where[::2]], axis=1).astype(np.int32)
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        # merged where they are: none; none; up to 262 tokens; up to 625
+        for chunks in (60, 2_000, 4_200, 10_000):
+            cand = rng.integers(0, c.n_sets, (chunks, 64, 2)).astype(np.int32)
+            cand[:, :left] = sim[rng.integers(0, 60, (chunks, left))]
+            cand = cand.reshape(-1, 2)[:-7 if left == 33 else None]
+            for sim_, tn, td in [("jaccard", 7, 10), ("cosine", 4, 5)]:
+                want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, tn, td, sim=sim_))
+                assert want.shape[0] >= left * chunks * 0.9
+                for plan in [dict(), dict(defer_from=5), dict(defer_from=5, staged=1, wg_per_cu=12),
+                             dict(defer_from=4, spill_iters=32)]:
+                    S.ssj_set_plan(ctx, S.make_plan(**plan))
+                    print(f"left {left} chunks {chunks} {sim_} {plan}", flush=True)
+                    got = oracle.sort_pairs(S.ssj_verify_sim(ctx, h, cand, sim_, tn, td))
+                    assert np.array_equal(got, want)
+                    d, n = torch.from_numpy(cand).cuda(), torch.zeros(1, dtype=torch.int64, device="cuda:0")
+                    S.ssj_verify_device_sim(ctx, h, d, sim_, tn, td, None, n)
+                    assert int(n) == want.shape[0]
+                if chunks in (60, 4_200):
+                    got = oracle.sort_pairs(S.ssj_verify_groups(ctx, h, h, *S.groups_of(cand), sim_, tn, td))
+                    assert np.array_equal(got, want)
+    finally:
+        S.ssj_set_plan(ctx, S.make_plan())
+        S.ssj_free_collection(ctx, h)
