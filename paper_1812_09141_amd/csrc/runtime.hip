@@ -55,6 +55,14 @@ constexpr int kMaxDevices = 64;
 constexpr int64_t kMaxLaunchPairs = ((int64_t)1 << 31) - 1;  // pairs per launch
 constexpr int kMaxSpillIters = 1 << 20;
 constexpr int kMaxWgPerCu = 64;
+// Chunks per wavefront from which wavefronts with a lane per pair lower their
+// priority as they progress.  Long sets, whose merges take the time: 4,000,000
+// similar pairs in shares of 12 (thresholds 7/10 and 3/10) 820 -> 760 us and 475 ->
+// 437, in shares of 5 765 -> 745 and 425 -> 415; 1,200,000 in shares of 4 221 -> 232.
+// Other sets: 168M candidates of heavy-tailed sizes in shares of 214 747 -> 739,
+// 27M in shares of 80 115 -> 112; 4M in shares of 12 57 -> 59 (in shares of 5 54 ->
+// 61), 7M in shares of 20 48 -> 53.
+constexpr uint32_t kYieldLong = 5, kYieldShort = 64;
 constexpr int64_t kWideMean = 40;  // mean set size above which a collection has wide signatures
 // device bytes per candidate pair of a request: the pair, a worst-case output
 // pair, and its queue entries
@@ -346,6 +354,8 @@ struct ssj_ctx {
 };
 
 namespace {
+
+bool long_sets(const ssj_coll* c) { return c->n_tokens > c->n_sets * kWideMean; }
 
 int hip_fail(ssj_ctx* ctx, const char* what, hipError_t e) {
     if (ctx) ctx->failed = true;
@@ -688,6 +698,7 @@ int enqueue_launch(ssj_ctx* ctx, const ssj_coll* coll, Scratch& sc, const Req* r
     a.group_off[n_req] = (uint32_t)groups;
     const bool two = plan_two_kernels(plan);
     a.two_kernels = two ? 1u : 0u;
+    a.yield_share = long_sets(coll) || long_sets(cs) ? kYieldLong : kYieldShort;
     if (two) {
         HIP_OR_FAIL(ctx, grow(sc.d_queues, sc.q_cap, (size_t)ssj::kQueues * std::max<uint64_t>(pairs, 1)));
     }
@@ -1476,7 +1487,7 @@ int ssj_upload_collection(ssj_ctx* ctx, const int64_t* offsets, int64_t n_sets,
         // signatures and the table of sizes, as many of them as half of what the
         // budget leaves, and the device, have room for
         const size_t n_classes = classes.size(), n_narrow = n_rec / 2 * ssj::kNarrowUnits;
-        const size_t n_wide = n_tokens > n_sets * kWideMean ? n_rec / 2 * ssj::kWideUnits : 0;
+        const size_t n_wide = long_sets(c) ? n_rec / 2 * ssj::kWideUnits : 0;
         const uint64_t room = (ctx->budget - ctx->resident.load() - bytes) / 2u, taken = ctx->aids.load();
         for (size_t n : {n_classes + n_narrow + n_wide, n_classes + n_narrow, n_classes, (size_t)0}) {
             if (n != 0 && taken + n * sizeof(uint4) > room) continue;

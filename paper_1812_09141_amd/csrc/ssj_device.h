@@ -118,6 +118,7 @@ struct LaunchArgs {
     int spill_lanes;                     // lanes per pair of the spill queue
     int mode;                            // Mode (kNarrow if inline_lanes > 1)
     uint32_t grouped;                    // != 0: every request of the launch is grouped
+    uint32_t yield_share;                // chunks of a wavefront from which a lane per pair yields as it progresses
     uint32_t two_kernels;                // != 0: the deferred kernel follows (and publishes the counts)
     uint32_t* probes;                    // grouped launches that defer: the probe id of every
                                          // queued pair, by global pair index
