@@ -22,8 +22,14 @@ constexpr uint32_t signature_bits(int units) { return 32u * (4u * (uint32_t)unit
 // ones (long or few pairs that they and the record tokens leave are queued),
 // narrow ones and merges through the window ring in LDS.
 enum Mode : int { kNarrow = 0, kWide = 1, kRing = 2 };
-// Staged output pairs per wavefront (in-order kernel).
-__host__ __device__ constexpr unsigned wave_stage(int mode) { return (mode == kRing ? 4u : 6u) * kWave; }
+// Staged output pairs per wavefront (in-order kernel).  A flush of a wavefront's
+// pairs is an atomic on the request's counter, about 10 ns each whoever makes it,
+// so lists most of whose pairs pass are bound by the flushes: 4M such pairs of a
+// heavy tail with 6 * kWave staged 155 us, with 8 * kWave 113 (half of them passing
+// 108 and 53), of long sets in the ring with 4 * kWave 475 and with 5 * kWave 461.
+// More would take LDS that wavefronts need (the ring: four workgroups of a compute
+// unit hold 160 KB).
+__host__ __device__ constexpr unsigned wave_stage(int mode) { return (mode == kRing ? 5u : 8u) * kWave; }
 
 // How a request turns set sizes into its required overlap alpha (the
 // equivalent overlap of paper Table 1).
