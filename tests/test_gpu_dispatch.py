@@ -378,3 +378,114 @@ def test_long_sets_where_signatures_leave_many_pairs(S, ctx, left):
     finally:
         S.ssj_set_plan(ctx, S.make_plan())
         S.ssj_free_collection(ctx, h)
+
+
+def _one_kernel(S, ctx, run):
+    """Whether the launches of run have no second kernel."""
+    S.ssj_timing_enable(ctx, 1)
+    S.ssj_timing_read(ctx, reset=True)
+    try:
+        run()
+        return S.ssj_timing_read(ctx, reset=True)[1] == 0.0
+    finally:
+        S.ssj_timing_enable(ctx, 0)
+
+
+@pytest.mark.parametrize("longest", [64, 65, 256, 257])
+def test_long_class_bounds_under_the_plan(S, ctx, longest):
+    """Sets of more than 40 tokens on average at thresholds below half of them, so
+    that launches run as their plan says: the longest pair on either side of a
+    class bound (128 | 129, 512 | 513) and budgets at the longest merge."""
+    rng = np.random.default_rng(800 + longest)
+    base = np.sort(rng.choice(4 * longest, longest, replace=False))
+    sets = [np.sort(rng.choice(base, size=int(rng.integers(max(1, longest // 2), longest)), replace=False)).tolist()
+            for _ in range(100)]
+    sets += [np.sort(rng.choice(4 * longest, int(rng.integers(longest // 2, longest)), replace=False)).tolist()
+             for _ in range(50)]
+    sets += [base.tolist(), base[1:].tolist(), base.tolist()]
+    c = synth.collection_from_sets(sorted(sets, key=len))
+    assert c.n_tokens > 40 * c.n_sets
+    cand = _pairs(c.n_sets, 5000, 1)
+    cand[:3] = [[c.n_sets - 1, c.n_sets - 2], [c.n_sets - 1, c.n_sets - 3], [c.n_sets - 3, c.n_sets - 2]]
+    steps = 2 * ((longest + 3) // 4)  # window steps that no merge outruns
+    last = int(np.searchsorted([32, 128, 512, 2048], 2 * longest))  # the class of the longest pair
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        for sim, tn, td in [("jaccard", 1, 4), ("jaccard", 1, 10), ("overlap", longest // 5, 1), ("cosine", 2, 5)]:
+            want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, tn, td, sim=sim))
+            assert 0 < want.shape[0] < cand.shape[0]
+            for kw in [dict(defer_from=d, lanes=(4, 8, 16, 64, 256)) for d in range(6)] + \
+                      [dict(defer_from=5, spill_iters=s, staged=g) for s in (1, steps - 1, steps) for g in (0, 1)]:
+                print(f"longest {longest} {sim} {tn}/{td} {kw}", flush=True)
+                S.ssj_set_plan(ctx, S.make_plan(**kw))
+                got = []
+                one = _one_kernel(S, ctx, lambda: got.append(S.ssj_verify_sim(ctx, h, cand, sim, tn, td)))
+                assert np.array_equal(oracle.sort_pairs(got[0]), want)
+                assert one == (kw.get("spill_iters", 0) in (0, steps) and last < kw["defer_from"])
+    finally:
+        S.ssj_set_plan(ctx, S.make_plan())
+        S.ssj_free_collection(ctx, h)
+
+
+@pytest.mark.parametrize("t", [(3, 10), (1, 4), (1, 10)])
+def test_long_near_duplicates_under_every_plan(S, ctx, t):
+    """Thousands of passing long pairs (10 to 600 tokens) at thresholds below half
+    of a mean set: every long-set plan with its own kernel, queues and resumed
+    merges, which higher thresholds leave to the signatures' mode."""
+    from test_gpu_parity import LONG_PLANS
+    from ssj_inputs import filter as cfilter
+    rng = np.random.default_rng(31)
+    c = synth.near_duplicate_collection(rng, n_base=1500, copies=3, max_size=600, universe=1_000_000,
+                                        change_frac=0.08, min_size=10, zipf_s=0.9)
+    cand = np.concatenate([cfilter.candidates(c.offsets, c.tokens, 7, 10), _pairs(c.n_sets, 60_000, 9)])
+    want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, *t))
+    assert 1000 < want.shape[0] < cand.shape[0]
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        for name, plan in LONG_PLANS:
+            print(f"long near-dup t={t} {name} n={cand.shape[0]}", flush=True)
+            # (None: a new context's plan)
+            S.ssj_set_plan(ctx, S.make_plan(**(plan or dict(defer_from=3, lanes=(4, 16, 64, 256, 256)))))
+            got = []
+            one = _one_kernel(S, ctx, lambda: got.append(S.ssj_verify(ctx, h, cand, *t)))
+            assert np.array_equal(oracle.sort_pairs(got[0]), want), name
+            assert one == (name in ("inline-16", "inline-64", "staged")), name
+            got = oracle.sort_pairs(S.ssj_verify_groups(ctx, h, h, *S.groups_of(cand), "jaccard", *t))
+            assert np.array_equal(got, want), name
+    finally:
+        S.ssj_set_plan(ctx, S.make_plan())
+        S.ssj_free_collection(ctx, h)
+
+
+@pytest.mark.parametrize("staged", [0, 1])
+def test_batch_of_counts_and_pairs_of_long_sets(S, ctx, staged):
+    """A batch that mixes requests with and without an output buffer on sets of
+    more than 40 tokens, where a staged plan has the window ring."""
+    import torch
+    c = synth.near_duplicate_collection(np.random.default_rng(5), n_base=80, copies=4, max_size=120, min_size=50,
+                                        universe=4000)
+    assert c.n_tokens > 40 * c.n_sets
+    S.ssj_set_plan(ctx, S.make_plan(defer_from=5, staged=staged, wg_per_cu=1))
+    h = S.ssj_upload_collection(ctx, c.offsets, c.tokens)
+    try:
+        sizes = [1, 63, 64, 65, 0, 300, 5000, 200_000, 64, 1, 70_000]
+        d_cnt = torch.full((len(sizes),), -7, dtype=torch.int64, device="cuda:0")
+        reqs, want, outs = [], [], []
+        for i, n in enumerate(sizes):
+            cand = _pairs(c.n_sets, n, 40 + i)
+            tn, td = [(1, 10), (1, 4), (0, 1)][i % 3]  # at 0 every pair passes: more than are staged
+            want.append(oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, tn, td)))
+            out = None if i % 2 else torch.full((max(n, 1), 2), -1, dtype=torch.int32, device="cuda:0")
+            outs.append(out)
+            reqs.append((torch.from_numpy(cand).to("cuda:0"), tn, td, out, d_cnt[i:i + 1]))
+        for _ in range(3):
+            d_cnt.fill_(-7)
+            assert _one_kernel(S, ctx, lambda: S.ssj_verify_batch_device(ctx, h, reqs))
+            torch.cuda.synchronize()
+            for i, w in enumerate(want):
+                assert int(d_cnt[i].item()) == w.shape[0], i
+                if outs[i] is not None:
+                    assert np.array_equal(oracle.sort_pairs(outs[i][:w.shape[0]].cpu().numpy()), w), i
+    finally:
+        S.ssj_set_plan(ctx, S.make_plan())
+        S.ssj_free_collection(ctx, h)
