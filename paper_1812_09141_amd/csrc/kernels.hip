@@ -795,10 +795,12 @@ __device__ __forceinline__ void walk(const LaunchArgs& a, uint32_t first, uint32
     // with 24 here the walk took 866 us, with 40 it took 775.)
     constexpr uint32_t kMostLeft = 40;
     // Launches of so few chunks are a chain of memory round trips, to which the
-    // signatures add one; their merges run side by side (some 2,600 candidates of
-    // two collections, one call after the other's result: 13.6 us with them, 13.1
-    // without; 177,000 candidates of short sets 12.9 and 13.0).
-    constexpr uint32_t kFewChunks = 512;
+    // narrow signatures add one; their merges run side by side.  With and without
+    // them, sets of about 12 tokens: 32,000 pairs 7.5 and 7.0 us, 200,000 11.1 and
+    // 10.5; of 30 tokens 32,000 pairs 21.3 and 20.2, 100,000 25.7 and 22.8; of a
+    // heavy tail 32,000 13.1 and 12.7, 200,000 20.1 and 19.9; 2,600 pairs of two
+    // collections, one call after the other's result, 13.6 and 13.1.
+    constexpr uint32_t kFewChunks = 4096;
     // Wide signatures: what they leave is queued, few pairs as a rule, or the long
     // ones at the end of a list whose sets ascend.  A list most of whose pairs are
     // similar is another matter, since a queue takes an atomic per 64 to 128 pairs
