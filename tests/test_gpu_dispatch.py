@@ -489,3 +489,36 @@ def test_batch_of_counts_and_pairs_of_long_sets(S, ctx, staged):
     finally:
         S.ssj_set_plan(ctx, S.make_plan())
         S.ssj_free_collection(ctx, h)
+
+
+@pytest.mark.parametrize("extra", [0, 1])
+@pytest.mark.parametrize("n, most", [(1, 2**31 - 1), (3, 60), (12, 2**31 - 1), (40, 10**6)])
+def test_narrow_signatures_of_large_launches(S, ctx, n, most, extra):
+    """Pairs of every overlap in lists of 4,096 chunks, which go without narrow
+    signatures, and of one pair more, of one collection and of two, flat and grouped."""
+    sets = _similar_at(n, most, n + 50, max(1, n // 25))
+    c = synth.collection_from_sets(sorted(sets, key=len))
+    o = synth.collection_from_sets(sorted(sets[::2] + sets[:5], key=len))
+    r, s = np.tril_indices(c.n_sets, 0)
+    cand = np.stack([r, s], axis=1).astype(np.int32)
+    cand = np.resize(cand, (4096 * 64 + extra, 2))
+    cand = cand[np.argsort(cand[:, 0], kind="stable")]
+    two = np.stack([cand[:, 0], cand[:, 1] % o.n_sets], axis=1)
+    h, ho = (S.ssj_upload_collection(ctx, x.offsets, x.tokens) for x in (c, o))
+    try:
+        for sim, a, b in [("jaccard", 1, 3), ("jaccard", 7, 10), ("jaccard", 1, 1), ("dice", 1, 2), ("cosine", 1, 2),
+                          ("cosine", 49999, 100000), ("overlap", max(1, n // 2), 1), ("overlap", 2**31 - 1, 1)]:
+            want = oracle.sort_pairs(oracle.select(c.offsets, c.tokens, cand, a, b, sim=sim))
+            want2 = oracle.sort_pairs(oracle.select_rs(c.offsets, c.tokens, o.offsets, o.tokens, two, a, b, sim=sim))
+            for plan in [dict(defer_from=3, lanes=(4, 16, 64, 256, 256)), dict(defer_from=5),
+                         dict(defer_from=5, spill_iters=2), dict(defer_from=5, hard_lanes=8)]:
+                print(f"n {n} + {extra} {sim} {a}/{b} {plan}: {want.shape[0]}", flush=True)
+                S.ssj_set_plan(ctx, S.make_plan(**plan))
+                assert np.array_equal(oracle.sort_pairs(S.ssj_verify_sim(ctx, h, cand, sim, a, b)), want)
+                assert np.array_equal(oracle.sort_pairs(S.ssj_verify_rs(ctx, h, ho, two, sim, a, b)), want2)
+            got = oracle.sort_pairs(S.ssj_verify_groups(ctx, h, h, *S.groups_of(cand), sim, a, b))
+            assert np.array_equal(got, want)
+    finally:
+        S.ssj_set_plan(ctx, S.make_plan())
+        S.ssj_free_collection(ctx, h)
+        S.ssj_free_collection(ctx, ho)
