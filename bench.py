@@ -149,12 +149,27 @@ def kernel_source_hash():
 
 def kernel_name_of(plan):
     """The verification kernels a plan names for a flat launch: lanes, hard lanes,
-    deferral, the Cosine rule, the window ring, groups.  (The launch drops what
-    its sets cannot need; long sets are queued for the deferred kernel.)"""
+    deferral, the Cosine rule, the window ring, groups.  (What a launch runs
+    depends on its sets and thresholds too: launched_kernels.)"""
     deferred = plan.defer_from < 5 or plan.spill_iters > 0
     tf = lambda v: "true" if v else "false"  # noqa: E731
     first = (f"k_verify_tiles<{plan.inline_lanes},{plan.hard_lanes},{tf(deferred)},false,"
              f"{tf(plan.staged)},false>")
+    return first + (" + k_verify_deferred<false,false>" if deferred else "")
+
+
+def launched_kernels(plan, deferred, mean, thresholds):
+    """The verification kernels that a flat Jaccard launch of a plan runs, by the
+    library's rules: mean is the collection's mean set size, deferred whether a
+    second kernel ran (its measured time).  Modes of the first: 0 narrow
+    signatures, 1 wide ones (long sets whose thresholds all ask for half of a mean
+    set or more), 2 the window ring (other launches of long sets)."""
+    tf = lambda v: "true" if v else "false"  # noqa: E731
+    long_sets = mean > 40
+    wide = plan.inline_lanes == 1 and long_sets and all(2 * tn / (tn + td) >= 0.5 for tn, td in thresholds)
+    mode = 1 if wide else 2 if plan.staged and long_sets else 0
+    first = (f"k_verify_tiles<{plan.inline_lanes},{0 if wide else plan.hard_lanes},{tf(deferred)},false,"
+             f"{mode},false>")
     return first + (" + k_verify_deferred<false,false>" if deferred else "")
 
 
@@ -332,14 +347,13 @@ def measure(W, args, src_hash):
     value = W.n_pairs * args.steps / elapsed
     b_alg, b_full = W.alg_bytes()
     launches = max(launches, 1)
-    deferred = plan.defer_from < 5 or plan.spill_iters > 0
     avg_in_ms = in_ms / launches
     avg_def_ms = def_ms / launches
-    # in-order kernel alone, or with the deferred kernel when one runs (events
-    # right before and after each verification kernel)
-    avg_kernel_ms = avg_in_ms + (avg_def_ms if deferred else 0.0)
+    # in-order kernel, and the deferred kernel when one runs, whatever the plan
+    # says (events right before and after each verification kernel)
+    avg_kernel_ms = avg_in_ms + avg_def_ms
     achieved = b_alg / (avg_kernel_ms * 1e-3) / 1e9 if avg_kernel_ms > 0 else 0.0
-    kname = kernel_name_of(plan)
+    kname = launched_kernels(plan, def_ms > 0.0, W.coll.n_tokens / W.coll.n_sets, W.w.thresholds)
     traffic = traffic_from_profiles(src_hash, W.name, kname)
     rate = (lambda b: b / (avg_kernel_ms * 1e-3) / 1e9) if avg_kernel_ms > 0 else None
     rec = {
@@ -357,6 +371,10 @@ def measure(W, args, src_hash):
             "peak": PEAK_HBM_GBS,
             "unit": "GB/s",
             "frac": round(achieved / PEAK_HBM_GBS, 5),
+            # achieved and frac are a rate of work: the bytes that a merge of every
+            # pair consumes, most of which the signatures make unnecessary to read
+            "basis": "alg_bytes_per_launch / avg_kernel_ms (bytes of a merge of every pair; signatures "
+                     "reject most pairs unread: traffic_frac is the share of the HBM peak)",
             "traffic": traffic,
             # measured DRAM bytes (copy-scaled FETCH_SIZE + WRITE_SIZE of the
             # committed counters) over the same kernel time
@@ -383,8 +401,7 @@ def measure(W, args, src_hash):
             dt = timed_steps(torch, W.step, n_sw, 2)
             a_in, a_def, a_l = S.ssj_timing_read(ctx, reset=True)
             S.ssj_timing_enable(ctx, 0)
-            dfr = p.defer_from < 5 or p.spill_iters > 0
-            k_ms = (a_in + (a_def if dfr else 0.0)) / max(a_l, 1)
+            k_ms = (a_in + a_def) / max(a_l, 1)
             sweep[spec] = {"pairs_per_s": round(W.n_pairs * n_sw / dt, 1), "parity": W.check(),
                            "kernel_ms": round(k_ms, 5),
                            "frac": round(b_alg / (k_ms * 1e-3) / 1e9 / PEAK_HBM_GBS, 4) if k_ms > 0 else None}
@@ -407,7 +424,7 @@ def count_mode(W, args):
                                for i, (tn, td) in enumerate(W.w.thresholds)))}
 
 
-def buckets(W, plan):
+def buckets(W):
     """Kernel time and B_alg rate per bucket of |r| + |s| (each bucket's
     candidates alone, in their order, one launch per step)."""
     import numpy as np
@@ -415,7 +432,6 @@ def buckets(W, plan):
     bks = [W.man["thresholds"][f"{tn}/{td}"].get("buckets") for tn, td in W.w.thresholds]
     if not all(b is not None for b in bks):
         return None
-    deferred = plan.defer_from < 5 or plan.spill_iters > 0
     bounds = [b["upper_bound"] for b in bks[0][:-1]]
     per = []
     b_of = [np.searchsorted(np.asarray(bounds), W.sizes[c[:, 0]] + W.sizes[c[:, 1]], side="left") for c in W.cands]
@@ -437,7 +453,7 @@ def buckets(W, plan):
         torch.cuda.synchronize()
         q_in, q_def, q_l = S.ssj_timing_read(W.ctx, reset=True)
         S.ssj_timing_enable(W.ctx, 0)
-        q_ms = (q_in + (q_def if deferred else 0.0)) / max(q_l, 1)
+        q_ms = (q_in + q_def) / max(q_l, 1)
         ok = True
         b_q = 0
         for i, (tn, td) in enumerate(W.w.thresholds):
@@ -764,7 +780,7 @@ def main():
             rec["count_mode"] = count_mode(W, args)
             parity &= rec["count_mode"]["parity"]
         if args.buckets:
-            per = buckets(W, plan)
+            per = buckets(W)
             if per is not None:
                 rec["buckets"] = per
         if W.cfg == 2:

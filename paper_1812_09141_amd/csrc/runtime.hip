@@ -63,7 +63,11 @@ constexpr int kMaxWgPerCu = 64;
 // 27M in shares of 80 115 -> 112; 4M in shares of 12 57 -> 59 (in shares of 5 54 ->
 // 61), 7M in shares of 20 48 -> 53.
 constexpr uint32_t kYieldLong = 5, kYieldShort = 64;
-constexpr int64_t kWideMean = 40;  // mean set size above which a collection has wide signatures
+// Mean set size above which a collection has wide signatures.  Candidates of 60,000
+// sets with wide and with narrow ones, at 7/10 and at 1/2: means of 25 tokens 26 and
+// 50 us, 60 and 50; of 35 29 and 52, 73 and 71; of 40 31 and 62, 81 and 93; of 50 34
+// and 66, 99 and 191; of 80 42 and 97, 185 and 935.
+constexpr int64_t kWideMean = 40;
 // device bytes per candidate pair of a request: the pair, a worst-case output
 // pair, and its queue entries
 constexpr size_t kBytesPerPair = 8 + 8 + 4 * ssj::kQueues;
@@ -611,6 +615,10 @@ bool capturing(hipStream_t st) {
 // Whether a launch of all pairs takes the wide signatures: both collections
 // have them, the plan has a lane per pair, every request asks two sets of mean
 // size to share half of it, and there are queues for the pairs that they leave.
+// (616,000 pairs of long sets, under a plan that queues nothing, with and without:
+// at shares of 0.82 33 and 316 us, of 0.57 127 and 301, of 0.46 177 and 386, of 0.18
+// 313 and 607; a new context's plan 32 and 169, 125 and 188, 170 and 211, 312 and
+// 311.  Below half they leave more and more to the second kernel.)
 // A stream being captured rules out an allocation, and the context's own queues
 // where the plan would use none: a later call may replace them, and a replay
 // would write to what was freed.  (Such a launch, or one for which memory is

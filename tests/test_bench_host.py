@@ -89,3 +89,22 @@ def test_more_than_one_gpu_is_refused():
                        text=True, timeout=120)
     assert r.returncode == 2
     assert "one GPU" in r.stderr
+
+
+def test_launched_kernels_follow_the_sets():
+    """The kernels the bench line names are the instances that launches run: by the
+    plan, the mean set size, the thresholds and whether a second kernel ran."""
+    p = bench.plan_of(S, "inline:1w12")
+    assert bench.launched_kernels(p, False, 8.4, [(3, 4)]) == "k_verify_tiles<1,0,false,false,0,false>"
+    assert bench.launched_kernels(p, True, 130, [(7, 10)]) == \
+        "k_verify_tiles<1,0,true,false,1,false> + k_verify_deferred<false,false>"
+    assert bench.launched_kernels(p, False, 130, [(7, 10), (1, 4)]) == "k_verify_tiles<1,0,false,false,0,false>"
+    ring = bench.plan_of(S, "inline:1b")
+    assert bench.launched_kernels(ring, False, 12, [(3, 5)]) == "k_verify_tiles<1,0,false,false,0,false>"
+    assert bench.launched_kernels(ring, False, 130, [(1, 4)]) == "k_verify_tiles<1,0,false,false,2,false>"
+    assert bench.launched_kernels(ring, False, 40, [(1, 3)]) == "k_verify_tiles<1,0,false,false,0,false>"
+    hard = bench.plan_of(S, "inline:1h8")
+    assert bench.launched_kernels(hard, True, 41, [(1, 3)]).startswith("k_verify_tiles<1,0,true,false,1,false>")
+    groups = bench.plan_of(S, "defer:16,3,4,8,16,32,64")
+    assert bench.launched_kernels(groups, True, 130, [(7, 10)]) == \
+        "k_verify_tiles<16,0,true,false,0,false> + k_verify_deferred<false,false>"
